@@ -88,6 +88,10 @@ void launch_cg_coef(const Dev &, const CgArgs &, double *, double *, hipStream_t
 void launch_diff_rhs(const Dev &, const CgArgs &, double *, hipStream_t);
 void launch_cg_begin(const Dev &, const CgArgs &, const double *, hipStream_t);
 void launch_cg_iters(const Dev &, const CgArgs &, int, int, hipStream_t);
+size_t cg_solve_smem(int, int);
+hipError_t cg_solve_init(int, int, int, int, bool *);
+hipError_t launch_cg_solve(const Dev &, const CgArgs &, const CgPlan &, int, int, const double *, int, unsigned,
+                           hipStream_t);
 // Gauss-Legendre nodes/weights on [-1, 1], ascending (Newton on P_n).
 void gauss_legendre(int n, std::vector<double> &x, std::vector<double> &w)
 {
@@ -222,6 +226,13 @@ struct bte_problem {
     double *cg_x = nullptr, *cg_r = nullptr, *cg_z = nullptr, *cg_p = nullptr, *cg_Ap = nullptr;
     double *cg_w0 = nullptr, *cg_w1 = nullptr, *cg_s1 = nullptr;
     double *cg_part = nullptr, *cg_scal = nullptr;
+    // one-launch CG: blocks, cells per thread (0: launches per iteration only), ghosts
+    int cg_nblk = 0, cg_R = 0;
+    bool cg_one = false;                  // the bound device can hold every block at once
+    std::vector<unsigned short> cg_lidx;
+    std::vector<int> cg_cell, cg_gptr, cg_gid;
+    CgPlan cgplan{};
+    unsigned cg_epoch = 0;                // tags used so far
     double *din = nullptr, *part = nullptr;
     void *e2 = nullptr;
     void *psi = nullptr, *psi2 = nullptr;                       // adjoint iterates (ctl.adjoint)
@@ -795,8 +806,87 @@ void finish_materials(bte_problem *p)
     if (p->wpart.empty()) p->wpart.assign(1, -1);
 }
 
+// Words of the one-launch CG: w of every cell, block partials (two slots
+// each), and the abort word.
+size_t cg_word_count(size_t nc) { return 2 * 2 * nc + 2 * 6 * kCgMaxBlocks + 1; }
+
+// Split of the cells over the blocks of the one-launch CG.  Up to 2 048 cells
+// one block takes the problem: 1.3 us per iteration there against 2.7 us on
+// eight blocks, which wait for each other.  Beyond, the fewest cells per
+// thread that keep the grid at one block per compute unit (65 536 cells in
+// 2D: 4.0, 3.7 and 3.8 us with 1, 2 and 4; 48^3: 5.8, 7.6 and 9.4), up to
+// four (eight spill: at 1.39 M cells no faster than a launch per iteration).
+// Every face with a neighbour counts as a coupling (the couplings of
+// interfaces and of gamma-dependent fields come and go).
+void build_cg_plan(bte_problem *p)
+{
+    const int nc = p->nc, nf = 2 * p->dim;
+    int R = 0, nblk = 0;
+    for (int r : {1, 2, 4}) {
+        nblk = (nc + kCgThreads * r - 1) / (kCgThreads * r);
+        if (nc <= 2048 ? nblk == 1 : nblk <= kCgMaxBlocks) {
+            R = r;
+            break;
+        }
+    }
+    if (!R) return;
+    const int cpb = kCgThreads * R;
+    // numbers: tile by tile of every geometry
+    std::vector<int> num(nc);
+    p->cg_cell.clear();
+    for (const Film &fm : p->films) {
+        const int tx = p->dim == 1 ? fm.n[0] : p->dim == 2 ? 32 : 8, ty = p->dim == 2 ? 16 : 8, tz = 8;
+        for (int z0 = 0; z0 < fm.n[2]; z0 += tz)
+            for (int y0 = 0; y0 < fm.n[1]; y0 += ty)
+                for (int x0 = 0; x0 < fm.n[0]; x0 += tx)
+                    for (int z = z0; z < std::min(fm.n[2], z0 + tz); ++z)
+                        for (int y = y0; y < std::min(fm.n[1], y0 + ty); ++y)
+                            for (int x = x0; x < std::min(fm.n[0], x0 + tx); ++x) {
+                                const int c = fm.cell0 + x + fm.n[0] * (y + fm.n[1] * z);
+                                num[c] = (int)p->cg_cell.size();
+                                p->cg_cell.push_back(c);
+                            }
+    }
+    p->cg_lidx.assign((size_t)nf * nc, 0);
+    p->cg_gptr.assign(nblk + 1, 0);
+    std::vector<int> mark(nc, -1), place(nc, 0);   // block that holds a cell as a ghost, and where
+    std::vector<char> sent(nc, 0);
+    int most = 0;
+    for (int blk = 0; blk < nblk; ++blk) {
+        const int i0 = blk * cpb, i1 = std::min(nc, i0 + cpb);
+        const int first = (int)p->cg_gid.size();
+        for (int f = 0; f < nf; ++f)
+            for (int i = i0; i < i1; ++i) {
+                const int j = p->nb[(size_t)f * nc + p->cg_cell[i]];
+                int l = i - i0;
+                if (j >= 0 && num[j] >= i0 && num[j] < i1) {
+                    l = num[j] - i0;
+                } else if (j >= 0) {
+                    if (mark[j] != blk) {
+                        mark[j] = blk;
+                        place[j] = (int)p->cg_gid.size() - first;
+                        p->cg_gid.push_back(j);
+                        sent[num[j]] = 1;
+                    }
+                    l = cpb + place[j];
+                }
+                if (l > 0x7fff) return;   // no room in 15 bits (nor in LDS)
+                p->cg_lidx[(size_t)f * nc + i] = (unsigned short)l;
+            }
+        p->cg_gptr[blk + 1] = (int)p->cg_gid.size();
+        most = std::max(most, (int)p->cg_gid.size() - first);
+    }
+    if (cg_solve_smem(R, most) > 150 * 1024) return;
+    for (int i = 0; i < nc; ++i)
+        if (sent[i]) p->cg_lidx[i] |= 0x8000u;
+    p->cg_R = R;
+    p->cg_nblk = nblk;
+    p->cgplan.max_ghost = most;
+}
+
 void plan_workspace(bte_problem *p)
 {
+    build_cg_plan(p);
     p->layout.clear();
     size_t off = 0;
     auto add = [&](const char *name, size_t bytes) {
@@ -844,6 +934,13 @@ void plan_workspace(bte_problem *p)
     add("fdone", 4 * (size_t)p->nfilm);
     add("cg_part", 8 * 6 * (size_t)((nc + kBlock - 1) / kBlock));
     add("cg_scal", 8 * 16);
+    if (p->cg_R > 0) {
+        add("cg_cell", 4 * nc);
+        add("cg_lidx", 2 * p->cg_lidx.size());
+        add("cg_gptr", 4 * p->cg_gptr.size());
+        add("cg_gid", 4 * p->cg_gid.size());
+        add("cg_words", 8 * (size_t)cg_word_count(nc));
+    }
     add("din", 8 * (size_t)p->nw * p->nl);
     const int nchunk_stream = (p->nk + kBlock - 1) / kBlock;
     p->npart_max = std::max(nchunk_stream, p->noct * p->nchunk_oct);
@@ -1173,6 +1270,25 @@ bte_status bte_bind(bte_problem *p, void *ws, size_t bytes)
     p->d_citems = wsptr<ColItem>(p, "citems");
     p->d_wrec = wsptr<int>(p, "wrec");
     p->d_wden = wsptr<double>(p, "wden");
+    p->cg_one = false;
+    if (p->cg_R > 0) {
+        HIPCHK(p, up("cg_cell", p->cg_cell.data(), 4 * p->cg_cell.size()));
+        HIPCHK(p, up("cg_lidx", p->cg_lidx.data(), 2 * p->cg_lidx.size()));
+        HIPCHK(p, up("cg_gptr", p->cg_gptr.data(), 4 * p->cg_gptr.size()));
+        HIPCHK(p, up("cg_gid", p->cg_gid.data(), 4 * p->cg_gid.size()));
+        CgPlan &q = p->cgplan;
+        q.cell = wsptr<int>(p, "cg_cell");
+        q.lidx = wsptr<unsigned short>(p, "cg_lidx");
+        q.gptr = wsptr<int>(p, "cg_gptr");
+        q.gid = wsptr<int>(p, "cg_gid");
+        q.wword = wsptr<unsigned long long>(p, "cg_words");
+        q.pword = q.wword + 4 * (size_t)p->nc;
+        q.abortw = (unsigned *)(q.pword + 2 * 6 * kCgMaxBlocks);
+        // no word may hold a tag of a coming solve
+        HIPCHK(p, hipMemset(q.wword, 0, 8 * cg_word_count(p->nc)));
+        p->cg_epoch = 0;
+        HIPCHK(p, cg_solve_init(p->dim, p->cg_R, q.max_ghost, p->cg_nblk, &p->cg_one));
+    }
     // default fields: no source, no extra scattering
     HIPCHK(p, hipMemset(wsptr<void>(p, "zrow"), 0, 8 * 8 * (size_t)p->nk));
     HIPCHK(p, hipMemset(wsptr<void>(p, "fdone"), 0, 4 * (size_t)p->nfilm));
@@ -1245,13 +1361,20 @@ template <typename T> bte_status moments_to(bte_problem *p, const T *e, const do
 }
 
 // Jacobi-preconditioned CG on the heat-diffusion (corr = 0) or correction
-// (corr = 1) operator, two launches per iteration; b is projected per
-// floating geometry beforehand, x afterwards.  Asynchronous when maxit fits
-// one chunk of launches; the iteration count is accumulated on the device
-// (cg_scal[9]).  Returns false on a HIP error.
+// (corr = 1) operator; b is projected per floating geometry beforehand, x
+// afterwards.  Asynchronous when maxit fits one chunk of launches or `epoch`
+// is given; the iteration count is accumulated on the device (cg_scal[9]).
+// Returns false on a HIP error.
+//
+// With `epoch` the solve runs in one launch (k_cg_solve) if the problem has
+// a plan for it, and *epoch is the solve's epoch: the caller compares the
+// abort word with it after its next synchronisation and, if they are equal
+// (a wait between the blocks gave up, nothing of x is valid), calls again
+// without `epoch`.  *epoch is 0 where one launch per iteration was used.
 constexpr int kCgChunk = 64;
 
-bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int maxit, hipStream_t s)
+bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int maxit, hipStream_t s,
+            unsigned *epoch = nullptr)
 {
     const Dev &d = p->dev;
     if (p->floating_any) {
@@ -1261,17 +1384,29 @@ bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int
     CgArgs g = cg_args(p, corr);
     g.x = x_out;
     g.rtol2 = rtol * rtol;
-    // one launch per iteration, enqueued in chunks; between chunks the host
-    // reads the done flag (one synchronisation per chunk)
-    launch_cg_begin(d, g, b, s);
-    constexpr int kChunk = kCgChunk;
-    for (int it0 = 0; it0 < maxit; it0 += kChunk) {
-        launch_cg_iters(d, g, it0, std::min(kChunk, maxit - it0), s);
-        if (it0 + kChunk < maxit) {
-            double done = 0;
-            if (hipMemcpyAsync(&done, p->cg_scal + 5, 8, hipMemcpyDeviceToHost, s) != hipSuccess) return false;
-            if (hipStreamSynchronize(s) != hipSuccess) return false;
-            if (done != 0.0) break;
+    if (epoch) *epoch = 0;
+    if (epoch && p->cg_one) {
+        const unsigned need = (unsigned)maxit + 2u;
+        if (p->cg_epoch > 0xffffffffu - need) {   // tags used up: start again on cleared words
+            if (hipMemsetAsync(p->cgplan.wword, 0, 8 * cg_word_count(p->nc), s) != hipSuccess) return false;
+            p->cg_epoch = 0;
+        }
+        *epoch = p->cg_epoch + 1;
+        p->cg_epoch += need;
+        if (launch_cg_solve(d, g, p->cgplan, p->cg_nblk, p->cg_R, b, maxit, *epoch, s) != hipSuccess) return false;
+    } else {
+        // one launch per iteration, enqueued in chunks; between chunks the host
+        // reads the done flag (one synchronisation per chunk)
+        launch_cg_begin(d, g, b, s);
+        constexpr int kChunk = kCgChunk;
+        for (int it0 = 0; it0 < maxit; it0 += kChunk) {
+            launch_cg_iters(d, g, it0, std::min(kChunk, maxit - it0), s);
+            if (it0 + kChunk < maxit) {
+                double done = 0;
+                if (hipMemcpyAsync(&done, p->cg_scal + 5, 8, hipMemcpyDeviceToHost, s) != hipSuccess) return false;
+                if (hipStreamSynchronize(s) != hipSuccess) return false;
+                if (done != 0.0) break;
+            }
         }
     }
     if (p->floating_any) {
@@ -1279,6 +1414,18 @@ bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int
         launch_sub_film_mean(d, x_out, p->fmean, s);
     }
     return hipGetLastError() == hipSuccess;
+}
+
+// run_cg to its end: one launch where there is a plan, repeated with a launch
+// per iteration if its blocks gave up waiting for each other.
+bool run_cg_now(bte_problem *p, int corr, double *b, double *x_out, double rtol, int maxit, hipStream_t s)
+{
+    unsigned epoch = 0, word = 0;
+    if (!run_cg(p, corr, b, x_out, rtol, maxit, s, &epoch)) return false;
+    if (!epoch) return true;
+    if (hipMemcpyAsync(&word, p->cgplan.abortw, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return false;
+    if (hipStreamSynchronize(s) != hipSuccess) return false;
+    return word != epoch || run_cg(p, corr, b, x_out, rtol, maxit, s);
 }
 
 // A captured launch sequence, instantiated once and replayed.
@@ -1360,7 +1507,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
     if (init) {
         CgArgs g = cg_args(p, 0);
         launch_diff_rhs(d, g, p->r, s);
-        if (!run_cg(p, 0, p->r, p->T0, 1e-13, 200000, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
+        if (!run_cg_now(p, 0, p->r, p->T0, 1e-13, 200000, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
         launch_set_equilibrium<T>(d, e, p->T0, s);
         HIPCHK(p, hipMemsetAsync(p->cg_scal, 0, 8 * 16, s));   // count correction CG only
     }
@@ -1412,10 +1559,14 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
         launch_film_eps(d, p->T0, p->T1, p->q0, p->q1, p->feps, p->fpart, p->fseg, s);
         HIPCHK(p, hipEventRecord(ev[3], s));
         HIPCHK(p, hipGetLastError());
+        unsigned cg_epoch = 0;
         if (synthetic) {
-            // a CG solve without host checks (cg_max_iter <= one chunk) is a
-            // fixed launch sequence: replayed from a graph
-            if (p->graphs && p->ctl.cg_max_iter <= kCgChunk) {
+            if (p->cg_one) {
+                if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s, &cg_epoch))
+                    FAIL(p, BTE_ERR_HIP, "CG failed");
+            } else if (p->graphs && p->ctl.cg_max_iter <= kCgChunk) {
+                // a CG solve without host checks (cg_max_iter <= one chunk) is a
+                // fixed launch sequence: replayed from a graph
                 HIPCHK(p, graph_run(gcg, p->cstream, s, [&](hipStream_t q) {
                     return run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, q);
                 }));
@@ -1428,10 +1579,16 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
         }
         HIPCHK(p, hipEventRecord(ev[4], s));
         HIPCHK(p, hipMemcpyAsync(feps.data(), p->feps, 8 * feps.size(), hipMemcpyDeviceToHost, s));
-        unsigned qabort = 0;
+        unsigned qabort = 0, cg_abort = 0;
         if (reg2d(p) && p->persistent && p->queue_ok)
             HIPCHK(p, hipMemcpyAsync(&qabort, p->d_queue + 1, 4, hipMemcpyDeviceToHost, s));
+        if (cg_epoch) HIPCHK(p, hipMemcpyAsync(&cg_abort, p->cgplan.abortw, 4, hipMemcpyDeviceToHost, s));
         HIPCHK(p, hipStreamSynchronize(s));
+        if (cg_epoch && cg_abort == cg_epoch) {
+            // the blocks gave up waiting for each other: this correction again, a launch per iteration
+            if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
+            launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, s);
+        }
         if (qabort) FAIL(p, BTE_ERR_HIP, "one-launch sweep: a wait for an upwind tile gave up");
         {
             float ms[4];
@@ -1694,7 +1851,7 @@ bte_status adjoint_impl(bte_problem *p, const T *e, double *grad, bte_solve_stat
         HIPCHK(p, hipEventRecord(ev[2], s));
         if (synthetic) {
             // v = L^-1 P^T y; the sweep's isotropic term becomes X + v
-            if (!run_cg(p, 1, p->adju, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s))
+            if (!run_cg_now(p, 1, p->adju, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s))
                 FAIL(p, BTE_ERR_HIP, "CG failed");
             launch_tl_update(nc, p->adjX, p->delta, p->TL, nullptr, nullptr, nullptr, s);
             X = p->TL;

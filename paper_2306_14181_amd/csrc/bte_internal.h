@@ -125,6 +125,21 @@ struct CgArgs {
     double rtol2;
 };
 
+// One-launch CG: blocks of kCgThreads threads, each owning kCgThreads * R
+// cells.
+constexpr int kCgThreads = 512;
+constexpr int kCgMaxBlocks = 256;
+struct CgPlan {
+    const int *cell;              // [nc] the cell of each number (block b owns the numbers b cpb ..)
+    const unsigned short *lidx;   // [2 dim][nc] by number: place of the neighbour's value in the block's LDS array (own
+                                  // cells, then ghosts); bit 15 of face 0: some other block holds the cell as a ghost
+    const int *gptr, *gid;        // [nblk + 1] first ghost of a block, ghost cells
+    unsigned long long *wword;    // [2][nc][2] w of a sent cell, tagged words by iteration parity
+    unsigned long long *pword;    // [2][kCgMaxBlocks][6] partial sums of a block, likewise
+    unsigned *abortw;             // epoch of a solve whose wait gave up
+    int max_ghost;
+};
+
 // Gauss-Legendre nodes / weights on [-1, 1], ascending.
 void gauss_legendre(int n, std::vector<double> &x, std::vector<double> &w);
 // Directions and weights on the sphere (two- and three-dimensional
