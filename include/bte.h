@@ -478,8 +478,8 @@ void bte_destroy(bte_problem *p);
  * moments, R = -(1/V) sum_j v (s.n) S e_ij - (e - C T_L / 4 pi) / tau +
  * C P / (4 pi C_tot), then A de = R with A_ii = 1/tau + (1/V) sum_{s.n>0}
  * v s.n S and A_ij = -(1/V) v |s.n| S for the interior upwind neighbour j,
- * solved in per-direction upwind (dependency-graph) order, one launch per
- * level of all directions together; on a cyclic graph the smallest-index
+ * solved in per-direction upwind (dependency-graph) order, every direction
+ * and group of bands by a block of its own; on a cyclic graph the smallest-index
  * cell left is taken with its unresolved upwind couplings lagged (their
  * increments count as zero).  e layout and moments as for bte_problem:
  * e[cell][direction][band], direction-major within a cell. */
@@ -542,8 +542,8 @@ size_t bte_mesh_workspace_bytes(const bte_mesh_problem *p);
 bte_status bte_mesh_bind(bte_mesh_problem *p, void *ws_dev, size_t bytes);
 int bte_mesh_num_cells(const bte_mesh_problem *p);
 int bte_mesh_num_directions(const bte_mesh_problem *p);
-/* Level launches of one sweep (the depth of the deepest direction's
- * dependency graph) and the number of lagged couplings over all directions. */
+/* Levels of one sweep (the depth of the deepest direction's dependency
+ * graph; counted as sweep_launches in the statistics) and the number of lagged couplings over all directions. */
 int bte_mesh_num_levels(const bte_mesh_problem *p);
 int bte_mesh_num_lagged(const bte_mesh_problem *p);
 /* Heat source P per cell (device double[n_cells], W/m^3; NULL: none). */

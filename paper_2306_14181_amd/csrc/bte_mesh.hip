@@ -11,24 +11,26 @@
 // diffuse-wall records, directions, and the sweep schedule:
 // for every direction the cells' upwind dependency graph is levelled (Kahn
 // order; a cycle is broken at its smallest-index cell, whose unresolved
-// upwind couplings are lagged), and the (direction, cell) items of all
-// directions are launched level by level.
+// upwind couplings are lagged), and each direction's cells are put into steps
+// of independent items (or, where the increments in flight do not fit the
+// LDS, the items of all directions are launched level by level).
 //
 // Device: e[cell][direction][band] as for the structured grids.  One
 // iteration = moments (T_L) -> gradients -> diffuse-wall inflow ->
-// residual R -> level launches, each thread one (direction, cell, band)
+// residual R -> the sweep, per (direction, cell, band)
 // item: de = (R + sum_upwind v |s.n| S/V de_j) / (1/tau + sum_out v s.n S/V)
 // with the geometric sums and the upwind cells of the (direction, cell)
-// item precomputed on the host, the increments replacing R in place,
-// e += de.
+// item precomputed on the host, e += de.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <array>
+#include <atomic>
 #include <map>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/bte.h"
@@ -70,6 +72,25 @@ struct MeshDev {
     const double *item_out;
     const int4 *item_up;
     const double4 *item_coef;
+};
+
+// One (direction, cell) item of the per-direction sweep (k_mesh_sweep_dir).
+// A cell's faces close, so at least one lets the direction out: tetrahedra,
+// triangles and quadrilaterals have at most three upwind faces.
+struct alignas(16) MeshRec {
+    unsigned short up[3], own;   // LDS slots of the upwind increments and of the own one
+    double cf[3], out;           // |s.n| S/V of the upwind faces, sum_{s.n>0} s.n S/V
+};
+constexpr int kDirThreads = 256;
+constexpr int kDirAhead = 4;    // steps a thread's own values are loaded ahead (their cells: twice that)
+
+// Schedule of the per-direction sweep: S items per step, nb bands per block.
+struct DirPlan {
+    const int *base;       // [na] first step of a direction (in the step-major arrays)
+    const int *nstep;      // [na] its steps, padded to a multiple of kDirAhead
+    const int *cell;       // [steps][S] cell of an item, -1: none
+    const MeshRec *rec;    // [steps][S]
+    int S, nb, ng, slots;  // items per step, bands per block, blocks per direction, LDS slots (zero slot first, waste last)
 };
 
 // Lane k of a cell's row.  BUF (FP32 states below 2 GiB): one buffer
@@ -330,6 +351,127 @@ __global__ __launch_bounds__(kBlock) void k_mesh_sweep_level(MeshDev d, T *__res
     e[ck] = (T)((double)e0 + de);
 }
 
+// The whole sweep in one launch: a block takes one direction and nb of its
+// bands and walks that direction's steps, each at most S items none of which
+// waits for another.  Directions and bands do not couple inside a sweep, so no
+// block waits for another one; a launch per level of all directions (the form
+// above) cost a kernel boundary and two dependent rounds of global loads per
+// level, 4.0 us on the 27 900-cell 2D mesh (610 levels).  Here a step's chain
+// is an LDS read of the upwind increments, four FP64 multiply-adds, a division
+// and an LDS write between two barriers.  Increments stay in LDS, in slots
+// that the host gives out again after an item's last reader (a few hundred
+// live at a time, 2 000 on 48 000 tetrahedra); the residual, the energy and the item records do not
+// depend on the sweep and are loaded kDirAhead steps before their use, the
+// cells that address them kDirAhead steps earlier still.  The barrier orders
+// LDS only, so those loads stay in flight across it.  Sweep of the 2D mesh x
+// 128 directions x 20 bands FP32 2.46 -> 0.59 ms, of 48 000 tetrahedra x 96
+// directions 1.73 -> 0.89 ms; what is left is the fetch of row pieces (12
+// bands, 48 bytes of a 128-byte line) in an order of its own per direction.
+// V consecutive bands per thread.  Blocks of one octant's directions go to one
+// XCD: their rows share cache lines.
+// EA: rows of the caller's e are aligned for them (the workspace's are).
+template <typename T, int V> struct alignas(sizeof(T) * V) BandVec { T x[V]; };
+
+template <typename T, int V, bool EA> __device__ inline BandVec<T, V> band_load(const T *p)
+{
+    if constexpr (EA) return *reinterpret_cast<const BandVec<T, V> *>(p);
+    BandVec<T, V> v;
+#pragma unroll
+    for (int i = 0; i < V; ++i) v.x[i] = p[i];
+    return v;
+}
+
+template <typename T, int V, bool EA> __device__ inline void band_store(T *p, const BandVec<T, V> &v)
+{
+    if constexpr (EA)
+        *reinterpret_cast<BandVec<T, V> *>(p) = v;
+    else
+#pragma unroll
+        for (int i = 0; i < V; ++i) p[i] = v.x[i];
+}
+
+__device__ inline void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <typename T, int V, bool EA>
+__global__ __launch_bounds__(kDirThreads) void k_mesh_sweep_dir(MeshDev d, DirPlan q, T *__restrict__ e,
+                                                               const T *__restrict__ b)
+{
+    extern __shared__ __align__(16) char lds_raw[];
+    T *inc = reinterpret_cast<T *>(lds_raw);   // [slots][nb]
+    using Vec = BandVec<T, V>;
+    const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int al = x * (d.na >> 3) + j / q.ng, l0 = (j % q.ng) * q.nb;
+    const int tpi = q.nb / V;
+    const int item = threadIdx.x / tpi, off = (threadIdx.x - item * tpi) * V;
+    const bool lane = item < q.S && l0 + off < d.nl;
+    const int l = lane ? l0 + off : 0;
+    const size_t nk = (size_t)d.nk;
+    const int k0 = al * d.nl + l;
+    double vl[V], itau[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        vl[i] = d.v[l + i];
+        itau[i] = d.itau[l + i];
+    }
+    const size_t first = (size_t)q.base[al] * q.S + (lane ? item : 0);
+    const int *__restrict__ cp = q.cell + first;
+    const MeshRec *__restrict__ rp = q.rec + first;
+    const int n = q.nstep[al];
+    if ((int)threadIdx.x < q.nb) inc[threadIdx.x] = (T)0;   // slot 0: the increment of an absent coupling
+    int cell[kDirAhead], next[kDirAhead];
+    MeshRec rec[kDirAhead];
+    Vec bv[kDirAhead], ev[kDirAhead];
+#pragma unroll
+    for (int u = 0; u < kDirAhead; ++u) {
+        cell[u] = cp[(size_t)u * q.S];
+        next[u] = cp[(size_t)(u + kDirAhead) * q.S];
+        rec[u] = rp[(size_t)u * q.S];
+        const size_t at = (size_t)(cell[u] < 0 ? 0 : cell[u]) * nk + k0;
+        bv[u] = *reinterpret_cast<const Vec *>(b + at);
+        ev[u] = band_load<T, V, EA>(e + at);
+    }
+    lds_barrier();
+    // the arrays hold 2 kDirAhead steps past a direction's last
+    for (int k = 0; k < n; k += kDirAhead) {
+#pragma unroll
+        for (int u = 0; u < kDirAhead; ++u) {
+            const MeshRec r = rec[u];
+            const Vec i0 = *reinterpret_cast<const Vec *>(inc + (int)r.up[0] * q.nb + off);
+            const Vec i1 = *reinterpret_cast<const Vec *>(inc + (int)r.up[1] * q.nb + off);
+            const Vec i2 = *reinterpret_cast<const Vec *>(inc + (int)r.up[2] * q.nb + off);
+            Vec de, en;
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                double num = (double)bv[u].x[i];
+                num += vl[i] * r.cf[0] * (double)i0.x[i];
+                num += vl[i] * r.cf[1] * (double)i1.x[i];
+                num += vl[i] * r.cf[2] * (double)i2.x[i];
+                const double q0 = num / (itau[i] + vl[i] * r.out);
+                de.x[i] = (T)q0;
+                en.x[i] = (T)((double)ev[u].x[i] + q0);
+            }
+            if (lane) {
+                *reinterpret_cast<Vec *>(inc + (int)r.own * q.nb + off) = de;
+                if (cell[u] >= 0) band_store<T, V, EA>(e + (size_t)cell[u] * nk + k0, en);
+            }
+            // step k + u + kDirAhead into this place
+            const size_t s1 = (size_t)(k + u + kDirAhead);
+            cell[u] = next[u];
+            next[u] = cp[(s1 + kDirAhead) * q.S];
+            rec[u] = rp[s1 * q.S];
+            const size_t at = (size_t)(cell[u] < 0 ? 0 : cell[u]) * nk + k0;
+            bv[u] = *reinterpret_cast<const Vec *>(b + at);
+            ev[u] = band_load<T, V, EA>(e + at);
+            lds_barrier();
+        }
+    }
+}
+
 // Moments per cell: T - T_ref, T_L - T_ref and q.  A block takes
 // kMomCells cells, so that each lane's direction and band weights serve all
 // of them; wave sums by shuffles, then one pass over the block's waves.
@@ -451,6 +593,11 @@ struct bte_mesh_problem {
     // host tables
     std::vector<int> fptr, fnb, ftag, frec, tag_bc, mirror, rec_cell, rec_face, lev_off, lsptr, lsnb, vorder;
     std::vector<int> item_c, item_al;
+    // per-direction sweep (dir_V > 0): bands per thread, schedule
+    int dir_V = 0;
+    std::vector<int> dir_base, dir_nstep, dir_cell;
+    std::vector<MeshRec> dir_rec;
+    DirPlan dir{};
     std::vector<int4> item_up;
     std::vector<double4> item_coef;
     std::vector<double> fgeo, xinv, lsd, tag_dT, s, w, C4, v, itau, rec_den, item_out;
@@ -612,6 +759,165 @@ static void morton_order(const std::vector<double> &xc, int nc, int D, std::vect
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key[a] < key[b]; });
 }
 
+// Schedule of one direction: cells in level order, each in the first step
+// after its upwind cells' that has room for it; slots given out step by step
+// and taken back after the step of an item's last reader.  cells / recs:
+// steps of S, n steps padded to a multiple of kDirAhead plus 2 kDirAhead empty
+// ones (read ahead).  Returns the number of slots (0: the zero slot).
+int dir_direction(const bte_mesh_problem *p, int al, const int *level, const uint8_t *lagm, int S, int &n,
+                  std::vector<int> &cells, std::vector<MeshRec> &recs)
+{
+    const int nc = p->nc;
+    std::vector<int> order(nc), start(p->nlev + 1, 0), step(nc), room, place;
+    for (int c = 0; c < nc; ++c) ++start[level[c] + 1];
+    for (int L = 0; L < p->nlev; ++L) start[L + 1] += start[L];
+    for (int i : p->vorder) order[start[level[i]]++] = i;   // Morton order inside a level
+    std::vector<MeshRec> rec(nc);
+    std::vector<std::array<int, 3>> up(nc);
+    std::vector<int> last(nc, -1), used, skip;   // last reader's step; items per step; next step that may have room
+    auto room_at = [&](int k) {
+        while (k < (int)used.size() && used[k] >= S) {
+            if (skip[k] <= k) skip[k] = k + 1;
+            k = skip[k];
+        }
+        return k;
+    };
+    for (int c : order) {
+        MeshRec r{};
+        up[c] = {-1, -1, -1};
+        int nu = 0, k = 0;
+        for (int f = p->fptr[c]; f < p->fptr[c + 1]; ++f) {
+            const double *fg = &p->fgeo[(size_t)f * kFG];
+            const double sn = p->s[3 * al] * fg[1] + p->s[3 * al + 1] * fg[2] + p->s[3 * al + 2] * fg[3];
+            if (sn > 0) {
+                r.out += sn * fg[0];
+            } else if (sn < 0 && p->fnb[f] >= 0 && !((lagm[c] >> (f - p->fptr[c])) & 1u)) {
+                if (nu == 3) return -1;
+                up[c][nu] = p->fnb[f];
+                r.cf[nu++] = -sn * fg[0];
+                k = std::max(k, step[p->fnb[f]] + 1);
+            }
+        }
+        rec[c] = r;
+        const int k0 = k;
+        k = room_at(k);
+        if (k > k0 && k0 < (int)skip.size()) skip[k0] = std::max(skip[k0], k);
+        if (k >= (int)used.size()) {
+            used.resize(k + 1, 0);
+            skip.resize(k + 1, 0);
+        }
+        step[c] = k;
+        ++used[k];
+        for (int i = 0; i < nu; ++i) last[up[c][i]] = std::max(last[up[c][i]], k);
+    }
+    const int ns = (int)used.size();
+    n = (ns + kDirAhead - 1) / kDirAhead * kDirAhead;
+    cells.assign((size_t)(n + 2 * kDirAhead) * S, -1);
+    recs.assign((size_t)(n + 2 * kDirAhead) * S, MeshRec{});
+    std::vector<int> fill(ns, 0), slot(nc, 0), spare;
+    std::vector<std::vector<int>> back(ns + 1);   // slots free again at the start of a step
+    std::vector<std::vector<int>> at(ns);
+    for (int c : order) at[step[c]].push_back(c);
+    int slots = 1;
+    for (int k = 0; k < ns; ++k) {
+        for (int x : back[k]) spare.push_back(x);
+        for (int c : at[k]) {
+            if (last[c] >= 0) {
+                if (spare.empty()) spare.push_back(slots++);
+                slot[c] = spare.back();
+                spare.pop_back();
+                back[last[c] + 1].push_back(slot[c]);
+            } else {
+                slot[c] = -1;   // nobody reads it: the waste slot
+            }
+        }
+    }
+    if (slots + 1 > 65535) return -1;
+    for (int k = 0; k < ns; ++k)
+        for (int c : at[k]) {
+            const size_t i = (size_t)k * S + fill[k]++;
+            MeshRec r = rec[c];
+            for (int m = 0; m < 3; ++m) r.up[m] = up[c][m] >= 0 ? (unsigned short)slot[up[c][m]] : 0;
+            r.own = slot[c] >= 0 ? (unsigned short)slot[c] : 0xffff;
+            cells[i] = c;
+            recs[i] = r;
+        }
+    return slots;
+}
+
+// fn(0) .. fn(n - 1) on a few host threads; false if one of them threw.
+template <typename F> bool on_threads(int n, F &&fn)
+{
+    const int nt = std::max(1, std::min({n, 8, (int)std::thread::hardware_concurrency()}));
+    std::atomic<int> next{0};
+    std::atomic<bool> ok{true};
+    auto work = [&] {
+        for (int i; (i = next.fetch_add(1)) < n && ok;) {
+            try {
+                fn(i);
+            } catch (...) {
+                ok = false;
+            }
+        }
+    };
+    std::vector<std::thread> th;
+    try {
+        for (int i = 1; i < nt; ++i) th.emplace_back(work);
+    } catch (...) {   // fewer threads than asked for
+    }
+    work();
+    for (std::thread &t : th) t.join();
+    return ok;
+}
+
+// Per-direction sweep of the mesh: bands per thread (vectors of up to 16 bytes
+// that the band count is a multiple of), bands per block, and the schedule of
+// every direction.  Bands per block: about one block per compute unit (27 900
+// cells x 128 directions x 20 bands: 0.59 ms with 12 bands, 0.63 with all 20
+// on half the units, 0.80 with 8, where the rows' cache lines are fetched more
+// often; 48 000 tetrahedra x 96 directions: 0.89, 0.91 and 0.98 ms), fewer
+// where the live increments do not fit the LDS.  False if they never do (the
+// launch per level is used then).
+bool dir_schedule(bte_mesh_problem *p, const std::vector<int> &level, const std::vector<uint8_t> &lagm)
+{
+    const int es = (int)p->esize();
+    int V = 16 / es;
+    while (p->nl % V) V /= 2;
+    const int ng0 = std::max(1, std::min(p->nl / V, 256 / p->na));
+    for (int nb = ((p->nl + ng0 - 1) / ng0 + V - 1) / V * V;; nb = std::max(V, nb / 2 / V * V)) {
+        const int S = kDirThreads / (nb / V);
+        std::vector<std::vector<int>> cells(p->na);
+        std::vector<std::vector<MeshRec>> recs(p->na);
+        std::vector<int> nstep(p->na, 0), w(p->na, 0);
+        const bool done = on_threads(p->na, [&](int al) {
+            const size_t o = (size_t)al * p->nc;
+            w[al] = dir_direction(p, al, &level[o], &lagm[o], S, nstep[al], cells[al], recs[al]);
+        });
+        if (!done || *std::min_element(w.begin(), w.end()) < 0) return false;
+        const int slots = *std::max_element(w.begin(), w.end());
+        if ((size_t)(slots + 1) * nb * es <= 150 * 1024) {
+            int total = 0;
+            for (int al = 0; al < p->na; ++al) {
+                p->dir_base.push_back(total);
+                total += nstep[al] + 2 * kDirAhead;
+                p->dir_cell.insert(p->dir_cell.end(), cells[al].begin(), cells[al].end());
+                p->dir_rec.insert(p->dir_rec.end(), recs[al].begin(), recs[al].end());
+                std::vector<MeshRec>().swap(recs[al]);
+            }
+            p->dir_nstep = nstep;
+            for (MeshRec &r : p->dir_rec)
+                if (r.own == 0xffff || r.own == 0) r.own = (unsigned short)slots;   // empty places and unread items
+            p->dir.S = S;
+            p->dir.nb = nb;
+            p->dir.ng = (p->nl + nb - 1) / nb;
+            p->dir.slots = slots + 1;
+            p->dir_V = V;
+            return true;
+        }
+        if (nb == V) return false;
+    }
+}
+
 // Everything after the cells' geometry: least-squares stencils and
 // matrices, directions, bands, diffuse-wall records and the sweep schedule.
 // V, xc (3 per cell), the face slots in p, and the vertices of each cell
@@ -718,9 +1024,9 @@ bte_status mesh_finish(bte_mesh_problem *p, const bte_material *mat, int stencil
     // level of a cell one more than its deepest non-lagged upwind cell
     std::vector<int> level((size_t)p->na * nc);
     std::vector<uint8_t> lagm((size_t)p->na * nc, 0);
-    p->nlag = 0;
-    int maxlev = 0;
-    for (int al = 0; al < p->na; ++al) {
+    std::vector<int> nlag(p->na, 0), deepest(p->na, 0);
+    const bool done_all = on_threads(p->na, [&](int al) {
+        int maxlev = 0;
         std::vector<std::vector<int>> down(nc), deps(nc);
         std::vector<int> indeg(nc, 0);
         for (int c = 0; c < nc; ++c)
@@ -770,9 +1076,18 @@ bte_status mesh_finish(bte_mesh_problem *p, const bte_material *mat, int stencil
             for (int f = p->fptr[c]; f < p->fptr[c + 1]; ++f)
                 if (p->fnb[f] == pr.second) lagm[(size_t)al * nc + c] |= (uint8_t)(1u << (f - p->fptr[c]));
         }
-        p->nlag += (int)lagged.size();
+        nlag[al] = (int)lagged.size();
+        deepest[al] = maxlev;
+    });
+    if (!done_all) MFAIL(p, BTE_ERR_ARG, "mesh: out of memory");
+    p->nlag = 0;
+    int maxlev = 0;
+    for (int al = 0; al < p->na; ++al) {
+        p->nlag += nlag[al];
+        maxlev = std::max(maxlev, deepest[al]);
     }
     p->nlev = maxlev + 1;
+    if (dir_schedule(p, level, lagm)) return BTE_OK;
     std::vector<int> cnt(p->nlev + 1, 0);
     for (size_t i = 0; i < level.size(); ++i) ++cnt[level[i] + 1];
     for (int L = 0; L < p->nlev; ++L) cnt[L + 1] += cnt[L];
@@ -1025,6 +1340,36 @@ void mesh_iteration_rhs(bte_mesh_problem *p, const T *e, const double *TLdev, T 
     }
 }
 
+template <typename T, int V> const void *dir_kernel(bool ea)
+{
+    return ea ? (const void *)k_mesh_sweep_dir<T, V, true> : (const void *)k_mesh_sweep_dir<T, V, false>;
+}
+template <typename T> const void *dir_kernel(int V, bool ea)
+{
+    return V == 1 ? dir_kernel<T, 1>(true) : V == 2 ? dir_kernel<T, 2>(ea) : dir_kernel<T, 4>(ea);
+}
+size_t dir_smem(const bte_mesh_problem *p) { return (size_t)p->dir.slots * p->dir.nb * p->esize(); }
+
+hipError_t dir_kernels_init(const bte_mesh_problem *p)
+{
+    hipError_t r = hipSuccess;
+    for (int ea = 0; ea < 2 && r == hipSuccess; ++ea) {
+        const void *f = p->ctl.precision == BTE_F64 ? dir_kernel<double>(p->dir_V, ea) : dir_kernel<float>(p->dir_V, ea);
+        r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dir_smem(p));
+    }
+    return r;
+}
+
+template <typename T> hipError_t launch_sweep_dir(const bte_mesh_problem *p, T *e, const T *b, hipStream_t s)
+{
+    MeshDev d = p->dev;
+    DirPlan q = p->dir;
+    void *args[] = {&d, &q, &e, &b};
+    const bool ea = ((uintptr_t)e & (sizeof(T) * p->dir_V - 1)) == 0;
+    return hipLaunchKernel(dir_kernel<T>(p->dir_V, ea), dim3((unsigned)(p->na * q.ng)), dim3(kDirThreads), args, dir_smem(p),
+                           s);
+}
+
 template <typename T>
 bte_status mesh_solve(bte_mesh_problem *p, T *e, int init, bte_solve_stats *stats, hipStream_t s)
 {
@@ -1043,7 +1388,8 @@ bte_status mesh_solve(bte_mesh_problem *p, T *e, int init, bte_solve_stats *stat
         MHIP(p, hipEventRecord(p->ev[0], s));
         mesh_iteration_rhs<T>(p, e, p->TLdev, (T *)p->b, s);
         MHIP(p, hipEventRecord(p->ev[1], s));
-        for (int L = 0; L < p->nlev; ++L) {
+        if (p->dir_V > 0) MHIP(p, launch_sweep_dir<T>(p, e, (const T *)p->b, s));
+        for (int L = 0; p->dir_V == 0 && L < p->nlev; ++L) {
             const int i0 = p->lev_off[L], n = p->lev_off[L + 1] - i0;
             const int blocks = (int)(((size_t)n * p->nl + kBlock - 1) / kBlock);
             hipLaunchKernelGGL(k_mesh_sweep_level<T>, dim3(blocks), dim3(kBlock), 0, s, d, e, (T *)p->b, i0, n);
@@ -1146,6 +1492,11 @@ size_t bte_mesh_workspace_bytes(const bte_mesh_problem *p)
     add(4 * p->rec_cell.size() + 4);
     add(4 * p->rec_face.size() + 4);
     add(8 * p->rec_den.size() + 8);
+    if (p->dir_V > 0) {
+        add(8 * (size_t)p->na);
+        add(4 * p->dir_cell.size());
+        add(sizeof(MeshRec) * p->dir_rec.size());
+    }
     add(4 * p->item_c.size());
     add(4 * p->item_al.size());
     add(8 * p->item_out.size());
@@ -1210,6 +1561,19 @@ bte_status bte_mesh_bind(bte_mesh_problem *p, void *ws_dev, size_t bytes)
     x = take(4 * nr + 4); MHIP(p, up(p->rec_cell.data(), 4 * nr, x)); d.rec_cell = (const int *)x;
     x = take(4 * nr + 4); MHIP(p, up(p->rec_face.data(), 4 * nr, x)); d.rec_face = (const int *)x;
     x = take(8 * nr + 8); MHIP(p, up(p->rec_den.data(), 8 * nr, x)); d.rec_den = (const double *)x;
+    if (p->dir_V > 0) {
+        DirPlan &q = p->dir;
+        x = take(8 * (size_t)p->na);
+        MHIP(p, up(p->dir_base.data(), 4 * (size_t)p->na, x));
+        MHIP(p, up(p->dir_nstep.data(), 4 * (size_t)p->na, x + 4 * (size_t)p->na));
+        q.base = (const int *)x;
+        q.nstep = q.base + p->na;
+        x = take(4 * p->dir_cell.size()); MHIP(p, up(p->dir_cell.data(), 4 * p->dir_cell.size(), x)); q.cell = (const int *)x;
+        x = take(sizeof(MeshRec) * p->dir_rec.size());
+        MHIP(p, up(p->dir_rec.data(), sizeof(MeshRec) * p->dir_rec.size(), x));
+        q.rec = (const MeshRec *)x;
+        MHIP(p, dir_kernels_init(p));
+    }
     {
         const size_t ni = p->item_c.size();
         x = take(4 * ni); MHIP(p, up(p->item_c.data(), 4 * ni, x)); d.item_c = (const int *)x;
