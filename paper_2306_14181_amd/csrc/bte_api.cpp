@@ -555,9 +555,10 @@ std::vector<int3> tile_candidates(const bte_problem *p, int kind)
         if (p->dim == 1) c = {make_int3(64, 1, 1), make_int3(32, 1, 1), make_int3(16, 1, 1)};
         else if (p->dim == 2) c = {make_int3(16, 4, 1), make_int3(4, 16, 1), make_int3(8, 4, 1)};   // LDS tiles
         else {
-            // column segments of 1 x 1 x z cells (k_sweep3d, at most 48 cells):
-            // shorter segments shorten each hyperplane launch, longer ones
-            // need fewer launches; lengths past the tallest geometry are the same
+            // column segments of 1 x 1 x z cells (k_sweep3d, at most 48 cells;
+            // a block takes kS3X x kS3Y columns): shorter segments shorten each
+            // hyperplane launch, longer ones need fewer launches; lengths past
+            // the tallest geometry are the same
             int nz = 1;
             for (const Film &fm : p->films) nz = std::max(nz, fm.n[2]);
             for (int z : {16, 8, 12, 24, 32, 48, 4, 2, 1}) {
@@ -602,6 +603,7 @@ std::vector<int3> tile_candidates(const bte_problem *p, int kind)
 size_t count_tiles(const bte_problem *p, int3 td)
 {
     size_t n = 0;
+    if (p->dim == 3 && td.x == 1 && td.y == 1) td.x = kS3X, td.y = kS3Y;   // sweeps: a block's columns
     for (const Film &fm : p->films)
         n += (size_t)((fm.n[0] + td.x - 1) / td.x) * ((fm.n[1] + td.y - 1) / td.y) * ((fm.n[2] + td.z - 1) / td.z);
     return n;
@@ -613,6 +615,29 @@ void choose_default_tiles(bte_problem *p)
     const int lanes_oct = p->na_oct * p->nl;
     const int nchunk = (lanes_oct + 63) / 64;
     p->tdim = tile_candidates(p, BTE_TUNE_SWEEP)[0];
+    // 3D segments: a hyperplane's blocks take rounds of one per compute unit,
+    // and a round its segment's cells, the 6 cells by which the last of 4 x 4
+    // columns starts late, and a start of about 8 more.  Few blocks per
+    // hyperplane favour short segments (24^3, 48 lane chunks and octants,
+    // FP64: 0.60, 0.50, 0.36 and 0.40 ms per sweep with 24, 16, 8 and 4),
+    // many long ones (48^3, 64: 3.41, 3.58, 3.75 and 4.67 ms with 48, 24, 16
+    // and 8)
+    if (p->dim == 3) {
+        double best = 0;
+        for (const int3 &t : tile_candidates(p, BTE_TUNE_SWEEP)) {
+            std::vector<double> blocks;
+            for (const Film &fm : p->films) {
+                const int a = (fm.n[0] + kS3X - 1) / kS3X, b = (fm.n[1] + kS3Y - 1) / kS3Y, c = (fm.n[2] + t.z - 1) / t.z;
+                if ((int)blocks.size() < a + b + c - 2) blocks.resize(a + b + c - 2, 0.0);
+                for (int i = 0; i < a; ++i)
+                    for (int j = 0; j < b; ++j)
+                        for (int k = 0; k < c; ++k) blocks[i + j + k] += p->noct * nchunk;
+            }
+            double cost = 0;
+            for (double n : blocks) cost += std::ceil(n / 256) * (t.z + 14);
+            if (best == 0 || cost < best) best = cost, p->tdim = t;
+        }
+    }
     // explicit steps in 1D: each block walks its octant's chunks in turn, so
     // a short domain needs short tiles to give the chip enough blocks; take
     // the largest tile that still yields two blocks per compute unit
@@ -643,7 +668,9 @@ void build_schedule(bte_problem *p)
     int maxd = 0;
     for (int f = 0; f < p->nfilm; ++f) {
         const Film &fm = p->films[f];
-        const int nt[3] = {(fm.n[0] + p->tdim.x - 1) / p->tdim.x, (fm.n[1] + p->tdim.y - 1) / p->tdim.y,
+        // 3D: tiles of kS3X x kS3Y columns
+        const int tx3 = p->dim == 3 ? kS3X : p->tdim.x, ty3 = p->dim == 3 ? kS3Y : p->tdim.y;
+        const int nt[3] = {(fm.n[0] + tx3 - 1) / tx3, (fm.n[1] + ty3 - 1) / ty3,
                            (fm.n[2] + p->tdim.z - 1) / p->tdim.z};
         for (int o = 0; o < p->noct; ++o) {
             int sg[3];
@@ -1186,7 +1213,8 @@ bte_status bte_bind(bte_problem *p, void *ws, size_t bytes)
     if (!p->items2.empty()) HIPCHK(p, up("items2", p->items2.data(), sizeof(Sweep2Item) * p->items2.size()));
     HIPCHK(p, up("titems", p->titems.data(), sizeof(TileItem) * p->titems.size()));
     if (!p->citems.empty()) HIPCHK(p, up("citems", p->citems.data(), sizeof(ColItem) * p->citems.size()));
-    if (tile_smem_size(p->tile_cap, (int)p->esize(), 1) > 160 * 1024) FAIL(p, BTE_ERR_UNSUPPORTED, "tile LDS");
+    if (p->dim < 3 && tile_smem_size(p->tile_cap, (int)p->esize(), 1) > 160 * 1024)   // 3D sweeps walk columns
+        FAIL(p, BTE_ERR_UNSUPPORTED, "tile LDS");
     HIPCHK(p, tile_kernels_init(160 * 1024));
     HIPCHK(p, adj_kernels_init(160 * 1024));
     Dev &d = p->dev;
