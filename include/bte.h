@@ -123,7 +123,8 @@ typedef struct {
 
 typedef struct {
     int iters;               /* source iterations performed                */
-    int cg_iters;            /* total CG iterations                        */
+    int cg_iters;            /* total CG iterations (none where the correction is
+                                solved by eigenvectors: bte_steady_solve)  */
     double eps_T, eps_q;     /* last convergence measures                  */
     int converged;
     double ms_total;         /* wall time of the call (host clock)         */
@@ -257,7 +258,10 @@ bte_status bte_transient_step(bte_problem *p, void *e_dev, int n_steps, double t
                               const double *pulse, void *stream);
 
 /* Steady solve (Algorithm 1), in place on e.  init != 0 starts from the
- * heat-diffusion solution (Sec. 3.5, eq. diff), else from e.  Synchronous
+ * heat-diffusion solution (Sec. 3.5, eq. diff), else from e.  The diffusion
+ * problems are solved by CG, or, for one geometry without pores, interfaces
+ * and scattering rates (gamma NULL) whose CG could not reach its cap before
+ * its tolerance, directly by the operator's eigenvectors.  Synchronous
  * (reads one convergence flag per iteration).  Returns BTE_ERR_NOT_CONVERGED
  * with the last iterate if max_iter is reached.  stats may be NULL. */
 bte_status bte_steady_solve(bte_problem *p, void *e_dev, int init, bte_solve_stats *stats,

@@ -88,6 +88,10 @@ void launch_cg_coef(const Dev &, const CgArgs &, double *, double *, hipStream_t
 void launch_diff_rhs(const Dev &, const CgArgs &, double *, hipStream_t);
 void launch_cg_begin(const Dev &, const CgArgs &, const double *, hipStream_t);
 void launch_cg_iters(const Dev &, const CgArgs &, int, int, hipStream_t);
+double axis_angle(int, bool, double, double, int);
+void axis_eigen(int, double, bool, double, double, double *, double *);
+hipError_t launch_direct(int, const int *, const double *, const double *, const double *, double *, double *, double *,
+                         double, hipStream_t);
 size_t cg_solve_smem(int, int);
 hipError_t cg_solve_init(int, int, int, int, bool *);
 hipError_t launch_cg_solve(const Dev &, const CgArgs &, const CgPlan &, int, int, const double *, int, unsigned,
@@ -233,6 +237,17 @@ struct bte_problem {
     std::vector<int> cg_cell, cg_gptr, cg_gid;
     CgPlan cgplan{};
     unsigned cg_epoch = 0;                // tags used so far
+    // diffusion operators (0: heat diffusion, 1: correction) by eigenvectors,
+    // while no per-cell scattering rate is set
+    struct Direct {
+        double c[3] = {0, 0, 0}, wall[6] = {0, 0, 0, 0, 0, 0};   // coupling per axis; wall share of it per face
+        std::vector<double> low;   // lowest eigenvalues over the largest diagonal, ascending
+        double zero = 0;     // eigenvalues up to this belong to the null vector
+        bool built = false;
+        double *V = nullptr, *lam = nullptr;
+    } direct[2];
+    bool direct_ok = false;    // the geometry has such operators
+    bool gamma_zero = true;
     double *din = nullptr, *part = nullptr;
     void *e2 = nullptr;
     void *psi = nullptr, *psi2 = nullptr;                       // adjoint iterates (ctl.adjoint)
@@ -911,9 +926,89 @@ void build_cg_plan(bte_problem *p)
     p->cgplan.max_ghost = most;
 }
 
+constexpr int kLow = 8;   // lowest eigenvalues looked at
+
+// Operators that the eigenvectors of each axis diagonalise: one geometry of
+// one conductivity (no pores, no interfaces), up to 512 cells per axis.
+void plan_direct(bte_problem *p)
+{
+    const Film &fm = p->films[0];
+    p->direct_ok = p->nfilm == 1 && p->nifc == 0 && fm.nsolid == fm.ncell;
+    for (int a = 0; a < p->dim; ++a) p->direct_ok = p->direct_ok && fm.n[a] <= 512;
+    if (!p->direct_ok) return;
+    double k0 = 0, cv = 0;
+    for (int l = 0; l < p->nl; ++l) {
+        const double C = p->C4[fm.moff + l] * p->omega, v = p->v[fm.moff + l];
+        k0 += C * v * v / p->itau[fm.moff + l];
+        cv += C * v;
+    }
+    for (int corr = 0; corr < 2; ++corr) {
+        bte_problem::Direct &q = p->direct[corr];
+        double dmax = 0;
+        std::vector<double> low(1, 0.0);   // the smallest eigenvalues of the sum, ascending
+        for (int a = 0; a < p->dim; ++a) {
+            const double k = k0 * p->M[a] + (corr ? cv * fm.h[a] * p->H[a] / p->omega : 0.0);
+            const double c = k * fm.ih[a] * fm.ih[a];
+            q.c[a] = c;
+            if (!(c > 0) || !std::isfinite(c)) {   // no conduction (all speeds zero)
+                p->direct_ok = false;
+                return;
+            }
+            for (int s = 0; s < 2; ++s) {
+                // the corner cells carry every low face and every high face
+                const uint32_t ab = axis_bits(p->code[s ? p->nc - 1 : 0], a);
+                const bool wall = !side_is_cell(ab, s ? 1 : -1) && side_wall(ab, s ? 1 : -1) == 0;
+                const double kd = 2.0 * k * fm.ih[a];
+                q.wall[2 * a + s] = wall ? (corr ? 1.0 / (1.0 / kd + 1.0 / fm.Hm[a]) : kd) * fm.ih[a] / c : 0.0;
+            }
+            const double al = q.wall[2 * a], ar = q.wall[2 * a + 1];
+            std::vector<double> sum;
+            for (int m = 0; m < std::min(fm.n[a], kLow + 1); ++m) {
+                const double h = std::sin(0.5 * axis_angle(fm.n[a], fm.periodic[a], al, ar, m));
+                for (double x : low) sum.push_back(x + 4.0 * c * h * h);
+            }
+            std::sort(sum.begin(), sum.end());
+            if ((int)sum.size() > kLow + 1) sum.resize(kLow + 1);
+            low.swap(sum);
+            dmax += c * (fm.periodic[a] ? 2.0 : std::max(2.0, 1.0 + std::max(al, ar)));
+        }
+        if (p->films[0].floating) low.erase(low.begin());   // the null vector: b has no part in it
+        q.low.clear();
+        for (double x : low) q.low.push_back(x / dmax);
+        q.zero = 1e-12 * (low.empty() ? dmax : low[0]);
+    }
+}
+
+// Iterations after which CG has met rtol in exact arithmetic, whatever the
+// right-hand side.  The preconditioned operator's eigenvalues are at most 2 (no
+// diagonal is below its row's couplings) and, in order, at least low[i]; with
+// the m lowest taken out by m iterations, |r| falls by 2 sqrt(kappa) prod(2 /
+// low[i]) exp(-2 k / sqrt(kappa_m)), kappa_m = 2 / low[m].
+double cg_bound(const bte_problem::Direct &q, double rtol)
+{
+    if (q.low.empty()) return 1.0;
+    double best = 1e300, lost = std::log(2.0 * std::sqrt(2.0 / q.low[0]) / std::min(rtol, 1.0));
+    for (size_t m = 0; m < q.low.size(); ++m) {
+        best = std::min(best, (double)m + 0.5 * std::sqrt(2.0 / q.low[m]) * lost);
+        lost += std::log(2.0 / q.low[m]);
+    }
+    return best;
+}
+
+// Whether a solve goes by eigenvectors: where CG could not have stopped short of
+// rtol, so that the direct solution is the one it was asked for (cg_bound
+// iterations allowed, or as many as cells).  With fewer the iterate that the cap
+// leaves is the result asked for.
+bool direct_use(const bte_problem *p, int corr, double rtol, int maxit)
+{
+    if (!p->direct_ok || !p->gamma_zero) return false;
+    return maxit >= std::min((double)p->nc, cg_bound(p->direct[corr], rtol));
+}
+
 void plan_workspace(bte_problem *p)
 {
     build_cg_plan(p);
+    plan_direct(p);
     p->layout.clear();
     size_t off = 0;
     auto add = [&](const char *name, size_t bytes) {
@@ -967,6 +1062,11 @@ void plan_workspace(bte_problem *p)
         add("cg_gptr", 4 * p->cg_gptr.size());
         add("cg_gid", 4 * p->cg_gid.size());
         add("cg_words", 8 * (size_t)cg_word_count(nc));
+    }
+    if (p->direct_ok) {
+        size_t n1 = 0;
+        for (int a = 0; a < p->dim; ++a) n1 += (size_t)p->films[0].n[a] * (p->films[0].n[a] + 1);
+        add("direct", 2 * 8 * n1);
     }
     add("din", 8 * (size_t)p->nw * p->nl);
     const int nchunk_stream = (p->nk + kBlock - 1) / kBlock;
@@ -1298,6 +1398,8 @@ bte_status bte_bind(bte_problem *p, void *ws, size_t bytes)
     p->d_citems = wsptr<ColItem>(p, "citems");
     p->d_wrec = wsptr<int>(p, "wrec");
     p->d_wden = wsptr<double>(p, "wden");
+    for (auto &q : p->direct) q.built = false;
+    p->gamma_zero = true;
     p->cg_one = false;
     if (p->cg_R > 0) {
         HIPCHK(p, up("cg_cell", p->cg_cell.data(), 4 * p->cg_cell.size()));
@@ -1340,6 +1442,7 @@ bte_status bte_set_fields(bte_problem *p, const double *P_dev, const double *gam
     if (gamma_dev) HIPCHK(p, hipMemcpyAsync(p->gamma, gamma_dev, nb, hipMemcpyDeviceToDevice, s));
     else HIPCHK(p, hipMemsetAsync(p->gamma, 0, nb, s));
     p->dev.P = P_dev ? p->P : nullptr;
+    p->gamma_zero = gamma_dev == nullptr;
     cell_setup(p, s);
     HIPCHK(p, hipGetLastError());
     return BTE_OK;
@@ -1401,6 +1504,35 @@ template <typename T> bte_status moments_to(bte_problem *p, const T *e, const do
 // without `epoch`.  *epoch is 0 where one launch per iteration was used.
 constexpr int kCgChunk = 64;
 
+// Eigenvectors of one operator, formed on the host and uploaded the first
+// time a solve of the bound problem takes them.
+hipError_t direct_build(bte_problem *p, int corr, hipStream_t s)
+{
+    bte_problem::Direct &q = p->direct[corr];
+    if (q.built) return hipSuccess;
+    const Film &fm = p->films[0];
+    size_t nv = 0, nlam = 0;
+    for (int a = 0; a < p->dim; ++a) nv += (size_t)fm.n[a] * fm.n[a], nlam += fm.n[a];
+    std::vector<double> host;
+    try {
+        host.resize(nv + nlam);
+    } catch (...) {
+        return hipErrorOutOfMemory;
+    }
+    double *V = host.data(), *lam = V + nv;
+    for (int a = 0; a < p->dim; ++a) {
+        axis_eigen(fm.n[a], q.c[a], fm.periodic[a], q.wall[2 * a], q.wall[2 * a + 1], V, lam);
+        V += (size_t)fm.n[a] * fm.n[a];
+        lam += fm.n[a];
+    }
+    q.V = wsptr<double>(p, "direct") + corr * (nv + nlam);
+    q.lam = q.V + nv;
+    hipError_t r = hipMemcpyAsync(q.V, host.data(), 8 * (nv + nlam), hipMemcpyHostToDevice, s);
+    if (r == hipSuccess) r = hipStreamSynchronize(s);
+    q.built = r == hipSuccess;
+    return r;
+}
+
 bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int maxit, hipStream_t s,
             unsigned *epoch = nullptr)
 {
@@ -1413,7 +1545,11 @@ bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int
     g.x = x_out;
     g.rtol2 = rtol * rtol;
     if (epoch) *epoch = 0;
-    if (epoch && p->cg_one) {
+    if (direct_use(p, corr, rtol, maxit) && p->direct[corr].built) {
+        const bte_problem::Direct &q = p->direct[corr];
+        if (launch_direct(p->dim, p->films[0].n, q.V, q.lam, b, x_out, p->cg_r, p->cg_z, q.zero, s) != hipSuccess)
+            return false;
+    } else if (epoch && p->cg_one) {
         const unsigned need = (unsigned)maxit + 2u;
         if (p->cg_epoch > 0xffffffffu - need) {   // tags used up: start again on cleared words
             if (hipMemsetAsync(p->cgplan.wword, 0, 8 * cg_word_count(p->nc), s) != hipSuccess) return false;
@@ -1449,6 +1585,7 @@ bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int
 bool run_cg_now(bte_problem *p, int corr, double *b, double *x_out, double rtol, int maxit, hipStream_t s)
 {
     unsigned epoch = 0, word = 0;
+    if (direct_use(p, corr, rtol, maxit) && direct_build(p, corr, s) != hipSuccess) return false;
     if (!run_cg(p, corr, b, x_out, rtol, maxit, s, &epoch)) return false;
     if (!epoch) return true;
     if (hipMemcpyAsync(&word, p->cgplan.abortw, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return false;
@@ -1539,6 +1676,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
         launch_set_equilibrium<T>(d, e, p->T0, s);
         HIPCHK(p, hipMemsetAsync(p->cg_scal, 0, 8 * 16, s));   // count correction CG only
     }
+    if (synthetic && direct_use(p, 1, p->ctl.cg_rtol, p->ctl.cg_max_iter)) HIPCHK(p, direct_build(p, 1, s));
     // moments of the start field
     launch_moments<T>(d, e, nullptr, p->part, s);
     launch_finalize(d, p->part, 1, p->Tref, nullptr, nullptr, nullptr, p->TL, p->T0, p->q0, s);

@@ -1,8 +1,10 @@
-"""The one-launch CG of the diffusion operators (k_cg_solve) where its split of
-the cells can go wrong: one block with and without full waves, one and two
-cells past a block, ragged tiles, periodic wraps, pores, two geometries in one
-problem (ghosts of both), and a problem past its largest grid (a launch per
-iteration).
+"""The diffusion solves: the one-launch CG (k_cg_solve) where its split of the
+cells can go wrong (one block with and without full waves, one and two cells
+past a block, ragged tiles, periodic wraps, pores, two geometries in one problem
+with ghosts of both, and a problem past its largest grid: a launch per
+iteration), and the solution by eigenvectors (bte_direct.hip) that geometries
+without pores and scattering rates take instead (one cell, odd and even
+periodic axes, every pair of ends, three axes).
 
 One source iteration (sequential scheme, FP64) from the heat-diffusion guess
 is compared with the oracle's: the guess is a CG solve to a relative residual
@@ -59,14 +61,18 @@ CASES = {
     "plane_33x17": geometry((33, 17), [D, D, T, S]),
     "plane_97x83": geometry((97, 83), [T, T, D, D]),
     "pores_periodic_47x47": geometry((47, 47), [P, P, P, P], pdT=(1.0, 0.0, 0.0), pores=True),
+    "periodic_12x9": geometry((12, 9), [P, P, P, P], pdT=(0.5, 0.0, 0.0)),
+    "box_plain": geometry((7, 6, 9), [T, S, D, T, P, P]),
+    "box_walls": geometry((33, 4, 5), [T, T, T, T, T, D]),
     "box_13": geometry((13, 14, 13), [T, T, D, S, S, D], pores=True),
     "box_periodic": geometry((9, 17, 16), [P, P, T, T, P, P], pdT=(1.0, 0.0, 0.0), pores=True),
 }
 
 
-def one_iteration(B, geos, mat, Ps, scheme, init, e=None, **ctl):
+def one_iteration(B, geos, mat, Ps, scheme, init, e=None, rates=False, **ctl):
     prob = B.Problem(geos, mat, dict(precision=B.F64, scheme=scheme, residual_temp=0.0, residual_flux=0.0, **ctl))
-    prob.set_fields(torch.as_tensor(np.concatenate(Ps), device="cuda"), None)
+    gam = torch.zeros(prob.n_cells, dtype=torch.float64, device="cuda") if rates else None
+    prob.set_fields(torch.as_tensor(np.concatenate(Ps), device="cuda"), gam)
     e = prob.zeros() if e is None else torch.as_tensor(e, device="cuda")
     st = prob.steady_solve(e, init=init, allow_not_converged=True)
     return e.cpu().numpy(), st
@@ -81,11 +87,12 @@ def source(g, k):
     return p
 
 
+@pytest.mark.parametrize("rates", [False, True])      # given (zero) scattering rates: CG
 @pytest.mark.parametrize("name", sorted(CASES))
-def test_guess_against_oracle(B, name):
+def test_guess_against_oracle(B, name, rates):
     g = CASES[name]
     mat, P_ = material(), source(g, 5)
-    e, _ = one_iteration(B, [g], mat, [P_], B.SEQUENTIAL, True, max_iter=1)
+    e, _ = one_iteration(B, [g], mat, [P_], B.SEQUENTIAL, True, rates=rates, max_iter=1)
     eo, _ = O.steady(O.Case(g, mat, P=P_), scheme=0, tol_T=0.0, tol_q=0.0, max_iter=1)
     bar = 2e-13 * sum((2 * n / np.pi) ** 2 + 1 for n in g["n"]) + 1e-11
     assert np.abs(e - eo).max() <= bar * np.abs(eo).max()
@@ -118,3 +125,16 @@ def test_capped_correction(B, n):
     eo, so = O.steady(case, scheme=1, tol_T=0.0, tol_q=0.0, max_iter=2, cg_rtol=1e-12, cg_maxit=25, e=e0.reshape(-1))
     assert st["cg_iters"] == so["cg_iters"] == 50
     assert np.abs(e - eo).max() <= 1e-10 * np.abs(eo).max()
+
+
+@pytest.mark.parametrize("name", ["line_63", "plane_33x17", "periodic_12x9", "box_plain"])
+def test_correction_by_eigenvectors(B, name):
+    """Three synthetic iterations with a cap that CG cannot reach: no CG iteration is counted, and the fields are the
+    oracle's, whose corrections are solved to 1e-13."""
+    g = CASES[name]
+    mat, P_ = material(), source(g, 7)
+    e, st = one_iteration(B, [g], mat, [P_], B.SYNTHETIC, True, max_iter=3, cg_rtol=1e-8, cg_max_iter=5000)
+    eo, _ = O.steady(O.Case(g, mat, P=P_), scheme=1, tol_T=0.0, tol_q=0.0, max_iter=3, cg_rtol=1e-13, cg_maxit=5000)
+    assert st["cg_iters"] == 0
+    bar = 1e-12 * sum((2 * n / np.pi) ** 2 + 1 for n in g["n"]) + 1e-11
+    assert np.abs(e - eo).max() <= bar * np.abs(eo).max()
