@@ -359,7 +359,9 @@ bte_status bte_set_persistent(bte_problem *p, int on);
  * counterpart; these calls only choose how the same arithmetic is blocked on
  * the GPU:
  *   BTE_TUNE_SWEEP     steady sweeps, one launch per tile diagonal: LDS
- *                      tiles in 1D; in 2D the register tile 8 x 8 x r (r =
+ *                      tiles of the transposed sweep in 1D (the forward
+ *                      sweep takes whole lines in one launch and has no
+ *                      choice); in 2D the register tile 8 x 8 x r (r =
  *                      tile rows per wavefront: 2, 1, and 4 in FP32) and
  *                      LDS tiles (other shapes); column segments 1 x 1 x z
  *                      in 3D;

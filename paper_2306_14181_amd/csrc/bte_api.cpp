@@ -31,6 +31,13 @@ hipError_t launch_sweep_tile(const Dev &, const T *, T *, const double *, const 
 template <typename T>
 hipError_t launch_transient_tile(const Dev &, const T *, T *, const double *, const double *, const TileItem *, int,
                                  int3, int, int, int, double, double, double *, hipStream_t);
+int line_parts(int lanes_oct);
+template <typename T>
+hipError_t launch_sweep1d(const Dev &, const T *, T *, const double *, const double *, const double *, int, int,
+                          double *, hipStream_t);
+template <typename T>
+hipError_t launch_transient1d(const Dev &, const T *, T *, const double *, double *, const double *, const TileItem *,
+                              int, int, double, double, hipStream_t);
 hipError_t tile_kernels_init(size_t);
 template <typename T>
 hipError_t launch_sweep_adj(const Dev &, const T *, T *, const double *, const double *, const SweepItem *, int, int,
@@ -653,9 +660,10 @@ void choose_default_tiles(bte_problem *p)
             if (best == 0 || cost < best) best = cost, p->tdim = t;
         }
     }
-    // explicit steps in 1D: each block walks its octant's chunks in turn, so
-    // a short domain needs short tiles to give the chip enough blocks; take
-    // the largest tile that still yields two blocks per compute unit
+    // explicit steps in 1D: a block takes every lane of its cells, so a short
+    // domain needs short tiles to give the chip enough blocks; take the
+    // largest tile that still yields a block per compute unit (two of the
+    // transposed step, whose blocks take an octant's lanes)
     const std::vector<int3> tc = tile_candidates(p, BTE_TUNE_TRANSIENT);
     p->tdim_tr = tc[0];
     if (p->dim == 1)
@@ -704,14 +712,18 @@ void build_schedule(bte_problem *p)
         }
     }
     std::stable_sort(recs.begin(), recs.end(), [](const Rec &a, const Rec &b) { return a.d < b.d; });
+    // 1D: octant 0 first, the forward step takes every lane of a tile in one block
     p->titems.clear();
-    for (int f = 0; f < p->nfilm; ++f) {
-        const Film &fm = p->films[f];
-        const int ntile = ((fm.n[0] + p->tdim_tr.x - 1) / p->tdim_tr.x) *
-                          ((fm.n[1] + p->tdim_tr.y - 1) / p->tdim_tr.y) * ((fm.n[2] + p->tdim_tr.z - 1) / p->tdim_tr.z);
-        for (int o = 0; o < p->noct; ++o)
-            for (int t = 0; t < ntile; ++t) p->titems.push_back({f, o, t, 0});
-    }
+    const int opass = p->dim == 1 ? p->noct : 1;
+    for (int op = 0; op < opass; ++op)
+        for (int f = 0; f < p->nfilm; ++f) {
+            const Film &fm = p->films[f];
+            const int ntile = ((fm.n[0] + p->tdim_tr.x - 1) / p->tdim_tr.x) *
+                              ((fm.n[1] + p->tdim_tr.y - 1) / p->tdim_tr.y) *
+                              ((fm.n[2] + p->tdim_tr.z - 1) / p->tdim_tr.z);
+            for (int o = op; o < p->noct; o += opass)
+                for (int t = 0; t < ntile; ++t) p->titems.push_back({f, o, t, 0});
+        }
     // Columns of one (geometry, octant, chunk) in strips of kColStrip along
     // x, each strip row by row: the y neighbours of a column are then walked
     // kColStrip and 2 kColStrip items earlier or later, close enough that
@@ -1071,6 +1083,7 @@ void plan_workspace(bte_problem *p)
     add("din", 8 * (size_t)p->nw * p->nl);
     const int nchunk_stream = (p->nk + kBlock - 1) / kBlock;
     p->npart_max = std::max(nchunk_stream, p->noct * p->nchunk_oct);
+    if (p->dim == 1) p->npart_max = std::max(p->npart_max, line_parts(p->na_oct * p->nl));
     add("part", 8 * (size_t)kMomN * nc * p->npart_max);
     add("e2", p->esize() * p->nelem());
     add("zrow", 8 * 8 * (size_t)p->nk);   // 8 cells of zeros (a missing row of a tile)
@@ -1626,12 +1639,17 @@ template <typename F> hipError_t graph_run(Graph &gr, hipStream_t cs, hipStream_
     return hipGraphLaunch(gr.x, s);
 }
 
-// One forward sweep (every tile-diagonal launch) from ein into eout: the
-// register-tile kernel for 2D geometries with 8 x 8 tiles, the column
-// segments in 3D, the LDS tiles otherwise.
+// One forward sweep (every tile-diagonal launch) from ein into eout: whole
+// lines in one launch in 1D, the register-tile kernel for 2D geometries with
+// 8 x 8 tiles, the column segments in 3D, the LDS tiles otherwise.
 template <typename T> hipError_t sweep_launches(bte_problem *p, const T *ein, T *eout, hipStream_t q)
 {
     const Dev &d = p->dev;
+    if (p->dim == 1) {
+        int max_n = 1;
+        for (const Film &fm : p->films) max_n = std::max(max_n, fm.n[0]);
+        return launch_sweep1d<T>(d, ein, eout, p->dpend, p->TL, p->din, p->na_oct, max_n, p->part, q);
+    }
     const bool reg = reg2d(p);
     const int3 lt = lds_tdim(p);
     if (reg && p->persistent && p->queue_ok) {
@@ -1687,7 +1705,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
     std::vector<int> fdone(p->nfilm, 0);
     int ndone = 0;
     int *fdone_dev = const_cast<int *>(d.fdone);
-    const int np = p->noct * p->nchunk_oct;
+    const int np = p->dim == 1 ? line_parts(p->na_oct * p->nl) : p->noct * p->nchunk_oct;
     bte_status ret = BTE_ERR_NOT_CONVERGED;
     // phase timers: events on the solve stream, read after the per-iteration sync
     hipEvent_t ev[5];
@@ -1716,7 +1734,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
         } else if (!sweep(s)) {
             FAIL(p, BTE_ERR_HIP, "sweep launch failed");
         }
-        if (reg2d(p) && p->persistent && p->queue_ok) st.sweep_launches += 1;
+        if (p->dim == 1 || (reg2d(p) && p->persistent && p->queue_ok)) st.sweep_launches += 1;
         else
             for (size_t dg = 0; dg + 1 < p->diag_off.size(); ++dg)
                 st.sweep_launches += p->diag_off[dg + 1] > p->diag_off[dg];
@@ -1860,10 +1878,14 @@ hipError_t one_step(bte_problem *p, const T *ein, T *eout, double src, hipEvent_
     if (ev && (r = hipEventRecord(ev[0], s)) != hipSuccess) return r;
     launch_walls<T>(d, ein, nullptr, p->d_wrec, p->d_wden, p->din, p->nw, s);
     if (ev && (r = hipEventRecord(ev[1], s)) != hipSuccess) return r;
-    // three-dimensional geometries: column kernel, partials per (octant,
-    // chunk); otherwise the tile kernel, partials per octant
+    // one-dimensional geometries: T_L in the same launch; three-dimensional
+    // ones: column kernel, partials per (octant, chunk); otherwise the tile
+    // kernel, partials per octant
     int np = p->noct;
-    if (p->dim == 3) {
+    if (p->dim == 1) {
+        r = launch_transient1d<T>(d, ein, eout, p->TL, p->TL, p->din, p->d_titems, (int)p->titems.size() / p->noct,
+                                  p->tdim_tr.x, src, p->ctl.dt, s);
+    } else if (p->dim == 3) {
         r = launch_transient3d<T>(d, ein, eout, p->TL, p->din, p->d_citems, (int)p->citems.size(), p->na_oct,
                                   p->nchunk_oct, src, p->ctl.dt, p->part, s);
         np = p->noct * p->nchunk_oct;
@@ -1873,7 +1895,7 @@ hipError_t one_step(bte_problem *p, const T *ein, T *eout, double src, hipEvent_
     }
     if (r != hipSuccess) return r;
     if (ev && (r = hipEventRecord(ev[2], s)) != hipSuccess) return r;
-    launch_finalize_tl(d, p->part, np, p->TL, s);
+    if (p->dim != 1) launch_finalize_tl(d, p->part, np, p->TL, s);
     if (ev && (r = hipEventRecord(ev[3], s)) != hipSuccess) return r;
     return hipGetLastError();
 }
@@ -2462,6 +2484,19 @@ template <typename T> hipError_t tune_run(bte_problem *p, int kind, const T *ein
 {
     const Dev &d = p->dev;
     T *eout = static_cast<T *>(p->e2);
+    if (p->dim == 1) {
+        if (kind == BTE_TUNE_TRANSIENT)   // T_L of the new state into scratch
+            return launch_transient1d<T>(d, ein, eout, p->TL, p->part, p->din, p->d_titems,
+                                         (int)p->titems.size() / p->noct, p->tdim_tr.x, 0.0, p->ctl.dt, s);
+        // the forward sweep has no tiles: the shape is the transposed sweep's
+        for (size_t dg = 0; dg + 1 < p->diag_off.size(); ++dg) {
+            const int i0 = p->diag_off[dg], cnt = p->diag_off[dg + 1] - i0;
+            const hipError_t r = launch_sweep_adj<T>(d, ein, eout, p->TL, p->din, p->d_items, i0, cnt, p->tdim,
+                                                     p->na_oct, p->nchunk_oct, p->tile_cap, p->part, s);
+            if (r != hipSuccess) return r;
+        }
+        return hipSuccess;
+    }
     if (kind == BTE_TUNE_TRANSIENT)
         return launch_transient_tile<T>(d, ein, eout, p->TL, p->din, p->d_titems, (int)p->titems.size(),
                                         p->tdim_tr, p->na_oct, p->nchunk_oct, p->tile_cap_tr, 0.0, p->ctl.dt,

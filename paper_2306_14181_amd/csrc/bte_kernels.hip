@@ -511,15 +511,36 @@ __global__ __launch_bounds__(kBlock) void k_apply_shift(Dev d, const T *in, T *o
 
 // Steady bookkeeping after a sweep: moments of e^{n+1} (T_L^kin, T, |q|),
 // the synthetic defect r = S (T_L^kin - T_L^n) and the squared changes.
-__global__ void k_steady_post(Dev d, const double *__restrict__ part, int np, const double *__restrict__ TLn,
-                              double *__restrict__ TLkin, double *__restrict__ Tnew, double *__restrict__ qnew,
-                              double *__restrict__ r, int synthetic)
+// kPostCells cells per block: thread (strand, element) sums one of the cells'
+// contiguous moments over every kPostStrands-th partial, then the strands are
+// added in a fixed order.  A thread per cell left its np x 5 loads a serial
+// chain: with the two convergence kernels 60 us at 1000 cells x 160 partials,
+// 15 us here (11 and 12 at 200 x 10).
+constexpr int kPostCells = 32, kPostStrands = 4;
+__global__ __launch_bounds__(kPostCells *kMomN *kPostStrands) void k_steady_post(
+    Dev d, const double *__restrict__ part, int np, const double *__restrict__ TLn, double *__restrict__ TLkin,
+    double *__restrict__ Tnew, double *__restrict__ qnew, double *__restrict__ r, int synthetic)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= d.nc) return;
-    double s[kMomN] = {0, 0, 0, 0, 0};
-    for (int p = 0; p < np; ++p)
-        for (int i = 0; i < kMomN; ++i) s[i] += part[((size_t)p * d.nc + c) * kMomN + i];
+    constexpr int E = kPostCells * kMomN;
+    __shared__ double sh[kPostStrands][E];
+    const int el = threadIdx.x % E, st = threadIdx.x / E;
+    const size_t row = (size_t)d.nc * kMomN, at = (size_t)blockIdx.x * E + el;
+    double v = 0.0;
+    if (at < row) {
+#pragma unroll 4
+        for (int p = st; p < np; p += kPostStrands) v += part[p * row + at];
+    }
+    sh[st][el] = v;
+    __syncthreads();
+    const int c = blockIdx.x * kPostCells + threadIdx.x;
+    if (threadIdx.x >= kPostCells || c >= d.nc) return;
+    double s[kMomN];
+#pragma unroll
+    for (int i = 0; i < kMomN; ++i) {
+        s[i] = 0.0;
+#pragma unroll
+        for (int q = 0; q < kPostStrands; ++q) s[i] += sh[q][threadIdx.x * kMomN + i];
+    }
     const bool solid = d.code[c] & kSolidBit;
     const double tl = solid ? s[1] / d.S[c] : 0.0;
     TLkin[c] = tl;
@@ -1066,9 +1087,9 @@ void launch_finalize_tl(const Dev &d, const double *part, int np, double *TLdev,
 void launch_steady_post(const Dev &d, const double *part, int np, const double *TLn, double *TLkin, double *Tnew,
                         double *qnew, double *r, int synthetic, hipStream_t s)
 {
-    const int grid = (d.nc + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_steady_post, dim3(grid), dim3(kBlock), 0, s, d, part, np, TLn, TLkin, Tnew, qnew, r,
-                       synthetic);
+    const int grid = (d.nc + kPostCells - 1) / kPostCells;
+    hipLaunchKernelGGL(k_steady_post, dim3(grid), dim3(kPostCells * kMomN * kPostStrands), 0, s, d, part, np, TLn, TLkin,
+                       Tnew, qnew, r, synthetic);
 }
 
 int film_segments(int max_cells) { return std::max(1, (max_cells + kFilmSeg - 1) / kFilmSeg); }

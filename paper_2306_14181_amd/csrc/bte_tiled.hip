@@ -1,5 +1,6 @@
 // bte_tiled.hip -- LDS-staged transport kernels: the steady sweep (tile
-// wavefronts) and the explicit transient step.  See bte_tile.h for the
+// wavefronts) and the explicit transient step of two-dimensional geometries,
+// and the transposed sweep in one and two dimensions.  See bte_tile.h for the
 // staging scheme.
 //
 // Per-element work is kept small: everything that depends only on the cell
@@ -370,7 +371,6 @@ hipError_t launch_sweep_tile(const Dev &d, const T *ein, T *eout, const double *
     if (d.dim == DIM && d.limiter == LIM)                                                                            \
         sweep_launch<T, DIM, LIM>(d, ein, eout, dpend, TLdev, din, items, item0, count, tdim, na_oct, nchunk_oct,    \
                                   cap, part, s);
-    BTE_SWEEP(1, 0) BTE_SWEEP(1, 1) BTE_SWEEP(1, 2)
     BTE_SWEEP(2, 0) BTE_SWEEP(2, 1) BTE_SWEEP(2, 2)
 #undef BTE_SWEEP
     return hipGetLastError();
@@ -419,40 +419,32 @@ hipError_t launch_transient_tile(const Dev &d, const T *ein, T *eout, const doub
     if (d.dim == DIM && d.limiter == LIM)                                                                            \
         transient_launch<T, DIM, LIM>(d, ein, eout, TLdev, din, items, nitems, tdim, na_oct, nchunk_oct, cap, src,   \
                                       dt, part, s);
-    BTE_TRANS(1, 0) BTE_TRANS(1, 1) BTE_TRANS(1, 2)
     BTE_TRANS(2, 0) BTE_TRANS(2, 1) BTE_TRANS(2, 2)
-    BTE_TRANS(3, 0) BTE_TRANS(3, 1) BTE_TRANS(3, 2)
 #undef BTE_TRANS
     return hipGetLastError();
 }
 
-template <typename T, int DIM, int LIM> hipError_t set_lds(size_t bytes)
+template <typename T, int LIM> hipError_t set_lds(size_t bytes)
 {
-    hipError_t a = hipSuccess, c = hipSuccess;
-    if constexpr (DIM < 3) {
-        a = hipFuncSetAttribute(reinterpret_cast<const void *>(k_sweep_tile<T, DIM, LIM>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        if (LIM == LIM_NONE)
-            c = hipFuncSetAttribute(reinterpret_cast<const void *>(k_sweep_tile<T, DIM, LIM_NONE, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    auto allow = [&](const void *k) { return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); };
+    hipError_t e = hipSuccess, r;
+    if ((r = allow(reinterpret_cast<const void *>(k_sweep_tile<T, 2, LIM>))) != hipSuccess) e = r;
+    if ((r = allow(reinterpret_cast<const void *>(k_transient_tile<T, 2, LIM>))) != hipSuccess) e = r;
+    if constexpr (LIM == LIM_NONE) {
+        if ((r = allow(reinterpret_cast<const void *>(k_sweep_tile<T, 1, LIM_NONE, true>))) != hipSuccess) e = r;
+        if ((r = allow(reinterpret_cast<const void *>(k_sweep_tile<T, 2, LIM_NONE, true>))) != hipSuccess) e = r;
     }
-    hipError_t b = hipFuncSetAttribute(reinterpret_cast<const void *>(k_transient_tile<T, DIM, LIM>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    return a != hipSuccess ? a : (b != hipSuccess ? b : c);
+    return e;
 }
 
 // allow the dynamic LDS the tiles need (above the 64 KiB default)
 hipError_t tile_kernels_init(size_t max_bytes)
 {
     hipError_t e = hipSuccess, r;
-#define BTE_LDS(T, DIM, LIM)                                                                                         \
-    if ((r = set_lds<T, DIM, LIM>(max_bytes)) != hipSuccess) e = r;
-    BTE_LDS(float, 1, 0) BTE_LDS(float, 1, 1) BTE_LDS(float, 1, 2)
-    BTE_LDS(float, 2, 0) BTE_LDS(float, 2, 1) BTE_LDS(float, 2, 2)
-    BTE_LDS(float, 3, 0) BTE_LDS(float, 3, 1) BTE_LDS(float, 3, 2)
-    BTE_LDS(double, 1, 0) BTE_LDS(double, 1, 1) BTE_LDS(double, 1, 2)
-    BTE_LDS(double, 2, 0) BTE_LDS(double, 2, 1) BTE_LDS(double, 2, 2)
-    BTE_LDS(double, 3, 0) BTE_LDS(double, 3, 1) BTE_LDS(double, 3, 2)
+#define BTE_LDS(T, LIM)                                                                                              \
+    if ((r = set_lds<T, LIM>(max_bytes)) != hipSuccess) e = r;
+    BTE_LDS(float, 0) BTE_LDS(float, 1) BTE_LDS(float, 2)
+    BTE_LDS(double, 0) BTE_LDS(double, 1) BTE_LDS(double, 2)
 #undef BTE_LDS
     return e;
 }
