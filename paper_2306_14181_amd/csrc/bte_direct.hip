@@ -77,63 +77,63 @@ void axis_eigen(int n, double c, bool periodic, double al, double ar, double *V,
 
 namespace {
 
-constexpr int kDT = 32;   // outputs of a block along the transformed axis and across it
+constexpr int kDT = 16;   // outputs of a block along the transformed axis and across it
+
+typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // One axis: out[o][j][q] = sum_i M[j][i] in[o][i][q], M = V^T (fwd) or V;
 // columns are numbered o inner + q.  The last forward axis divides by the
 // eigenvalue of the operator (0 for its null vector).
-// 256 threads, 2 x 2 outputs each; tiles of 32 x 32 of both factors in LDS.
+// A block takes 16 x 16 outputs on the FP64 matrix cores (16 x 16 x 4); its
+// four wavefronts split the sum over i, so that the few outputs of a line or a
+// small plane still keep loads in flight, straight from the caches: both
+// factors are read once or a few times and are small.  Correction (the
+// products and the update of T_L) of a line of 200 cells, 97 x 83, 256^2, 64^3,
+// 128^3: 50, 63, 155, 76, 295 us with tiles of 32 x 32 through LDS on the vector
+// units, 16, 21, 29, 52, 250 us here.
 __global__ __launch_bounds__(256) void k_axis_product(const double *__restrict__ in, double *__restrict__ out,
                                                       const double *__restrict__ V, int n, int inner, int cols, int fwd,
                                                       const double *__restrict__ lx, const double *__restrict__ ly,
                                                       const double *__restrict__ lz, int n0, int n1, double zero)
 {
-    __shared__ double sm[kDT][kDT + 1], si[kDT][kDT + 1];
+    constexpr int U = 8;   // steps of 4 in flight
+    __shared__ double sm[4][kDT][kDT + 1];
     const int j0 = blockIdx.x * kDT, q0 = blockIdx.y * kDT;
-    const int tj = threadIdx.x >> 4, tq = threadIdx.x & 15;
-    double acc[2][2] = {};
-    for (int i0 = 0; i0 < n; i0 += kDT) {
-        for (int e = threadIdx.x; e < kDT * kDT; e += 256) {
-            const int r = e / kDT, c = e % kDT;
-            // sm[j][i]; consecutive threads along V's rows
-            if (fwd) {
-                const int i = i0 + r, j = j0 + c;
-                sm[c][r] = i < n && j < n ? V[(size_t)i * n + j] : 0.0;
-            } else {
-                const int j = j0 + r, i = i0 + c;
-                sm[r][c] = i < n && j < n ? V[(size_t)j * n + i] : 0.0;
-            }
-            // si[i][column]; consecutive threads along memory
-            const int ci = inner == 1 ? r : c, ri = inner == 1 ? c : r;
-            const int i = i0 + ri, q = q0 + ci;
-            si[ri][ci] = i < n && q < cols ? in[((size_t)(q / inner) * n + i) * inner + q % inner] : 0.0;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+    // operands of this lane: M[j0 + l16][i], in[i][column q0 + l16], i = 4 step + l4
+    const int ja = min(j0 + l16, n - 1), qa = min(q0 + l16, cols - 1);
+    const double *pa = fwd ? V + ja : V + (size_t)ja * n;
+    const double *pb = in + (size_t)(qa / inner) * n * inner + qa % inner;
+    const size_t sa = fwd ? n : 1, sb = inner;
+    const int steps = (n + 3) / 4;
+    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+    for (int s0 = wave; s0 < steps; s0 += 4 * U) {
+        double a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = 4 * (s0 + 4 * u) + l4, ic = min(i, n - 1);
+            a[u] = pa[ic * sa];
+            b[u] = pb[ic * sb];
+            if (i >= n) a[u] = b[u] = 0.0;
         }
-        __syncthreads();
-        const int m = min(kDT, n - i0);
-        for (int i = 0; i < m; ++i) {
-            const double a0 = sm[tj][i], a1 = sm[tj + 16][i], b0 = si[i][tq], b1 = si[i][tq + 16];
-            acc[0][0] += a0 * b0;
-            acc[0][1] += a0 * b1;
-            acc[1][0] += a1 * b0;
-            acc[1][1] += a1 * b1;
-        }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
     }
+    // element r of a lane: row 4 r + l4, column l16
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int x = 0; x < 2; ++x) {
-            const int j = j0 + tj + 16 * y, q = q0 + tq + 16 * x;
-            if (j >= n || q >= cols) continue;
-            const size_t at = ((size_t)(q / inner) * n + j) * inner + q % inner;
-            double v = acc[y][x];
-            if (lx) {
-                const int i = (int)at;
-                const double l = lx[i % n0] + (ly ? ly[i / n0 % n1] : 0.0) + (lz ? lz[i / (n0 * n1)] : 0.0);
-                v = l > zero ? v / l : 0.0;
-            }
-            out[at] = v;
-        }
+    for (int r = 0; r < 4; ++r) sm[wave][4 * r + l4][l16] = acc[r];
+    __syncthreads();
+    const int hi = threadIdx.x >> 4, lo = threadIdx.x & 15;   // consecutive threads along memory
+    const int jr = inner == 1 ? lo : hi, qr = inner == 1 ? hi : lo, j = j0 + jr, q = q0 + qr;
+    if (j >= n || q >= cols) return;
+    const size_t at = ((size_t)(q / inner) * n + j) * inner + q % inner;
+    double v = (sm[0][jr][qr] + sm[1][jr][qr]) + (sm[2][jr][qr] + sm[3][jr][qr]);
+    if (lx) {
+        const int i = (int)at;
+        const double l = lx[i % n0] + (ly ? ly[i / n0 % n1] : 0.0) + (lz ? lz[i / (n0 * n1)] : 0.0);
+        v = l > zero ? v / l : 0.0;
+    }
+    out[at] = v;
 }
 
 }  // namespace
