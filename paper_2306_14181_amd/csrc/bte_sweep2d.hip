@@ -12,10 +12,14 @@
 // each handing the increments of its last row to the next through LDS.
 // Everything that depends only on the cell (global index, geometry code,
 // T_L, scattering rate, source, pending correction) is loaded once, one
-// cell per lane, and read back with readlane or broadcast LDS loads.  The
-// FP64 moment partials of a row are reduced through a small LDS transpose.
-// With two rows per wavefront, at 124 VGPRs and 26 KiB of LDS (FP32), four
-// blocks share a compute unit.
+// cell per lane, and read back with readlane or broadcast LDS loads.  Rows
+// whose cells all have an interior stencil take straight-line code.  The FP64
+// moment partials of two rows are a product on the matrix cores.
+// Bound by the latency of each block (loads, wait for the upwind tiles,
+// recurrence, stores) and by issue.  256^2 cells x 2560 lanes FP32, one launch:
+// 0.758 ms with a branch per cell and the moments on the vector units (1236
+// VALU, 962 SALU and 145 LDS instructions a wavefront), 0.747 with the moments
+// on the matrix cores, 0.668 with the straight-line rows too (871, 665, 91).
 #include "bte_internal.h"
 #include "bte_stencil.h"
 #include "bte_tile.h"
@@ -26,7 +30,8 @@ namespace bte {
 namespace {
 
 constexpr int kTX = 8, kTY = 8;
-constexpr int kWS = 65;   // row stride of a staged row in the moment transpose
+
+typedef double double4v __attribute__((ext_vector_type(4)));
 
 struct Frame2 {
     int o0, o1, e0, e1, sg0, sg1, n0, n1, cell0, per0, per1;
@@ -193,6 +198,11 @@ __device__ inline int diffuse_rank2(uint32_t code, int f)
     return n;
 }
 
+// Scalars of a tile cell, read at once.
+template <typename T> struct alignas(16) Rec4 {
+    T gam, tl, qs, pad;
+};
+
 // Per tile cell mode word (built once per wave, read as a uniform value)
 enum : uint32_t {
     W_SOLID = 1u, W_FX = 2u, W_FY = 4u,        // solid; interior stencil along x / y
@@ -203,12 +213,13 @@ enum : uint32_t {
 
 // Occupancy the compiler is held to (waves per SIMD) for kRW rows per
 // wavefront, FP32: four waves per SIMD at one or two rows (four blocks of
-// four wavefronts per compute unit at two rows), two at four rows; the
-// one-launch form, which keeps a few more values across its wait, three
-// (four would spill).  FP64: two (its registers allow no more without spills).
-template <typename T, int kRW, bool QUEUE> constexpr int sweep2d_waves()
+// four wavefronts per compute unit at two rows; the one-launch form, which
+// keeps a few more values across its wait, spills 7 of them and is faster for
+// it: batch of 24 films 2.34 ms at three waves, 2.18 at four), two at four
+// rows.  FP64: two (its registers allow no more without spills).
+template <typename T, int kRW> constexpr int sweep2d_waves()
 {
-    return sizeof(T) == 8 ? 2 : (kRW == 4 ? 2 : (QUEUE ? 3 : 4));
+    return sizeof(T) == 8 ? 2 : (kRW == 4 ? 2 : 4);
 }
 
 // QUEUE: the whole sweep in one launch, one block per item: a block takes
@@ -217,25 +228,27 @@ template <typename T, int kRW, bool QUEUE> constexpr int sweep2d_waves()
 // (queue_wait) before it reads their new values, and publishes its own
 // after its stores.  Otherwise the launch covers one tile diagonal.
 template <typename T, int LIM, int kRW, bool QUEUE>
-__global__ __launch_bounds__(64 * (kTY / kRW), (sweep2d_waves<T, kRW, QUEUE>())) void k_sweep2d(
+__global__ __launch_bounds__(64 * (kTY / kRW), (sweep2d_waves<T, kRW>())) void k_sweep2d(
     Dev d, const T *__restrict__ ein, T *__restrict__ eout, const double *__restrict__ dpend,
     const double *__restrict__ TLdev, const double *__restrict__ din, const Sweep2Item *__restrict__ items,
     int item0, int na_oct, int nchunk_oct, double *__restrict__ part, unsigned *__restrict__ queue)
 {
     constexpr int kWT = kTY / kRW;   // wavefronts per tile (one block)
-    // moment weights of lane l2 = 8 p + q at lc[q][m][p]: the lanes of the
-    // row transpose below read the eight p of one (q, m) at once, eight
-    // consecutive doubles (no bank conflicts)
-    __shared__ double lc[8][kMomN][8];
+    // staged cells' values lie kMS apart: 16 cells' reads of 16 bytes at the
+    // same lane take 64 different banks
+    constexpr int kMS = sizeof(T) == 4 ? 68 : 66;
+    // moment weights of the lanes; the last row is zero
+    __shared__ alignas(16) double lc[kMomN + 1][66];
     // increments of the last row of wavefront w, read by wavefront w + 1
     __shared__ T sH[64][kTX];
     // Per wavefront: a staging area of one row (diffuse inflow values, slot
-    // 2 j + axis; then the row's new values for the moment transpose) and
+    // 2 j + axis; then the new values of two rows for the moments) and
     // the per-cell scalars of the tile (x = pending correction plus jump,
     // gamma, T_L, source; halo x), read back as broadcast LDS loads rather
     // than lane-by-lane register broadcasts.
-    __shared__ T sStg[kWT][16][64];
-    __shared__ T sPC[kWT][4][64];
+    __shared__ alignas(16) T sStg[kWT][16 * kMS];
+    __shared__ T sPX[kWT][64];
+    __shared__ alignas(16) Rec4<T> sPC[kWT][64];
     __shared__ T sHX[kWT][64];
     int item = item0 + (int)blockIdx.x;
     if constexpr (QUEUE) {
@@ -273,12 +286,12 @@ __global__ __launch_bounds__(64 * (kTY / kRW), (sweep2d_waves<T, kRW, QUEUE>()))
     const T cp0 = (T)(vq * fabs(s0) * it.ih0), cp1 = (T)(vq * fabs(s1) * it.ih1);
     const T hh0 = (T)(0.5 * it.h0), hh1 = (T)(0.5 * it.h1), ih0 = (T)it.ih0, ih1 = (T)it.ih1;
     if (w == 0) {
-        double *lq = &lc[lane & 7][0][lane >> 3];
-        lq[0] = active ? wq : 0.0;
-        lq[8] = active ? wq * itq : 0.0;
-        lq[16] = active ? wq * vq * s0 : 0.0;
-        lq[24] = active ? wq * vq * s1 : 0.0;
-        lq[32] = active ? wq * vq * s2 : 0.0;
+        lc[0][lane] = active ? wq : 0.0;
+        lc[1][lane] = active ? wq * itq : 0.0;
+        lc[2][lane] = active ? wq * vq * s0 : 0.0;
+        lc[3][lane] = active ? wq * vq * s1 : 0.0;
+        lc[4][lane] = active ? wq * vq * s2 : 0.0;
+        lc[5][lane] = 0.0;
     }
     const Frame2 F = frame2(it);
     const int e0 = F.e0, e1 = F.e1;
@@ -408,12 +421,10 @@ __global__ __launch_bounds__(64 * (kTY / kRW), (sweep2d_waves<T, kRW, QUEUE>()))
         t_x = sol ? (T)t_xd : (T)0;
         h_x = (T)(h_xd + h_j);
     }
-    T *const px = &sPC[w][0][0], *const pgam = &sPC[w][1][0], *const ptl = &sPC[w][2][0],
-            *const pqs = &sPC[w][3][0], *const phx = &sHX[w][0];
+    T *const px = &sPX[w][0], *const phx = &sHX[w][0];
+    Rec4<T> *const prec = &sPC[w][0];
     px[lane] = t_x;
-    pgam[lane] = t_gam;
-    ptl[lane] = t_tl;
-    pqs[lane] = t_qs;
+    prec[lane] = {t_gam, t_tl, t_qs, (T)0};
     phx[lane] = h_x;
     const T A0 = cp0 + cp1 + itau;
     // x of the cells of row q (tile row, or halo row -2, -1, e1)
@@ -421,7 +432,7 @@ __global__ __launch_bounds__(64 * (kTY / kRW), (sweep2d_waves<T, kRW, QUEUE>()))
         return (q >= 0 && q < e1) ? px + 8 * q : phx + (q == -2 ? 0 : (q == -1 ? 8 : 16));
     };
     auto row_x = [&](int q, int j) -> T { return row_xp(q)[j]; };
-    T *const wl = &sStg[w][0][0];   // staging of one row of this wavefront
+    T *const wl = &sStg[w][0];   // staging of one row of this wavefront
 
     // corrected window and x halo
 #pragma unroll
@@ -477,6 +488,36 @@ __global__ __launch_bounds__(64 * (kTY / kRW), (sweep2d_waves<T, kRW, QUEUE>()))
     // uncoupled upwind increment is dropped by a zero factor (inside the
     // tile every increment is finite; the seeds are selected)
     T aa[kRW][kTX], rdn[kRW][kTX];
+    auto finish = [&](int i, int j, int t, T dx, T dy) {
+        const Rec4<T> rc = prec[t];
+        const T ec = y[i + 2][j];
+        const T num = -(cp0 * dx + cp1 * dy) - (ec - C4 * rc.tl) * (itau + rc.gam) + C4 * rc.qs;
+        const T den = A0 + rc.gam;
+        T rden;
+        if constexpr (sizeof(T) == 4) rden = __builtin_amdgcn_rcpf(den);
+        else rden = (T)1 / den;
+        aa[i][j] = num * rden;
+        rdn[i][j] = rden;
+    };
+    // rows whose cells all have an interior stencil: straight-line code, its
+    // LDS reads and arithmetic of 16 cells overlapping (cell by cell under
+    // branches each waits for its own)
+    constexpr uint32_t kIn = W_SOLID | W_FX | W_FY;
+    const uint64_t mine = (kRW == 8 ? ~0ull : (1ull << (8 * kRW)) - 1) << (8 * rb);
+    const bool interior = nrow == kRW && (__ballot((t_w & kIn) == kIn) & mine) == mine;
+    if (interior) {
+#pragma unroll
+        for (int i = 0; i < kRW; ++i) {
+            const T *ym2 = y[i], *ym1 = y[i + 1], *ec = y[i + 2], *yp1 = y[i + 3];
+#pragma unroll
+            for (int j = 0; j < kTX; ++j) {
+                const T ex2 = j >= 2 ? ec[j - 2] : xh[i][j], ex1 = j >= 1 ? ec[j - 1] : xh[i][1];
+                const T exd = j + 1 < kTX ? ec[j + 1] : xh[i][2];
+                finish(i, j, 8 * (rb + i) + j, delta_fast<T, LIM>(ex2, ex1, ec[j], exd),
+                       delta_fast<T, LIM>(ym2[j], ym1[j], ec[j], yp1[j]));
+            }
+        }
+    } else
 #pragma unroll
     for (int i = 0; i < kRW; ++i) {
         if (i >= nrow) break;
@@ -526,7 +567,6 @@ __global__ __launch_bounds__(64 * (kTY / kRW), (sweep2d_waves<T, kRW, QUEUE>()))
         for (int j = 0; j < kTX; ++j) {
             const int t = 8 * r + j;
             const uint32_t wd = (uint32_t)rl((int)t_w, t);
-            T num = (T)0, rden = (T)0;
             if (wd & W_SOLID) {
                 const T ex2 = j >= 2 ? ec[j - 2] : (j == 1 ? xh1 : xh0);
                 const T ex1 = j >= 1 ? ec[j - 1] : xh1;
@@ -562,15 +602,10 @@ __global__ __launch_bounds__(64 * (kTY / kRW), (sweep2d_waves<T, kRW, QUEUE>()))
                                                ym1[j], ec[j], yp1[j], fw, cd, xd, (double)px[t], al, l, active,
                                                C4, hh1, ih1, nk);
                 }
-                const T gam = pgam[t];
-                const T itc = itau + gam;
-                num = -(cp0 * dx + cp1 * dy) - (ec[j] - C4 * ptl[t]) * itc + C4 * pqs[t];
-                const T den = A0 + gam;
-                if constexpr (sizeof(T) == 4) rden = __builtin_amdgcn_rcpf(den);
-                else rden = (T)1 / den;
+                finish(i, j, t, dx, dy);
+                continue;
             }
-            aa[i][j] = num * rden;
-            rdn[i][j] = rden;
+            aa[i][j] = rdn[i][j] = (T)0;
         }
     }
 
@@ -640,55 +675,48 @@ __global__ __launch_bounds__(64 * (kTY / kRW), (sweep2d_waves<T, kRW, QUEUE>()))
     // streamed out (nontemporal stores): no launch reads them back through
     // this L2, and dirty lines left in it would be written back at the end
     // of the launch, in the gap before the next diagonal.
+    // The moments of 16 cells (two rows) are a product of the five weights of
+    // the 64 lanes with the cells' values: 16 steps of the FP64 matrix cores,
+    // lane group g of 16 taking the lanes 16 g + step.
+    constexpr int kRM = kRW == 1 ? 1 : 2;   // rows of a product
 #pragma unroll
-    for (int i = 0; i < kRW; ++i) {
-        if (i >= nrow) break;
-        const int r = rb + i;
-        const int b = cbase + rowstep * r;
+    for (int h = 0; h < kRW; h += kRM) {
+        if (h >= nrow) break;
 #pragma unroll
-        for (int j = 0; j < kTX; ++j) {
-            T en = (T)0;
-            if (j < e0) {
-                en = y[i + 2][j] + dv[i][j];
-                if (active) {
-                    if constexpr (QUEUE) dev_store(&eout[(size_t)(b + sx * j) * nk + k], en);
-                    else __builtin_nontemporal_store(en, &eout[(size_t)(b + sx * j) * nk + k]);
+        for (int i = h; i < h + kRM; ++i) {
+            if (i >= nrow) break;
+            // the row's cells lie sx nk values apart
+            T *const row = eout + (size_t)(cbase + rowstep * (rb + i)) * nk;
+#pragma unroll
+            for (int j = 0; j < kTX; ++j) {
+                T en = (T)0;
+                if (j < e0) {
+                    en = y[i + 2][j] + dv[i][j];
+                    if (active) {
+                        T *const at = row + (ptrdiff_t)(sx * j) * nk + k;
+                        if constexpr (QUEUE) dev_store(at, en);
+                        else __builtin_nontemporal_store(en, at);
+                    }
                 }
+                wl[(8 * (i - h) + j) * kMS + lane] = active ? en : (T)0;
             }
-            wl[j * kWS + lane] = active ? en : (T)0;
         }
-        // lane = 8 cell + part: part sums 8 of the 64 lanes (the staged row
-        // has a stride of 65 values: the 64 lanes read 64 distinct banks)
-        const int j = lane >> 3, p = lane & 7;
-        double acc[kMomN] = {0, 0, 0, 0, 0};
+        const int n16 = lane & 15, g = lane >> 4, col = kRM == 1 ? n16 & 7 : n16;
+        const T *const xr = wl + col * kMS + 16 * g;
+        const double *const wr = &lc[n16 < kMomN ? n16 : kMomN][16 * g];
+        double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const double x = (double)wl[j * kWS + 8 * p + q];
-#pragma unroll
-            for (int m = 0; m < kMomN; ++m) acc[m] += lc[q][m][p] * x;
-        }
-#pragma unroll
-        for (int m = 0; m < kMomN; ++m) {
-            // sum of the 8 lanes of a cell: quad butterflies, then the two
-            // quads of each half row (data-parallel-primitive moves, no LDS)
-            double v = acc[m];
-            v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
-            v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
-            v += dpp_f64<0x141>(v);   // row_half_mirror
-            acc[m] = v;
-        }
-        const int t = 8 * r + j;
+        for (int q = 0; q < 16; ++q) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(wr[q], (double)xr[q], acc, 0, 0, 0);
+        // lane (g, column): moment g, and moment 4 in group 0
+        const int t = 8 * (rb + h) + n16;
         const int c = __shfl(t_c, t, 64);
         const uint32_t wd = (uint32_t)__shfl((int)t_w, t, 64);
-        const double gm = __shfl(t_gamd, t, 64);
-        if (p == 0 && j < e0 && c >= 0) {
+        const double gm = __shfl(t_gamd, t, 64), m0 = __shfl(acc[0], n16, 64);
+        if (n16 < 8 * kRM && h + (n16 >> 3) < nrow && (n16 & 7) < e0 && c >= 0) {
             double *o = part + ((size_t)(it.oct * nchunk_oct + it.chunk) * d.nc + c) * kMomN;
             const bool sol = wd & W_SOLID;
-            __builtin_nontemporal_store(sol ? acc[0] : 0.0, &o[0]);
-            __builtin_nontemporal_store(sol ? acc[1] + gm * acc[0] : 0.0, &o[1]);
-            __builtin_nontemporal_store(sol ? acc[2] : 0.0, &o[2]);
-            __builtin_nontemporal_store(sol ? acc[3] : 0.0, &o[3]);
-            __builtin_nontemporal_store(sol ? acc[4] : 0.0, &o[4]);
+            __builtin_nontemporal_store(sol ? (g == 1 ? acc[0] + gm * m0 : acc[0]) : 0.0, &o[g]);
+            if (g == 0) __builtin_nontemporal_store(sol ? acc[1] : 0.0, &o[4]);
         }
     }
     if constexpr (QUEUE) {
