@@ -343,13 +343,16 @@ bte_status bte_set_graphs(bte_problem *p, int on);
 
 /* Launch form of the two-dimensional steady sweep (the transport sweep of
  * Algorithm 1, Sec. 3.3-3.5) with the register-tile kernel (8 x 8 tiles).
- * on == 0: one launch per tile diagonal (the default).  on != 0: one launch
+ * on == 0: one launch per tile diagonal.  on != 0: one launch
  * per sweep; each block takes a ticket (the work items in sweep order),
  * does everything that reads only the previous iterate, then waits for the
  * items of its x- and y-upwind tiles and reads their new values.  The
  * results are bitwise those of the launch-per-diagonal form.  Every wait is
  * bounded: a wait that gives up (about a second) sets an abort word, the
- * launch ends, and bte_steady_solve returns BTE_ERR_HIP.  Errors:
+ * launch ends, and bte_steady_solve returns BTE_ERR_HIP.  Without a call the
+ * library takes the faster form for the problem (one launch where a tile
+ * diagonal has few work items) and, if a wait gives up, goes on with one
+ * launch per diagonal.  Errors:
  * BTE_ERR_UNSUPPORTED for a one- or three-dimensional problem (on != 0);
  * the LDS-tile shapes of a 2D problem keep one launch per diagonal. */
 bte_status bte_set_persistent(bte_problem *p, int on);

@@ -463,7 +463,8 @@ class Problem:
 
     def set_persistent(self, on=False):
         """Launch form of the two-dimensional register-tile sweep: one launch per tile diagonal
-        (on=False) or one launch per sweep (on=True; BteError in 1D and 3D)."""
+        (on=False) or one launch per sweep (on=True; BteError in 1D and 3D).  Without a call the library
+        takes the faster form for the problem."""
         self._check(load().bte_set_persistent(self._h, int(bool(on))))
 
     def tile_candidates(self, kind):

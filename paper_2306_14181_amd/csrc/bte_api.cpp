@@ -90,7 +90,7 @@ void launch_film_eps(const Dev &, const double *, const double *, const double *
 void launch_film_mean(const Dev &, const double *, double *, double *, int, hipStream_t);
 void launch_sub_film_mean(const Dev &, double *, const double *, hipStream_t);
 void launch_tl_update(int, const double *, const double *, double *, double *, const int *, const int *,
-                      hipStream_t);
+                      const unsigned *, hipStream_t);
 void launch_cg_coef(const Dev &, const CgArgs &, double *, double *, hipStream_t);
 void launch_diff_rhs(const Dev &, const CgArgs &, double *, hipStream_t);
 void launch_cg_begin(const Dev &, const CgArgs &, const double *, hipStream_t);
@@ -277,7 +277,7 @@ struct bte_problem {
     // private stream (the caller's may be the null stream, which cannot be
     // captured) and replayed on the caller's stream
     bool graphs = true;
-    bool persistent = false;   // 2D register-tile sweeps in one launch (bte_set_persistent)
+    int persistent = -1;       // 2D register-tile sweeps in one launch: 0, 1 (bte_set_persistent), -1: one_launch's rule
     bool queue_ok = false;     // every item's upwind items precede it (build_schedule)
     hipStream_t cstream = nullptr;
     ~bte_problem()
@@ -543,6 +543,21 @@ int tile_cap_of(const bte_problem *p, int3 td)
 // kernel.  The LDS-tile kernels (and the 2D adjoint sweep, which has no
 // register form) take the shape with z = 1 then.
 bool reg2d(const bte_problem *p) { return p->dim == 2 && p->tdim.x == 8 && p->tdim.y == 8; }
+// 2D sweeps in one launch: as the caller chose, else where the tile diagonals
+// are short.  A launch per diagonal costs its start and its last, part-empty
+// round each time; one launch costs each block its ticket and its wait for the
+// upwind tiles, and wins while a diagonal fills the chip's 1024 resident blocks
+// at most about once.  ms per sweep, launch per diagonal / one launch, FP32
+// unless noted, by items per diagonal: 97 x 83 FP64 (50) 0.343 / 0.142; squares
+// of 64 (171) 0.211 / 0.130, 256 (650) 1.129 / 0.668, 512 (1290) 3.18 / 2.37;
+// batches of 24 films of 30 to 200 cells a side (1300) 2.19 / 2.19, of 96 (5000)
+// 7.22 / 8.51, of 200 films of 16 to 40 (3200) 1.10 / 1.23.
+bool one_launch(const bte_problem *p)
+{
+    if (!reg2d(p) || !p->queue_ok) return false;
+    if (p->persistent >= 0) return p->persistent != 0;
+    return p->items.size() <= 1536 * (p->diag_off.size() - 1);
+}
 int3 lds_tdim(const bte_problem *p) { return reg2d(p) ? make_int3(8, 8, 1) : p->tdim; }
 
 // Tile shapes the LDS-tile kernels may use for one kind (bte_tune_kind), the
@@ -1642,7 +1657,7 @@ template <typename F> hipError_t graph_run(Graph &gr, hipStream_t cs, hipStream_
 // One forward sweep (every tile-diagonal launch) from ein into eout: whole
 // lines in one launch in 1D, the register-tile kernel for 2D geometries with
 // 8 x 8 tiles, the column segments in 3D, the LDS tiles otherwise.
-template <typename T> hipError_t sweep_launches(bte_problem *p, const T *ein, T *eout, hipStream_t q)
+template <typename T> hipError_t sweep_launches(bte_problem *p, const T *ein, T *eout, hipStream_t q, bool one)
 {
     const Dev &d = p->dev;
     if (p->dim == 1) {
@@ -1652,7 +1667,7 @@ template <typename T> hipError_t sweep_launches(bte_problem *p, const T *ein, T 
     }
     const bool reg = reg2d(p);
     const int3 lt = lds_tdim(p);
-    if (reg && p->persistent && p->queue_ok) {
+    if (one) {
         // the whole sweep in one launch: every item waits for its upwind items
         const int n = (int)p->items2.size();
         hipError_t r = launch_queue_reset(p->d_queue, n, q);
@@ -1720,21 +1735,24 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
     double active_cells = 0;
     for (const Film &fm : p->films) active_cells += fm.ncell;
     Graph gsweep[2], gcg;   // captured in this call, replayed by its iterations
+    bool gave_up = false;   // a one-launch sweep that nobody asked for gave up waiting: launches per diagonal from then on
     if (p->graphs && !p->cstream) HIPCHK(p, hipStreamCreateWithFlags(&p->cstream, hipStreamNonBlocking));
     for (int iter = 1; iter <= p->ctl.max_iter; ++iter) {
         const T *ein = buf[cur];
         T *eout = buf[1 - cur];
+        const bool one = one_launch(p) && !gave_up;
+        const unsigned *qword = one ? p->d_queue + 1 : nullptr;
         st.updates += active_cells * (double)p->nk;
         HIPCHK(p, hipEventRecord(ev[0], s));
         launch_walls<T>(d, ein, p->dpend, p->d_wrec, p->d_wden, p->din, p->nw, s);
         HIPCHK(p, hipEventRecord(ev[1], s));
-        auto sweep = [&](hipStream_t q) -> bool { return sweep_launches<T>(p, ein, eout, q) == hipSuccess; };
-        if (p->graphs) {
+        auto sweep = [&](hipStream_t q) -> bool { return sweep_launches<T>(p, ein, eout, q, one) == hipSuccess; };
+        if (p->graphs && !gave_up) {
             HIPCHK(p, graph_run(gsweep[cur], p->cstream, s, sweep));
         } else if (!sweep(s)) {
             FAIL(p, BTE_ERR_HIP, "sweep launch failed");
         }
-        if (p->dim == 1 || (reg2d(p) && p->persistent && p->queue_ok)) st.sweep_launches += 1;
+        if (p->dim == 1 || one) st.sweep_launches += 1;
         else
             for (size_t dg = 0; dg + 1 < p->diag_off.size(); ++dg)
                 st.sweep_launches += p->diag_off[dg + 1] > p->diag_off[dg];
@@ -1757,23 +1775,30 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
             } else if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s)) {
                 FAIL(p, BTE_ERR_HIP, "CG failed");
             }
-            launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, s);
+            launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, qword, s);
         } else {
-            launch_tl_update(nc, p->TLkin, nullptr, p->TL, nullptr, d.fid, d.fdone, s);
+            launch_tl_update(nc, p->TLkin, nullptr, p->TL, nullptr, d.fid, d.fdone, qword, s);
         }
         HIPCHK(p, hipEventRecord(ev[4], s));
         HIPCHK(p, hipMemcpyAsync(feps.data(), p->feps, 8 * feps.size(), hipMemcpyDeviceToHost, s));
         unsigned qabort = 0, cg_abort = 0;
-        if (reg2d(p) && p->persistent && p->queue_ok)
-            HIPCHK(p, hipMemcpyAsync(&qabort, p->d_queue + 1, 4, hipMemcpyDeviceToHost, s));
+        if (one) HIPCHK(p, hipMemcpyAsync(&qabort, qword, 4, hipMemcpyDeviceToHost, s));
         if (cg_epoch) HIPCHK(p, hipMemcpyAsync(&cg_abort, p->cgplan.abortw, 4, hipMemcpyDeviceToHost, s));
         HIPCHK(p, hipStreamSynchronize(s));
+        if (qabort) {
+            if (p->persistent > 0) FAIL(p, BTE_ERR_HIP, "one-launch sweep: a wait for an upwind tile gave up");
+            // T_L and the pending correction are still those of this iteration's start: the iteration again
+            gave_up = true;
+            st.updates -= active_cells * (double)p->nk;
+            st.sweep_launches -= 1;
+            --iter;
+            continue;
+        }
         if (cg_epoch && cg_abort == cg_epoch) {
             // the blocks gave up waiting for each other: this correction again, a launch per iteration
             if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
-            launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, s);
+            launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, qword, s);
         }
-        if (qabort) FAIL(p, BTE_ERR_HIP, "one-launch sweep: a wait for an upwind tile gave up");
         {
             float ms[4];
             for (int i = 0; i < 4; ++i) HIPCHK(p, hipEventElapsedTime(&ms[i], ev[i], ev[i + 1]));
@@ -2041,7 +2066,7 @@ bte_status adjoint_impl(bte_problem *p, const T *e, double *grad, bte_solve_stat
             // v = L^-1 P^T y; the sweep's isotropic term becomes X + v
             if (!run_cg_now(p, 1, p->adju, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s))
                 FAIL(p, BTE_ERR_HIP, "CG failed");
-            launch_tl_update(nc, p->adjX, p->delta, p->TL, nullptr, nullptr, nullptr, s);
+            launch_tl_update(nc, p->adjX, p->delta, p->TL, nullptr, nullptr, nullptr, nullptr, s);
             X = p->TL;
         }
         HIPCHK(p, hipEventRecord(ev[3], s));
@@ -2466,8 +2491,8 @@ bte_status use_tiles(bte_problem *p, int kind, int3 t)
     build_schedule(p);
     if (p->items.size() > p->items_cap || p->titems.size() > p->titems_cap)
         FAIL(p, BTE_ERR_STATE, "work list larger than its reserved room");
-    if (p->persistent && !p->queue_ok) {
-        p->persistent = false;
+    if (p->persistent > 0 && !p->queue_ok) {
+        p->persistent = 0;
         FAIL(p, BTE_ERR_STATE, "sweep order: an item precedes one of its upwind items");
     }
     HIPCHK(p, hipMemcpy(p->d_items, p->items.data(), sizeof(SweepItem) * p->items.size(), hipMemcpyHostToDevice));
@@ -2501,7 +2526,7 @@ template <typename T> hipError_t tune_run(bte_problem *p, int kind, const T *ein
         return launch_transient_tile<T>(d, ein, eout, p->TL, p->din, p->d_titems, (int)p->titems.size(),
                                         p->tdim_tr, p->na_oct, p->nchunk_oct, p->tile_cap_tr, 0.0, p->ctl.dt,
                                         p->part, s);
-    return sweep_launches<T>(p, ein, eout, s);
+    return sweep_launches<T>(p, ein, eout, s, one_launch(p));
 }
 
 template <typename T>

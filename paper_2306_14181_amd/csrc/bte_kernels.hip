@@ -664,13 +664,14 @@ __global__ void k_sub_film_mean(Dev d, double *__restrict__ x, const double *__r
 }
 
 // T_L^{n+1} = T_L^kin + delta, pending correction = delta (cells of
-// converged geometries keep both, when fid / fdone are given)
+// converged geometries keep both, when fid / fdone are given; all cells keep
+// them when the sweep's abort word, if given, is set)
 __global__ void k_tl_update(int n, const double *__restrict__ TLkin, const double *__restrict__ delta,
                             double *__restrict__ TL, double *__restrict__ dpend, const int *__restrict__ fid,
-                            const int *__restrict__ fdone)
+                            const int *__restrict__ fdone, const unsigned *__restrict__ abortw)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n) return;
+    if (c >= n || (abortw && *abortw)) return;
     if (fdone && fdone[fid[c]]) return;
     const double dl = delta ? delta[c] : 0.0;
     TL[c] = TLkin[c] + dl;
@@ -1114,10 +1115,10 @@ void launch_sub_film_mean(const Dev &d, double *x, const double *mean, hipStream
 }
 
 void launch_tl_update(int n, const double *TLkin, const double *delta, double *TL, double *dpend, const int *fid,
-                      const int *fdone, hipStream_t s)
+                      const int *fdone, const unsigned *abortw, hipStream_t s)
 {
     hipLaunchKernelGGL(k_tl_update, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, n, TLkin, delta, TL, dpend,
-                       fid, fdone);
+                       fid, fdone, abortw);
 }
 
 void launch_cg_coef(const Dev &d, const CgArgs &g, double *coef, double *dg, hipStream_t s)
