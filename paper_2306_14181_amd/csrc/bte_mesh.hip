@@ -31,6 +31,7 @@
 #include <map>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/bte.h"
@@ -93,12 +94,16 @@ struct DirPlan {
     int S, nb, ng, slots;  // items per step, bands per block, blocks per direction, LDS slots (zero slot first, waste last)
 };
 
-// Lane k of a cell's row.  BUF (FP32 states below 2 GiB): one buffer
-// descriptor over the whole state, the row's byte offset as the scalar
+// V consecutive bands of a row.
+template <typename T, int V> struct alignas(sizeof(T) * V) BandVec { T x[V]; };
+
+// Bands k .. k + V - 1 of a cell's row.  BUF (FP32 states below 2 GiB): one
+// buffer descriptor over the whole state, the row's byte offset as the scalar
 // offset and the lane's as the vector offset, so that a row costs no vector
 // address arithmetic; otherwise a plain load.
-template <typename T, bool BUF>
+template <typename T, bool BUF, int V>
 struct RowReader {
+    using Vec = BandVec<T, V>;
     const T *e;
     int nk, k;
     __amdgpu_buffer_rsrc_t r;
@@ -106,27 +111,50 @@ struct RowReader {
     {
         if constexpr (BUF) r = __builtin_amdgcn_make_buffer_rsrc((void *)e_, (short)0, nk_ * nc * 4, 0x00020000);
     }
-    __device__ T operator()(int c) const
+    __device__ Vec operator()(int c) const
     {
-        if constexpr (BUF && sizeof(T) == 4)
-            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, k * 4, c * nk * 4, 0));
-        else
-            return e[(size_t)c * nk + k];
+        if constexpr (BUF && sizeof(T) == 4) {
+            if constexpr (V == 4) return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(r, k * 4, c * nk * 4, 0));
+            else if constexpr (V == 2)
+                return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b64(r, k * 4, c * nk * 4, 0));
+            else return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b32(r, k * 4, c * nk * 4, 0));
+        } else {
+            return *reinterpret_cast<const Vec *>(e + (size_t)c * nk + k);
+        }
     }
 };
 
-// gradient of lane k of cell c: D components at g[(c * D + q) * nk + k]
-template <typename T, int D, bool BUF>
-__global__ __launch_bounds__(kBlock) void k_mesh_grad(MeshDev d, const T *__restrict__ e, T *__restrict__ g, int nkb)
+// Work of the gradient and the residual: a wavefront takes 64 V bands of one
+// cell, a block the same bands of four cells that follow each other in Morton
+// order, whose stencils share most rows.  With V = 16 bytes a lane the scalar
+// work per row (index, offset, weights) and the direction's face geometry
+// serve four times the bands.  FP32, gradient and residual of 48 000 tetrahedra
+// x 1920: 1.67 and 0.85 ms with a band a lane and a cell a block, 1.33 and 0.69
+// here (their sum 2.40 with 8 bytes a lane); of 27 900 triangles and
+// quadrilaterals x 2560: 0.53 and 0.60, here 0.35 and 0.39 (0.88).  The gradient
+// of a tetrahedron is 56 rows x 5 FP64 operations a band, 0.66 ms of issue.
+constexpr int kRhsCells = kBlock / 64;
+__device__ inline bool rhs_work(const MeshDev &d, int nch, int V, int &c, int &k)
 {
-    // block = (cell, block of 256 lanes); cells in the Morton visit order
-    const int i = blockIdx.x / nkb;
-    const int c = d.vorder[i];
-    const int k = (blockIdx.x - i * nkb) * kBlock + threadIdx.x;
-    if (k >= d.nk) return;
-    const RowReader<T, BUF> row(e, d.nk, k, d.nc);
-    const double ec = (double)row(c);
-    double y[3] = {0.0, 0.0, 0.0};
+    const int i = (int)(blockIdx.x / nch) * kRhsCells + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    k = ((int)(blockIdx.x % nch) * 64 + (int)(threadIdx.x & 63)) * V;
+    if (i >= d.nc || k >= d.nk) return false;
+    c = d.vorder[i];
+    return true;
+}
+
+// gradient of bands k .. of cell c: D components at g[(c * D + q) * nk + k]
+template <typename T, int D, bool BUF, int V>
+__global__ __launch_bounds__(kBlock) void k_mesh_grad(MeshDev d, const T *__restrict__ e, T *__restrict__ g, int nch)
+{
+    using Vec = BandVec<T, V>;
+    int c, k;
+    if (!rhs_work(d, nch, V, c, k)) return;
+    const RowReader<T, BUF, V> row(e, d.nk, k, d.nc);
+    const Vec ev = row(c);
+    double ec[V], y[V][3] = {};
+#pragma unroll
+    for (int i = 0; i < V; ++i) ec[i] = (double)ev.x[i];
     // stencil rows eight, then four at a time in flight (the loads do not
     // wait on each other's sums), summed in stencil order; the row indices
     // and offsets are read through pointers that step by whole groups, so
@@ -136,43 +164,42 @@ __global__ __launch_bounds__(kBlock) void k_mesh_grad(MeshDev d, const T *__rest
     int n = d.lsptr[c + 1] - j0;
     const int *nbp = d.lsnb + j0;
     const double *ldp = d.lsd + 3 * (size_t)j0;
-    const size_t nk = (size_t)d.nk;
+    auto add = [&](const Vec &v, const double *ld) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const double diff = (double)v.x[i] - ec[i];
+#pragma unroll
+            for (int q = 0; q < D; ++q) y[i][q] += ld[q] * diff;
+        }
+    };
     for (; n >= 8; n -= 8, nbp += 8, ldp += 24) {
-        T v[8];
+        Vec v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = row(nbp[u]);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const double diff = (double)v[u] - ec;
-#pragma unroll
-            for (int q = 0; q < D; ++q) y[q] += ldp[3 * u + q] * diff;
-        }
+        for (int u = 0; u < 8; ++u) add(v[u], ldp + 3 * u);
     }
     if (n >= 4) {
-        T v[4];
+        Vec v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) v[u] = row(nbp[u]);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const double diff = (double)v[u] - ec;
-#pragma unroll
-            for (int q = 0; q < D; ++q) y[q] += ldp[3 * u + q] * diff;
-        }
+        for (int u = 0; u < 4; ++u) add(v[u], ldp + 3 * u);
         n -= 4;
         nbp += 4;
         ldp += 12;
     }
-    for (; n > 0; --n, ++nbp, ldp += 3) {
-        const double diff = (double)row(*nbp) - ec;
-#pragma unroll
-        for (int q = 0; q < D; ++q) y[q] += ldp[q] * diff;
-    }
+    for (; n > 0; --n, ++nbp, ldp += 3) add(row(*nbp), ldp);
     const double *xi = d.xinv + 6 * (size_t)c;
-    const double gx = xi[0] * y[0] + xi[1] * y[1] + xi[2] * y[2];
-    const double gy = xi[1] * y[0] + xi[3] * y[1] + xi[4] * y[2];
-    g[((size_t)c * D) * d.nk + k] = (T)gx;
-    g[((size_t)c * D + 1) * d.nk + k] = (T)gy;
-    if constexpr (D == 3) g[((size_t)c * D + 2) * d.nk + k] = (T)(xi[2] * y[0] + xi[4] * y[1] + xi[5] * y[2]);
+    Vec o[D];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        o[0].x[i] = (T)(xi[0] * y[i][0] + xi[1] * y[i][1] + xi[2] * y[i][2]);
+        o[1].x[i] = (T)(xi[1] * y[i][0] + xi[3] * y[i][1] + xi[4] * y[i][2]);
+        if constexpr (D == 3) o[2].x[i] = (T)(xi[2] * y[i][0] + xi[4] * y[i][1] + xi[5] * y[i][2]);
+    }
+#pragma unroll
+    for (int q = 0; q < D; ++q) *reinterpret_cast<Vec *>(g + ((size_t)c * D + q) * d.nk + k) = o[q];
 }
 
 // outgoing second-order face value of lane k of cell c at the offset l of
@@ -218,11 +245,13 @@ __global__ __launch_bounds__(kBlock) void k_mesh_walls(MeshDev d, const T *__res
 // every face's loads are issued before the sums, which run in face order,
 // and the upwind side is picked per lane without branches (a lane with
 // s.n = 0 adds zero).
-template <typename T, int D, int NF>
-__device__ inline double interior_flux(const MeshDev &d, const T *__restrict__ e, const T *__restrict__ g, int c,
-                                       int k, int f0, const int *nbv, double sx, double sy, double sz)
+template <typename T, int D, int NF, int V>
+__device__ inline void interior_flux(const MeshDev &d, const T *__restrict__ e, const T *__restrict__ g, int c, int k,
+                                     int f0, const int *nbv, double sx, double sy, double sz, double (&acc)[V])
 {
-    double sn[NF], ev[NF], gv[NF][3], lo[NF][3];
+    using Vec = BandVec<T, V>;
+    double sn[NF], lo[NF][3];
+    Vec ev[NF], gv[NF][D];
 #pragma unroll
     for (int u = 0; u < NF; ++u) {
         const double *fg = d.fgeo + (size_t)(f0 + u) * kFG;
@@ -233,34 +262,36 @@ __device__ inline double interior_flux(const MeshDev &d, const T *__restrict__ e
         const double m = own ? 0.0 : 1.0;
 #pragma unroll
         for (int q = 0; q < D; ++q) lo[u][q] = fg[4 + q] - m * fg[7 + q];
-        ev[u] = (double)e[(size_t)src * d.nk + k];
+        ev[u] = *reinterpret_cast<const Vec *>(e + (size_t)src * d.nk + k);
 #pragma unroll
-        for (int q = 0; q < D; ++q) gv[u][q] = (double)g[((size_t)src * D + q) * d.nk + k];
+        for (int q = 0; q < D; ++q) gv[u][q] = *reinterpret_cast<const Vec *>(g + ((size_t)src * D + q) * d.nk + k);
     }
-    double acc = 0.0;
 #pragma unroll
     for (int u = 0; u < NF; ++u) {
-        double ef = ev[u] + gv[u][0] * lo[u][0] + gv[u][1] * lo[u][1];
-        if constexpr (D == 3) ef += gv[u][2] * lo[u][2];
-        acc += sn[u] * d.fgeo[(size_t)(f0 + u) * kFG] * ef;
+        const double a = sn[u] * d.fgeo[(size_t)(f0 + u) * kFG];
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            double ef = (double)ev[u].x[i] + (double)gv[u][0].x[i] * lo[u][0] + (double)gv[u][1].x[i] * lo[u][1];
+            if constexpr (D == 3) ef += (double)gv[u][2].x[i] * lo[u][2];
+            acc[i] += a * ef;
+        }
     }
-    return acc;
 }
 
-// R = -(1/V) sum_f v (s.n) S e_f - (e - C4 T_L) / tau + C4 P / C_tot
-template <typename T, int D>
+// R = -(1/V) sum_f v (s.n) S e_f - (e - C4 T_L) / tau + C4 P / C_tot; the V
+// bands of a lane are one direction's
+template <typename T, int D, int V>
 __global__ __launch_bounds__(kBlock) void k_mesh_residual(MeshDev d, const T *__restrict__ e, const T *__restrict__ g,
                                                           const double *__restrict__ din,
                                                           const double *__restrict__ TLdev, T *__restrict__ R,
-                                                          int nkb)
+                                                          int nch)
 {
-    const int i = blockIdx.x / nkb;
-    const int c = d.vorder[i];
-    const int k = (blockIdx.x - i * nkb) * kBlock + threadIdx.x;
-    if (k >= d.nk) return;
+    using Vec = BandVec<T, V>;
+    int c, k;
+    if (!rhs_work(d, nch, V, c, k)) return;
     const int al = k / d.nl, l = k - al * d.nl;
     const double sx = d.s[3 * al], sy = d.s[3 * al + 1], sz = d.s[3 * al + 2];
-    double acc = 0.0;
+    double acc[V] = {};
     const int f0 = d.fptr[c], f1 = d.fptr[c + 1];
     const int nf = f1 - f0;
     int nbv[4] = {-1, -1, -1, -1};
@@ -274,47 +305,60 @@ __global__ __launch_bounds__(kBlock) void k_mesh_residual(MeshDev d, const T *__
     }
     if (inner) {
         if constexpr (D == 3)
-            acc = interior_flux<T, D, 4>(d, e, g, c, k, f0, nbv, sx, sy, sz);
+            interior_flux<T, D, 4, V>(d, e, g, c, k, f0, nbv, sx, sy, sz, acc);
+        else if (nf == 4)
+            interior_flux<T, D, 4, V>(d, e, g, c, k, f0, nbv, sx, sy, sz, acc);
         else
-            acc = nf == 4 ? interior_flux<T, D, 4>(d, e, g, c, k, f0, nbv, sx, sy, sz)
-                          : interior_flux<T, D, 3>(d, e, g, c, k, f0, nbv, sx, sy, sz);
+            interior_flux<T, D, 3, V>(d, e, g, c, k, f0, nbv, sx, sy, sz, acc);
     }
     for (int f = inner ? f1 : f0; f < f1; ++f) {
         const double *fg = d.fgeo + (size_t)f * kFG;
         const double sn = sx * fg[1] + sy * fg[2] + sz * fg[3];
         const int nb = d.fnb[f];
-        double ef;
+        double ef[V];
+        // face values of cell src's bands from ks at the offset l from its centre
+        auto out = [&](int src, int ks, double lx, double ly, double lz) {
+#pragma unroll
+            for (int i = 0; i < V; ++i) ef[i] = face_out<T, D>(d, e, g, src, ks + i, lx, ly, lz);
+        };
         if (nb >= 0) {
             // interior face: the upwind cell per lane, so that the lanes of
             // a wave issue one set of loads whichever side is upwind (a lane
             // with s.n = 0 adds zero)
             const bool own = sn > 0.0;
-            ef = face_out<T, D>(d, e, g, own ? c : nb, k, own ? fg[4] : fg[4] - fg[7], own ? fg[5] : fg[5] - fg[8],
-                                own ? fg[6] : fg[6] - fg[9]);
+            out(own ? c : nb, k, own ? fg[4] : fg[4] - fg[7], own ? fg[5] : fg[5] - fg[8],
+                own ? fg[6] : fg[6] - fg[9]);
         } else if (sn > 0.0) {
-            ef = face_out<T, D>(d, e, g, c, k, fg[4], fg[5], fg[6]);
+            out(c, k, fg[4], fg[5], fg[6]);
         } else if (sn < 0.0) {
             const int tag = d.ftag[f];
             const int kind = d.tag_bc[tag];
             if (kind == BTE_BC_THERMAL) {
-                ef = d.C4[l] * d.tag_dT[tag];
+#pragma unroll
+                for (int i = 0; i < V; ++i) ef[i] = d.C4[l + i] * d.tag_dT[tag];
             } else if (kind == BTE_BC_SPECULAR) {
                 // the wall's normal axis (the face is normal to x, y or z)
                 const int axis = fabs(fg[1]) > 0.5 ? 0 : (fabs(fg[2]) > 0.5 ? 1 : 2);
-                const int km = d.mirror[axis * d.na + al] * d.nl + l;
-                ef = face_out<T, D>(d, e, g, c, km, fg[4], fg[5], fg[6]);
+                out(c, d.mirror[axis * d.na + al] * d.nl + l, fg[4], fg[5], fg[6]);
             } else {
-                ef = din[(size_t)d.frec[f] * d.nl + l];
+#pragma unroll
+                for (int i = 0; i < V; ++i) ef[i] = din[(size_t)d.frec[f] * d.nl + l + i];
             }
         } else {
             continue;
         }
-        acc += sn * fg[0] * ef;
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[i] += sn * fg[0] * ef[i];
     }
-    const double ec = (double)e[(size_t)c * d.nk + k];
-    double r = -d.v[l] * acc - (ec - d.C4[l] * TLdev[c]) * d.itau[l];
-    if (d.P) r += d.C4[l] * d.P[c] / d.Ctot;
-    R[(size_t)c * d.nk + k] = (T)r;
+    const Vec ec = *reinterpret_cast<const Vec *>(e + (size_t)c * d.nk + k);
+    Vec o;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        double r = -d.v[l + i] * acc[i] - ((double)ec.x[i] - d.C4[l + i] * TLdev[c]) * d.itau[l + i];
+        if (d.P) r += d.C4[l + i] * d.P[c] / d.Ctot;
+        o.x[i] = (T)r;
+    }
+    *reinterpret_cast<Vec *>(R + (size_t)c * d.nk + k) = o;
 }
 
 // One level of the sweep: thread = (item, band).  b holds R on entry and the
@@ -370,8 +414,6 @@ __global__ __launch_bounds__(kBlock) void k_mesh_sweep_level(MeshDev d, T *__res
 // V consecutive bands per thread.  Blocks of one octant's directions go to one
 // XCD: their rows share cache lines.
 // EA: rows of the caller's e are aligned for them (the workspace's are).
-template <typename T, int V> struct alignas(sizeof(T) * V) BandVec { T x[V]; };
-
 template <typename T, int V, bool EA> __device__ inline BandVec<T, V> band_load(const T *p)
 {
     if constexpr (EA) return *reinterpret_cast<const BandVec<T, V> *>(p);
@@ -1312,32 +1354,39 @@ bte_status mesh_build_tet(bte_mesh_problem *p, const bte_tet_mesh *m, const bte_
     return mesh_finish(p, mat, m->gradient_stencil, xc, cptr, cvtx, m->n_vertices);
 }
 
+template <typename T, int D, int V>
+void mesh_rhs(bte_mesh_problem *p, const T *e, const double *TLdev, T *R, hipStream_t s)
+{
+    const MeshDev &d = p->dev;
+    const int nch = (p->nk + 64 * V - 1) / (64 * V);
+    const dim3 grid((unsigned)((size_t)nch * ((p->nc + kRhsCells - 1) / kRhsCells)));
+    if (sizeof(T) == 4 && p->nelem() * 4 < (size_t(1) << 31))
+        hipLaunchKernelGGL((k_mesh_grad<T, D, sizeof(T) == 4, V>), grid, dim3(kBlock), 0, s, d, e, (T *)p->g, nch);
+    else
+        hipLaunchKernelGGL((k_mesh_grad<T, D, false, V>), grid, dim3(kBlock), 0, s, d, e, (T *)p->g, nch);
+    if (p->nrec > 0)
+        hipLaunchKernelGGL((k_mesh_walls<T, D>), dim3(p->nrec), dim3(kBlock), 0, s, d, e, (const T *)p->g, p->din);
+    hipLaunchKernelGGL((k_mesh_residual<T, D, V>), grid, dim3(kBlock), 0, s, d, e, (const T *)p->g, p->din, TLdev, R,
+                       nch);
+}
+
+// Bands per lane: 16 bytes, or as many as divide the band count (a lane's
+// bands are one direction's) and the alignment of the caller's e and R allow
+// (the workspace's rows are aligned for them).
 template <typename T>
 void mesh_iteration_rhs(bte_mesh_problem *p, const T *e, const double *TLdev, T *R, hipStream_t s)
 {
-    const MeshDev &d = p->dev;
-    const int nkb = (p->nk + kBlock - 1) / kBlock;
-    const dim3 grid((unsigned)((size_t)nkb * p->nc));
-    const bool buf = sizeof(T) == 4 && p->nelem() * 4 < (size_t(1) << 31);
-    if (p->dim == 3) {
-        if (buf)
-            hipLaunchKernelGGL((k_mesh_grad<T, 3, true>), grid, dim3(kBlock), 0, s, d, e, (T *)p->g, nkb);
-        else
-            hipLaunchKernelGGL((k_mesh_grad<T, 3, false>), grid, dim3(kBlock), 0, s, d, e, (T *)p->g, nkb);
-        if (p->nrec > 0)
-            hipLaunchKernelGGL((k_mesh_walls<T, 3>), dim3(p->nrec), dim3(kBlock), 0, s, d, e, (const T *)p->g, p->din);
-        hipLaunchKernelGGL((k_mesh_residual<T, 3>), grid, dim3(kBlock), 0, s, d, e, (const T *)p->g, p->din, TLdev,
-                           R, nkb);
-    } else {
-        if (buf)
-            hipLaunchKernelGGL((k_mesh_grad<T, 2, true>), grid, dim3(kBlock), 0, s, d, e, (T *)p->g, nkb);
-        else
-            hipLaunchKernelGGL((k_mesh_grad<T, 2, false>), grid, dim3(kBlock), 0, s, d, e, (T *)p->g, nkb);
-        if (p->nrec > 0)
-            hipLaunchKernelGGL((k_mesh_walls<T, 2>), dim3(p->nrec), dim3(kBlock), 0, s, d, e, (const T *)p->g, p->din);
-        hipLaunchKernelGGL((k_mesh_residual<T, 2>), grid, dim3(kBlock), 0, s, d, e, (const T *)p->g, p->din, TLdev,
-                           R, nkb);
-    }
+    int V = 16 / (int)sizeof(T);
+    while (V > 1 && (p->nl % V != 0 || ((uintptr_t)e | (uintptr_t)R) % (V * sizeof(T)) != 0)) V /= 2;
+    auto run = [&](auto dim) {
+        constexpr int D = decltype(dim)::value;
+        if constexpr (sizeof(T) == 4)
+            if (V == 4) return mesh_rhs<T, D, 4>(p, e, TLdev, R, s);
+        if (V == 2) return mesh_rhs<T, D, 2>(p, e, TLdev, R, s);
+        mesh_rhs<T, D, 1>(p, e, TLdev, R, s);
+    };
+    if (p->dim == 3) run(std::integral_constant<int, 3>{});
+    else run(std::integral_constant<int, 2>{});
 }
 
 template <typename T, int V> const void *dir_kernel(bool ea)
