@@ -59,7 +59,7 @@ hipError_t launch_sweep2d(const Dev &, const T *, T *, const double *, const dou
 hipError_t launch_queue_reset(unsigned *, int, hipStream_t);
 template <typename T>
 hipError_t launch_transient3d(const Dev &, const T *, T *, const double *, const double *, const ColItem *, int, int,
-                              int, double, double, double *, hipStream_t);
+                              int, int, double, double, double *, hipStream_t);
 template <typename T>
 hipError_t launch_adj_step(const Dev &, const T *, T *, const T *, const double *, const double *, const double *,
                            const TileItem *, int, int3, int, int, int, double, double *, hipStream_t);
@@ -176,6 +176,7 @@ namespace {
 // Width (in columns) of the strips in which the three-dimensional column
 // walks are ordered.
 constexpr int kColStrip = 16;
+constexpr size_t kQuadMin = 4096;   // wavefronts of 2 x 2 columns
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -215,6 +216,7 @@ struct bte_problem {
     std::vector<int> diag_off;
     std::vector<TileItem> titems;   // transient: (geometry, octant, tile)
     std::vector<ColItem> citems;    // three-dimensional transient: (geometry, octant, chunk, column)
+    std::vector<ColItem> qitems;    // the same by 2 x 2 columns (forward step; empty: column by column)
     int tile_cap = 0;               // star slots of a full tile
     int floating_any = 0, thermal_any = 0;
     // workspace
@@ -264,7 +266,7 @@ struct bte_problem {
     Sweep2Item *d_items2 = nullptr;
     unsigned *d_queue = nullptr;   // one-launch 2D sweep: ticket, abort word, item flags
     TileItem *d_titems = nullptr;
-    ColItem *d_citems = nullptr;
+    ColItem *d_citems = nullptr, *d_qitems = nullptr;
     int *d_wrec = nullptr;
     double *d_wden = nullptr;
     int npart_max = 0;
@@ -755,6 +757,31 @@ void build_schedule(bte_problem *p)
                             for (int x = x0; x < std::min(x0 + kColStrip, fm.n[0]); ++x)
                                 p->citems.push_back({f, o, ch, x + fm.n[0] * y});
         }
+    // 2 x 2 columns for the forward step, where every geometry has them, a
+    // plane's rows lie within 31-bit byte offsets and they still fill the
+    // chip's 4096 resident wavefronts once.  us a step, one column / 2 x 2, MC
+    // limiter, FP32 unless noted, by wavefronts of 2 x 2: 16^3 x 320 (512) 27 /
+    // 51, 20 x 20 x 200 x 1280 (2400) 561 / 626, 24^3 x 1280 (3456) 98 / 95, 32^3
+    // x 5120 (20 480) 605 / 493, FP64 32^3 x 2560 (10 240) 579 / 550, 64^3 x 5120
+    // (81 920) 4602 / 3538
+    p->qitems.clear();
+    bool quads = p->dim == 3;
+    size_t nq = 0;
+    for (const Film &fm : p->films) {
+        quads = quads && fm.n[0] > 1 && fm.n[1] > 1 &&
+                (size_t)fm.n[0] * fm.n[1] * p->nk * p->esize() < (size_t(1) << 31);
+        nq += (size_t)((fm.n[0] + 1) / 2) * ((fm.n[1] + 1) / 2) * p->noct * p->nchunk_oct;
+    }
+    if (quads && nq >= kQuadMin)
+        for (int f = 0; f < p->nfilm; ++f) {
+            const Film &fm = p->films[f];
+            for (int o = 0; o < p->noct; ++o)
+                for (int ch = 0; ch < p->nchunk_oct; ++ch)
+                    for (int x0 = 0; x0 < fm.n[0]; x0 += kColStrip)
+                        for (int y = 0; y < fm.n[1]; y += 2)
+                            for (int x = x0; x < std::min(x0 + kColStrip, fm.n[0]); x += 2)
+                                p->qitems.push_back({f, o, ch, std::min(x, fm.n[0] - 2) + fm.n[0] * std::min(y, fm.n[1] - 2)});
+        }
     p->tile_cap = tile_cap_of(p, lds_tdim(p));
     p->tile_cap_tr = tile_cap_of(p, p->tdim_tr);
     p->items.clear();
@@ -1063,6 +1090,7 @@ void plan_workspace(bte_problem *p)
     add("queue", 4 * (p->dim == 2 ? p->items_cap + 2 : 0));
     add("titems", sizeof(TileItem) * p->titems_cap);
     add("citems", sizeof(ColItem) * p->citems.size());
+    add("qitems", sizeof(ColItem) * p->qitems.size());
     for (const char *n : {"gamma", "P", "S", "TL", "TLkin", "T0", "T1", "q0", "q1", "r", "delta", "dpend", "cg_x",
                           "cg_r", "cg_z", "cg_p", "cg_Ap", "cg_w0", "cg_w1", "cg_s1"})
         add(n, 8 * nc);
@@ -1341,6 +1369,7 @@ bte_status bte_bind(bte_problem *p, void *ws, size_t bytes)
     if (!p->items2.empty()) HIPCHK(p, up("items2", p->items2.data(), sizeof(Sweep2Item) * p->items2.size()));
     HIPCHK(p, up("titems", p->titems.data(), sizeof(TileItem) * p->titems.size()));
     if (!p->citems.empty()) HIPCHK(p, up("citems", p->citems.data(), sizeof(ColItem) * p->citems.size()));
+    if (!p->qitems.empty()) HIPCHK(p, up("qitems", p->qitems.data(), sizeof(ColItem) * p->qitems.size()));
     if (p->dim < 3 && tile_smem_size(p->tile_cap, (int)p->esize(), 1) > 160 * 1024)   // 3D sweeps walk columns
         FAIL(p, BTE_ERR_UNSUPPORTED, "tile LDS");
     HIPCHK(p, tile_kernels_init(160 * 1024));
@@ -1424,6 +1453,7 @@ bte_status bte_bind(bte_problem *p, void *ws, size_t bytes)
     p->d_queue = wsptr<unsigned>(p, "queue");
     p->d_titems = wsptr<TileItem>(p, "titems");
     p->d_citems = wsptr<ColItem>(p, "citems");
+    p->d_qitems = wsptr<ColItem>(p, "qitems");
     p->d_wrec = wsptr<int>(p, "wrec");
     p->d_wden = wsptr<double>(p, "wden");
     for (auto &q : p->direct) q.built = false;
@@ -1911,8 +1941,10 @@ hipError_t one_step(bte_problem *p, const T *ein, T *eout, double src, hipEvent_
         r = launch_transient1d<T>(d, ein, eout, p->TL, p->TL, p->din, p->d_titems, (int)p->titems.size() / p->noct,
                                   p->tdim_tr.x, src, p->ctl.dt, s);
     } else if (p->dim == 3) {
-        r = launch_transient3d<T>(d, ein, eout, p->TL, p->din, p->d_citems, (int)p->citems.size(), p->na_oct,
-                                  p->nchunk_oct, src, p->ctl.dt, p->part, s);
+        const bool quad = !p->qitems.empty();
+        r = launch_transient3d<T>(d, ein, eout, p->TL, p->din, quad ? p->d_qitems : p->d_citems,
+                                  (int)(quad ? p->qitems : p->citems).size(), quad, p->na_oct, p->nchunk_oct, src,
+                                  p->ctl.dt, p->part, s);
         np = p->noct * p->nchunk_oct;
     } else {
         r = launch_transient_tile<T>(d, ein, eout, p->TL, p->din, p->d_titems, (int)p->titems.size(), p->tdim_tr,

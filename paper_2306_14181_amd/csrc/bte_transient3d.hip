@@ -305,6 +305,383 @@ __global__ __launch_bounds__(256) void k_transient3d(Dev d, const T *__restrict_
     }
 }
 
+// Four columns (2 x 2 in the flow frame) per wavefront, for problems that
+// still fill the chip with them: a column's stencil shares its neighbours with
+// the three others, so a step reads 16 rows for four cells instead of 28, an
+// axis' limited slopes 3 for two cells instead of 4, and the four cells'
+// independent arithmetic hides the latency of one another.  Rows are read
+// through a buffer descriptor at the plane, the row as a scalar offset, the
+// lane as a vector offset: no address arithmetic.  An axis along which all four
+// cells have the interior stencil is straight-line code; a cell's scalars are
+// one LDS record.  The last pair of an odd width or depth starts one column early.
+// Bound by issue and by the wall steps' own loads: 64^3 cells x 5120 lanes FP32,
+// MC limiter, 4.60 -> 3.54 ms a step (8 bytes a lane moved: 3.0 TB/s), 32^3 605 ->
+// 493 us, FP64 48^3 x 1280 unlimited 1107 -> 870 us.
+template <typename T> struct alignas(16) QuadRec {
+    double gam;
+    T tl, qs;
+};
+
+template <typename T, int LIM, bool JMP>
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_transient3d_quad(
+    Dev d, const T *__restrict__ ein, T *__restrict__ eout, const double *__restrict__ TLdev,
+    const double *__restrict__ din, const ColItem *__restrict__ items, int nitems, int na_oct, int nchunk_oct, double src,
+    double dt, double *__restrict__ part)
+{
+    // T_L partials of two steps of a wavefront (slot 4 (step & 1) + cell), and
+    // the records of 64 steps
+    __shared__ double red[4][8][64];
+    __shared__ QuadRec<T> recs[4][64][4];
+    const int nb = gridDim.x, bb = blockIdx.x;
+    const int lb = (bb & 7) * (nb >> 3) + (bb >> 3);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wi = lb * 4 + wv;
+    if (wi >= nitems) return;
+    const int lane = threadIdx.x & 63;
+    const ColItem it = items[wi];
+    const Film &fm = d.film[it.film];
+    const int sg0 = octant_sign(d, it.oct, na_oct, 0), sg1 = octant_sign(d, it.oct, na_oct, 1),
+              sg2 = octant_sign(d, it.oct, na_oct, 2);
+    const int nl = d.nl, nk = d.nk, nc = d.nc;
+    const int kbeg = it.oct * na_oct * nl, kend = kbeg + na_oct * nl;
+    const int k = kbeg + it.chunk * 64 + lane;
+    const bool active = k < kend;
+    const int kk = active ? k : kbeg;
+    const LaneT<T> L = lane_make<T>(d, fm, kk);
+    const T C4 = L.C4;
+    const int n0 = fm.n[0], n1 = fm.n[1], n2 = fm.n[2], plane = n0 * n1;
+    const int xl = it.col % n0, yl = it.col / n0;                            // lowest corner
+    const int xa = sg0 > 0 ? xl : xl + 1, ya = sg1 > 0 ? yl : yl + 1;        // first corner of the flow
+    const double *zd = static_cast<const double *>(d.zrow);
+    const int koff = kk * (int)sizeof(T);
+
+    // flow positions -2, -1, 2 of an axis (halo index 0, 1, 2): geometric
+    // position or -1, and the jump of the values there
+    int hx[3], hy[3];
+    T kx[3], ky[3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        const int off = m < 2 ? m - 2 : 2;
+        int j;
+        hx[m] = wrap_pos(xa + sg0 * off, n0, fm.periodic[0], j);
+        kx[m] = JMP ? C4 * (T)(j * fm.pdT[0]) : (T)0;
+        hy[m] = wrap_pos(ya + sg1 * off, n1, fm.periodic[1], j);
+        ky[m] = JMP ? C4 * (T)(j * fm.pdT[1]) : (T)0;
+    }
+    // cells at z = 0: the four columns (q = i + 2 j), the x halo of row j, the
+    // y halo of column i (-1: none), and their rows' byte offsets from the
+    // plane's first row (a missing one: the column's own; its value is not used)
+    int cq[4], cx[2][3], cy[2][3], oq[4], ox[2][3], oy[2][3];
+    const int rowb = nk * (int)sizeof(T);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) cq[i + 2 * j] = xa + sg0 * i + n0 * (ya + sg1 * j);
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            cx[r][m] = hx[m] >= 0 ? hx[m] + n0 * (ya + sg1 * r) : -1;
+            cy[r][m] = hy[m] >= 0 ? xa + sg0 * r + n0 * hy[m] : -1;
+            ox[r][m] = (cx[r][m] >= 0 ? cx[r][m] : cq[2 * r]) * rowb;
+            oy[r][m] = (cy[r][m] >= 0 ? cy[r][m] : cq[r]) * rowb;
+        }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) oq[q] = cq[q] * rowb;
+
+    // plane of flow index f (wrapped), -1 outside a non-periodic column
+    auto zplane = [&](int f, int &jz) { return wrap_pos(sg2 > 0 ? f : n2 - 1 - f, n2, fm.periodic[2], jz); };
+    auto base = [&](int z) { return ein + (size_t)(fm.cell0 + plane * z) * nk; };
+    auto rsrc = [&](const T *p) { return __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0, -1, 0x00020000); };
+    auto ld = [&](__amdgpu_buffer_rsrc_t r, int off) -> T {
+        if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, koff, off, 0));
+        else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, koff, off, 0));
+    };
+    auto ldv = [&](__amdgpu_buffer_rsrc_t r, int off) -> T {
+        if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+        else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    };
+    // the halo rows' with the lane's: twelve scalars fewer (they would spill)
+    int vx[2][3], vy[2][3];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            vx[a][m] = ox[a][m] + koff;
+            vy[a][m] = oy[a][m] + koff;
+        }
+    auto jump_z = [&](int jz) -> T { return JMP ? C4 * (T)(jz * fm.pdT[2]) : (T)0; };
+
+    // z window (flow order) with its jumps, limited z slope of the upwind cells
+    T ez2[4], ez1[4], ec[4], ezd[4], lzu[4];
+    auto window = [&](int f, T (&v)[4]) {
+        int jz;
+        const int z = zplane(f, jz);
+        const auto r = rsrc(base(z >= 0 ? z : 0));
+        const T jv = jump_z(jz);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = JMP ? ld(r, oq[q]) + jv : ld(r, oq[q]);
+    };
+    window(-2, ez2);
+    window(-1, ez1);
+    window(0, ec);
+    window(1, ezd);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) lzu[q] = (LIM == LIM_NONE) ? (T)0 : lim_diff<T, LIM>(ez1[q] - ez2[q], ec[q] - ez1[q]);
+
+    const T tdt = (T)dt, tsrc = (T)src;
+    const T itau = L.itau;
+    const T cp0 = L.cpl[0], cp1 = L.cpl[1], cp2 = L.cpl[2];
+    double *__restrict__ pout = part + (size_t)(it.oct * nchunk_oct + it.chunk) * nc;
+    // columns that the wavefront writes: all, but the lower one of a pair that
+    // starts at an odd place (the last of an odd width or depth) is its neighbour's
+    bool own[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int x = xa + sg0 * (q & 1), y = ya + sg1 * (q >> 1);
+        own[q] = !((xl & 1) && x == xl) && !((yl & 1) && y == yl);
+    }
+    // the column of this lane's slot in the partials' reduction
+    const int slot = lane >> 3;
+    const bool slot_own = (slot & 3) == 0 ? own[0] : (slot & 3) == 1 ? own[1] : (slot & 3) == 2 ? own[2] : own[3];
+    const int pcell = xa + sg0 * (slot & 1) + n0 * (ya + sg1 * ((slot >> 1) & 1));
+
+    struct Pre {
+        T nz[4], x[2][3], y[2][3];
+    };
+    const long long zstep = (long long)(sg2 > 0 ? plane : -plane) * nk;
+    const int z0 = sg2 > 0 ? 0 : n2 - 1;
+    const T *pxy = base(z0);                               // plane of the step being prefetched
+    const T *pz = base(z0) + zstep;                        // plane of flow index f + 3, before the advance
+    T *po = eout + (size_t)(fm.cell0 + plane * z0) * nk;   // plane of the step
+    auto prefetch = [&](int f, Pre &p) {
+        if (f + 1 < n2 && f >= 0) pxy += zstep;
+        const auto r = rsrc(pxy);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                p.x[a][m] = ldv(r, vx[a][m]);
+                p.y[a][m] = ldv(r, vy[a][m]);
+            }
+        pz += zstep;
+        const T *pn = pz;
+        T jv = (T)0;
+        if (f + 3 >= n2) {   // past the column's end: periodic image with its jump, or a value not used
+            int jz;
+            const int z = zplane(f + 3, jz);
+            pn = base(z >= 0 ? z : 0);
+            jv = jump_z(jz);
+        }
+        const auto rn = rsrc(pn);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) p.nz[q] = JMP ? ld(rn, oq[q]) + jv : ld(rn, oq[q]);
+    };
+    // records of 64 steps, one per lane.  r_mode: bits 0 to 2, all four cells
+    // have the interior stencil along x, y, z; bit 3, all are solid
+    int r_mode = 0;
+    auto records = [&](int f0) {
+        const int fl = min(f0 + lane, n2 - 1);
+        const int o = fm.cell0 + plane * (sg2 > 0 ? fl : n2 - 1 - fl);
+        int jz;
+        const int zu = zplane(fl - 1, jz);
+        uint32_t code[4], ux[2], uy[2], uz[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            code[q] = d.code[o + cq[q]];
+            uz[q] = d.code[(zu >= 0 ? fm.cell0 + plane * zu : o) + cq[q]];
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            ux[r] = d.code[o + (cx[r][1] >= 0 ? cx[r][1] : cq[0])];
+            uy[r] = d.code[o + (cy[r][1] >= 0 ? cy[r][1] : cq[0])];
+        }
+        int mode = 15;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = q & 1, j = q >> 1, c = o + cq[q];
+            const uint32_t ab0 = axis_bits(code[q], 0), ab1 = axis_bits(code[q], 1), ab2 = axis_bits(code[q], 2);
+            const uint32_t cu0 = i ? code[q - 1] : ux[j], cu1 = j ? code[q - 2] : uy[i];
+            if (!(side_is_cell(ab0, -sg0) && side_is_cell(ab0, sg0) && side_is_cell(axis_bits(cu0, 0), -sg0))) mode &= ~1;
+            if (!(side_is_cell(ab1, -sg1) && side_is_cell(ab1, sg1) && side_is_cell(axis_bits(cu1, 1), -sg1))) mode &= ~2;
+            if (!(side_is_cell(ab2, -sg2) && side_is_cell(ab2, sg2) && side_is_cell(axis_bits(uz[q], 2), -sg2))) mode &= ~4;
+            if (!(code[q] & kSolidBit)) mode = 0;
+            recs[wv][lane][q] = {d.gamma[c], (T)TLdev[c], (T)(*(d.P ? d.P + c : zd) / fm.Ctot)};
+        }
+        r_mode = mode;
+    };
+    // mirror lanes of the three axes (specular walls)
+    int km[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) km[a] = (d.mirror[a * d.na + L.al] * nl + L.l) * (int)sizeof(T);
+
+    // face-value differences of two cells of an axis: the slope of the first is
+    // also the upwind slope of the second
+    auto pair = [&](const T (&h)[3], T a, T b, T &da, T &db) {
+        if constexpr (LIM == LIM_NONE) {
+            da = delta_fast<T, LIM>(h[0], h[1], a, b);
+            db = delta_fast<T, LIM>(h[1], a, b, h[2]);
+        } else {
+            const T d0 = h[1] - h[0], d1 = a - h[1], d2 = b - a, d3 = h[2] - b;
+            const T s0 = lim_diff<T, LIM>(d0, d1), s1 = lim_diff<T, LIM>(d1, d2), s2 = lim_diff<T, LIM>(d2, d3);
+            da = d1 + (T)0.5 * (s1 - s0);
+            db = d2 + (T)0.5 * (s2 - s1);
+        }
+    };
+    // one cell's on the general path: code of the cell and of its upwind
+    // neighbour, byte offsets of its row and its downwind neighbour's from the
+    // descriptors rc and rd, jump of the latter's values
+    auto general = [&](int a, int sg, uint32_t code, uint32_t cu, int c, __amdgpu_buffer_rsrc_t rc, int oc,
+                       __amdgpu_buffer_rsrc_t rd, int od, T kd, T e2, T e1, T e0, T ed) -> T {
+        const uint32_t ab = axis_bits(code, a);
+        const bool hu = side_is_cell(ab, -sg), hd = side_is_cell(ab, sg);
+        const bool hu2 = hu && side_is_cell(axis_bits(cu, a), -sg);
+        if (hu2 && hd) return delta_fast<T, LIM>(e2, e1, e0, ed);
+        const T hh = L.hh[a], ih = L.ih[a];
+        const T fout = e0 + hh * slope_flow<T>(LIM, hu, hd, e1, e0, ed, ih);
+        T fin;
+        if (hu) {
+            fin = e1 + hh * slope_flow<T>(LIM, hu2, true, e2, e1, e0, ih);
+        } else {
+            const int kind = side_wall(ab, -sg);
+            if (kind == 0) {
+                fin = C4 * (T)(side_outer(code, a, -sg) ? fm.wallT[face_of(a, -sg)] : d.poreT);
+            } else if (kind == 1) {
+                // the mirror direction's outgoing face value
+                auto ldm = [&](__amdgpu_buffer_rsrc_t r, int off) -> T {
+                    if constexpr (sizeof(T) == 4)
+                        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, km[a], off, 0));
+                    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, km[a], off, 0));
+                };
+                const T em = ldm(rc, oc);
+                T gm = (T)0;
+                if (LIM == LIM_NONE && hd) gm = (em - (ldm(rd, od) + kd)) * ih;
+                fin = em + hh * gm;
+            } else {
+                fin = (T)din[(size_t)diffuse_index(d, c, code, face_of(a, -sg)) * d.nl + L.l];
+            }
+        }
+        return fout - fin;
+    };
+
+    auto step = [&](int f, const Pre &in, Pre &out) {
+        const int zo = fm.cell0 + plane * (sg2 > 0 ? f : n2 - 1 - f);
+        prefetch(f, out);
+        const int mode = __builtin_amdgcn_readlane(r_mode, f & 63);
+        T X[2][3], Y[2][3], lz[4], dx[4], dy[4], dz[4];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                X[a][m] = JMP ? in.x[a][m] + kx[m] : in.x[a][m];
+                Y[a][m] = JMP ? in.y[a][m] + ky[m] : in.y[a][m];
+            }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) lz[q] = (LIM == LIM_NONE) ? (T)0 : lim_diff<T, LIM>(ec[q] - ez1[q], ezd[q] - ec[q]);
+        uint32_t code[4];
+        __amdgpu_buffer_rsrc_t here;
+        if (mode != 15) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) code[q] = d.code[zo + cq[q]];
+            here = rsrc(ein + (size_t)zo * nk);
+        }
+        if (mode & 1) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) pair(X[r], ec[2 * r], ec[2 * r + 1], dx[2 * r], dx[2 * r + 1]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = q & 1, j = q >> 1;
+                const uint32_t cu = i ? code[q - 1] : (cx[j][1] >= 0 ? d.code[zo + cx[j][1]] : 0u);
+                dx[q] = general(0, sg0, code[q], cu, zo + cq[q], here, oq[q], here, i ? (cx[j][2] >= 0 ? cx[j][2] : cq[2 * j]) * rowb : oq[2 * j + 1],
+                                i ? kx[2] : (T)0, i ? X[j][1] : X[j][0], i ? ec[2 * j] : X[j][1], ec[q],
+                                i ? X[j][2] : ec[2 * j + 1]);
+            }
+        }
+        if (mode & 2) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) pair(Y[r], ec[r], ec[r + 2], dy[r], dy[r + 2]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = q & 1, j = q >> 1;
+                const uint32_t cu = j ? code[q - 2] : (cy[i][1] >= 0 ? d.code[zo + cy[i][1]] : 0u);
+                dy[q] = general(1, sg1, code[q], cu, zo + cq[q], here, oq[q], here, j ? (cy[i][2] >= 0 ? cy[i][2] : cq[i]) * rowb : oq[i + 2],
+                                j ? ky[2] : (T)0, j ? Y[i][1] : Y[i][0], j ? ec[i] : Y[i][1], ec[q],
+                                j ? Y[i][2] : ec[i + 2]);
+            }
+        }
+        if (mode & 4) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                dz[q] = LIM == LIM_NONE ? delta_fast<T, LIM>(ez2[q], ez1[q], ec[q], ezd[q])
+                                        : (ec[q] - ez1[q]) + (T)0.5 * (lz[q] - lzu[q]);
+        } else {
+            int jz, jd;
+            const int zu = zplane(f - 1, jz), zn = zplane(f + 1, jd);
+            const auto next = rsrc(base(zn >= 0 ? zn : 0));
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                dz[q] = general(2, sg2, code[q], zu >= 0 ? d.code[fm.cell0 + plane * zu + cq[q]] : 0u, zo + cq[q], here,
+                                oq[q], next, oq[q], jump_z(jd), ez2[q], ez1[q], ec[q], ezd[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const QuadRec<T> rc = recs[wv][f & 63][q];
+            const T itc = itau + (T)rc.gam;
+            const T D = cp0 * dx[q] + cp1 * dy[q] + cp2 * dz[q];
+            T en = ec[q] + tdt * (-D - (ec[q] - C4 * rc.tl) * itc + C4 * tsrc * rc.qs);
+            double acc = active ? (L.witau + L.w * rc.gam) * (double)en : 0.0;
+            if (!(mode & 8) && !(code[q] & kSolidBit)) {   // a pore keeps its value
+                en = ec[q];
+                acc = 0.0;
+            }
+            // streamed out (nontemporal): the step never reads its output back
+            if (active && own[q])
+                __builtin_nontemporal_store(en, reinterpret_cast<T *>(reinterpret_cast<char *>(po) + (unsigned)oq[q] + koff));
+            red[wv][4 * (f & 1) + q][lane] = acc;
+        }
+        po += zstep;
+        // partials of two steps' eight cells, reduced transposed (lane = 8 slot + part)
+        if ((f & 1) || f == n2 - 1) {
+            const int pp = lane & 7, fj = (f & ~1) + (slot >> 2);
+            double v = 0.0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v += red[wv][slot][8 * pp + i];
+            v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
+            v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
+            v += dpp_f64<0x141>(v);   // row_half_mirror
+            // (pores get a zero partial: the T_L update ignores them)
+            if (pp == 0 && fj <= f && slot_own)
+                __builtin_nontemporal_store(v, &pout[fm.cell0 + pcell + plane * (sg2 > 0 ? fj : n2 - 1 - fj)]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            ez2[q] = ez1[q];
+            ez1[q] = ec[q];
+            ec[q] = ezd[q];
+            ezd[q] = in.nz[q];
+            lzu[q] = lz[q];
+        }
+    };
+
+    Pre A, B;
+    prefetch(-1, A);
+    for (int f0 = 0; f0 < n2; f0 += 64) {
+        records(f0);
+        const int f1 = min(f0 + 64, n2);
+        int f = f0;
+        for (; f + 1 < f1; f += 2) {
+            step(f, A, B);
+            step(f + 1, B, A);
+        }
+        if (f < f1) {
+            step(f, A, B);
+            A = B;
+        }
+    }
+}
+
 // Transposed explicit step of the transient adjoint (reverse mode of
 // e^{k+1} = e^k + dt R(e^k)) on three-dimensional geometries, column by
 // column like k_transient3d:  lam^k = lam^{k+1} + dt J^T lam^{k+1} with the
@@ -619,11 +996,17 @@ template hipError_t launch_adj_step3d<double>(const Dev &, const double *, doubl
 
 template <typename T, int LIM>
 void transient3d_launch(const Dev &d, const T *ein, T *eout, const double *TLdev, const double *din,
-                        const ColItem *items, int nitems, int na_oct, int nchunk_oct, double src, double dt,
+                        const ColItem *items, int nitems, int quad, int na_oct, int nchunk_oct, double src, double dt,
                         double *part, hipStream_t s)
 {
     const int blocks = ((nitems + 3) / 4 + 7) / 8 * 8;
-    if (d.jumps)
+    if (quad && d.jumps)
+        hipLaunchKernelGGL((k_transient3d_quad<T, LIM, true>), dim3(blocks), dim3(256), 0, s, d, ein, eout, TLdev, din,
+                           items, nitems, na_oct, nchunk_oct, src, dt, part);
+    else if (quad)
+        hipLaunchKernelGGL((k_transient3d_quad<T, LIM, false>), dim3(blocks), dim3(256), 0, s, d, ein, eout, TLdev, din,
+                           items, nitems, na_oct, nchunk_oct, src, dt, part);
+    else if (d.jumps)
         hipLaunchKernelGGL((k_transient3d<T, LIM, true>), dim3(blocks), dim3(256), 0, s, d, ein, eout, TLdev, din,
                            items, nitems, na_oct, nchunk_oct, src, dt, part);
     else
@@ -631,26 +1014,27 @@ void transient3d_launch(const Dev &d, const T *ein, T *eout, const double *TLdev
                            items, nitems, na_oct, nchunk_oct, src, dt, part);
 }
 
+// items: columns, or with quad the lowest corners of 2 x 2 columns
 template <typename T>
 hipError_t launch_transient3d(const Dev &d, const T *ein, T *eout, const double *TLdev, const double *din,
-                              const ColItem *items, int nitems, int na_oct, int nchunk_oct, double src, double dt,
-                              double *part, hipStream_t s)
+                              const ColItem *items, int nitems, int quad, int na_oct, int nchunk_oct, double src,
+                              double dt, double *part, hipStream_t s)
 {
     if (nitems <= 0) return hipSuccess;
     if (d.limiter == LIM_NONE)
-        transient3d_launch<T, LIM_NONE>(d, ein, eout, TLdev, din, items, nitems, na_oct, nchunk_oct, src, dt, part, s);
+        transient3d_launch<T, LIM_NONE>(d, ein, eout, TLdev, din, items, nitems, quad, na_oct, nchunk_oct, src, dt, part, s);
     else if (d.limiter == LIM_MC)
-        transient3d_launch<T, LIM_MC>(d, ein, eout, TLdev, din, items, nitems, na_oct, nchunk_oct, src, dt, part, s);
+        transient3d_launch<T, LIM_MC>(d, ein, eout, TLdev, din, items, nitems, quad, na_oct, nchunk_oct, src, dt, part, s);
     else
-        transient3d_launch<T, LIM_MINMOD>(d, ein, eout, TLdev, din, items, nitems, na_oct, nchunk_oct, src, dt, part,
+        transient3d_launch<T, LIM_MINMOD>(d, ein, eout, TLdev, din, items, nitems, quad, na_oct, nchunk_oct, src, dt, part,
                                           s);
     return hipGetLastError();
 }
 
 template hipError_t launch_transient3d<float>(const Dev &, const float *, float *, const double *, const double *,
-                                              const ColItem *, int, int, int, double, double, double *, hipStream_t);
+                                              const ColItem *, int, int, int, int, double, double, double *, hipStream_t);
 template hipError_t launch_transient3d<double>(const Dev &, const double *, double *, const double *, const double *,
-                                               const ColItem *, int, int, int, double, double, double *,
+                                               const ColItem *, int, int, int, int, double, double, double *,
                                                hipStream_t);
 
 }  // namespace bte
