@@ -12,7 +12,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -87,10 +89,10 @@ void launch_steady_post(const Dev &, const double *, int, const double *, double
 int film_segments(int max_cells);
 void launch_film_eps(const Dev &, const double *, const double *, const double *, const double *, double *, double *,
                      int, hipStream_t);
-void launch_film_mean(const Dev &, const double *, double *, double *, int, hipStream_t);
+void launch_film_mean(const Dev &, const double *, double *, double *, int, double *, hipStream_t);
 void launch_sub_film_mean(const Dev &, double *, const double *, hipStream_t);
 void launch_tl_update(int, const double *, const double *, double *, double *, const int *, const int *,
-                      const unsigned *, hipStream_t);
+                      const Report &, hipStream_t);
 void launch_cg_coef(const Dev &, const CgArgs &, double *, double *, hipStream_t);
 void launch_diff_rhs(const Dev &, const CgArgs &, double *, hipStream_t);
 void launch_cg_begin(const Dev &, const CgArgs &, const double *, hipStream_t);
@@ -182,8 +184,13 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 }  // namespace
 
+struct HostFree {
+    void operator()(double *q) const { (void)hipHostFree(q); }
+};
+
 struct bte_problem {
     std::string err;
+    std::unique_ptr<double, HostFree> report;   // pinned: 5 measures per geometry and two abort words (Report)
     int dim = 0, nfilm = 0, nc = 0, na = 0, nl = 0, nk = 0, noct = 0, na_oct = 0;
     bte_control ctl{};
     double Tref = 0, Ctot = 0, vmax = 0, itau_max = 0;
@@ -1346,10 +1353,38 @@ bte_status bte_bind(bte_problem *p, void *ws, size_t bytes)
     if (!ws || bytes < p->ws_bytes) FAIL(p, BTE_ERR_ARG, "workspace too small (%zu < %zu)", bytes, p->ws_bytes);
     if ((uintptr_t)ws & 255) FAIL(p, BTE_ERR_ARG, "workspace must be 256-byte aligned");
     p->ws = (char *)ws;
+    // tables: neighbours in the workspace go up in one copy (a small problem has
+    // twenty of them, a copy takes 8 us whatever its size); what lies between
+    // them is padding or room that is written before it is read
+    constexpr size_t kStage = 256 * 1024, kGap = 4096;
+    const std::unique_ptr<char[]> stage(new (std::nothrow) char[kStage]);
+    char *stage_to = nullptr;
+    size_t staged = 0;
+    auto flush = [&]() -> hipError_t {
+        const hipError_t r = staged ? hipMemcpy(stage_to, stage.get(), staged, hipMemcpyHostToDevice) : hipSuccess;
+        staged = 0;
+        return r;
+    };
     auto up = [&](const char *name, const void *src, size_t n) -> hipError_t {
         if (n == 0) return hipSuccess;
-        return hipMemcpy(wsptr<char>(p, name), src, n, hipMemcpyHostToDevice);
+        char *to = wsptr<char>(p, name);
+        if (n > kStage || !stage) return hipMemcpy(to, src, n, hipMemcpyHostToDevice);
+        if (staged && (to < stage_to + staged || to > stage_to + staged + kGap || (size_t)(to - stage_to) + n > kStage)) {
+            const hipError_t r = flush();
+            if (r != hipSuccess) return r;
+        }
+        if (!staged) stage_to = to;
+        const size_t at = to - stage_to;
+        std::memset(stage.get() + staged, 0, at - staged);
+        std::memcpy(stage.get() + at, src, n);
+        staged = at + n;
+        return hipSuccess;
     };
+    if (!p->report) {
+        void *q = nullptr;
+        HIPCHK(p, hipHostMalloc(&q, 8 * (5 * (size_t)p->nfilm + 2), hipHostMallocDefault));
+        p->report.reset(static_cast<double *>(q));
+    }
     HIPCHK(p, up("s", p->s.data(), 8 * p->s.size()));
     HIPCHK(p, up("w", p->w.data(), 8 * p->w.size()));
     HIPCHK(p, up("mirror", p->mirror.data(), 4 * p->mirror.size()));
@@ -1477,6 +1512,7 @@ bte_status bte_bind(bte_problem *p, void *ws, size_t bytes)
         p->cg_epoch = 0;
         HIPCHK(p, cg_solve_init(p->dim, p->cg_R, q.max_ghost, p->cg_nblk, &p->cg_one));
     }
+    HIPCHK(p, flush());
     // default fields: no source, no extra scattering
     HIPCHK(p, hipMemset(wsptr<void>(p, "zrow"), 0, 8 * 8 * (size_t)p->nk));
     HIPCHK(p, hipMemset(wsptr<void>(p, "fdone"), 0, 4 * (size_t)p->nfilm));
@@ -1596,7 +1632,7 @@ bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int
 {
     const Dev &d = p->dev;
     if (p->floating_any) {
-        launch_film_mean(d, b, p->fmean, p->fpart, p->fseg, s);
+        launch_film_mean(d, b, p->fmean, p->fpart, p->fseg, nullptr, s);
         launch_sub_film_mean(d, b, p->fmean, s);
     }
     CgArgs g = cg_args(p, corr);
@@ -1632,7 +1668,7 @@ bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int
         }
     }
     if (p->floating_any) {
-        launch_film_mean(d, x_out, p->fmean, p->fpart, p->fseg, s);
+        launch_film_mean(d, x_out, p->fmean, p->fpart, p->fseg, nullptr, s);
         launch_sub_film_mean(d, x_out, p->fmean, s);
     }
     return hipGetLastError() == hipSuccess;
@@ -1743,7 +1779,6 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
     // moments of the start field
     launch_moments<T>(d, e, nullptr, p->part, s);
     launch_finalize(d, p->part, 1, p->Tref, nullptr, nullptr, nullptr, p->TL, p->T0, p->q0, s);
-    std::vector<double> feps(5 * (size_t)p->nfilm);
     // per-geometry convergence: a converged geometry is no longer swept or
     // corrected (its field, T_L and pending correction stay as they were
     // when it met the tolerances)
@@ -1771,7 +1806,12 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
         const T *ein = buf[cur];
         T *eout = buf[1 - cur];
         const bool one = one_launch(p) && !gave_up;
-        const unsigned *qword = one ? p->d_queue + 1 : nullptr;
+        Report rep;
+        rep.out = p->report.get();
+        rep.feps = p->feps;
+        rep.n = 5 * p->nfilm;
+        rep.sweep_abort = one ? p->d_queue + 1 : nullptr;
+        rep.cg_abort = p->cgplan.abortw;
         st.updates += active_cells * (double)p->nk;
         HIPCHK(p, hipEventRecord(ev[0], s));
         launch_walls<T>(d, ein, p->dpend, p->d_wrec, p->d_wden, p->din, p->nw, s);
@@ -1805,17 +1845,15 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
             } else if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s)) {
                 FAIL(p, BTE_ERR_HIP, "CG failed");
             }
-            launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, qword, s);
+            launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, rep, s);
         } else {
-            launch_tl_update(nc, p->TLkin, nullptr, p->TL, nullptr, d.fid, d.fdone, qword, s);
+            launch_tl_update(nc, p->TLkin, nullptr, p->TL, nullptr, d.fid, d.fdone, rep, s);
         }
         HIPCHK(p, hipEventRecord(ev[4], s));
-        HIPCHK(p, hipMemcpyAsync(feps.data(), p->feps, 8 * feps.size(), hipMemcpyDeviceToHost, s));
-        unsigned qabort = 0, cg_abort = 0;
-        if (one) HIPCHK(p, hipMemcpyAsync(&qabort, qword, 4, hipMemcpyDeviceToHost, s));
-        if (cg_epoch) HIPCHK(p, hipMemcpyAsync(&cg_abort, p->cgplan.abortw, 4, hipMemcpyDeviceToHost, s));
         HIPCHK(p, hipStreamSynchronize(s));
-        if (qabort) {
+        const double *const feps = p->report.get();
+        const unsigned cg_abort = cg_epoch ? (unsigned)feps[rep.n + 1] : 0u;
+        if (feps[rep.n] != 0.0) {
             if (p->persistent > 0) FAIL(p, BTE_ERR_HIP, "one-launch sweep: a wait for an upwind tile gave up");
             // T_L and the pending correction are still those of this iteration's start: the iteration again
             gave_up = true;
@@ -1827,7 +1865,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
         if (cg_epoch && cg_abort == cg_epoch) {
             // the blocks gave up waiting for each other: this correction again, a launch per iteration
             if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
-            launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, qword, s);
+            launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, Report{}, s);
         }
         {
             float ms[4];
@@ -1888,7 +1926,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
     // shift to zero mean T - T_ref (T0 now holds the last moments)
     double *fshift = nullptr;
     if (p->floating_any) {
-        launch_film_mean(d, p->T0, p->fmean, p->fpart, p->fseg, s);
+        launch_film_mean(d, p->T0, p->fmean, p->fpart, p->fseg, nullptr, s);
         // only floating films are shifted: zero the others on the host side
         std::vector<double> fm(p->nfilm);
         HIPCHK(p, hipMemcpyAsync(fm.data(), p->fmean, 8 * fm.size(), hipMemcpyDeviceToHost, s));
@@ -2027,7 +2065,7 @@ bte_status adjoint_impl(bte_problem *p, const T *e, double *grad, bte_solve_stat
     double sws = 0, svv = 0;
     for (int al = 0; al < p->na; ++al) sws += p->w[al] * p->w[al] * p->s[3 * al] * p->s[3 * al];
     for (int l = 0; l < p->nl; ++l) svv += p->v[l] * p->v[l];
-    std::vector<double> g2(p->nfilm), mres(p->nfilm);
+    std::vector<double> g2(p->nfilm);
     for (int f = 0; f < p->nfilm; ++f) {
         const Film &fm = p->films[f];
         const double gf = fm.len[0] / (fm.pdT[0] * fm.ncell);
@@ -2060,10 +2098,10 @@ bte_status adjoint_impl(bte_problem *p, const T *e, double *grad, bte_solve_stat
                                         p->na_oct, p->nchunk_oct, p->tile_cap_tr, p->part, s));
             launch_adj_post(d, p->part, p->noct, p->adju, p->adjr2, s);
         }
-        launch_film_mean(d, p->adjr2, p->fmean, p->fpart, p->fseg, s);
+        launch_film_mean(d, p->adjr2, p->fmean, p->fpart, p->fseg, p->report.get(), s);
         HIPCHK(p, hipEventRecord(ev[2], s));
-        HIPCHK(p, hipMemcpyAsync(mres.data(), p->fmean, 8 * mres.size(), hipMemcpyDeviceToHost, s));
         HIPCHK(p, hipStreamSynchronize(s));
+        const double *const mres = p->report.get();
         {
             float ms[2];
             for (int i = 0; i < 2; ++i) HIPCHK(p, hipEventElapsedTime(&ms[i], ev[i], ev[i + 1]));
@@ -2098,7 +2136,7 @@ bte_status adjoint_impl(bte_problem *p, const T *e, double *grad, bte_solve_stat
             // v = L^-1 P^T y; the sweep's isotropic term becomes X + v
             if (!run_cg_now(p, 1, p->adju, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s))
                 FAIL(p, BTE_ERR_HIP, "CG failed");
-            launch_tl_update(nc, p->adjX, p->delta, p->TL, nullptr, nullptr, nullptr, nullptr, s);
+            launch_tl_update(nc, p->adjX, p->delta, p->TL, nullptr, nullptr, nullptr, Report{}, s);
             X = p->TL;
         }
         HIPCHK(p, hipEventRecord(ev[3], s));

@@ -143,6 +143,15 @@ struct CgPlan {
     int max_ghost;
 };
 
+// What an iteration's last kernel hands to the host: n convergence measures,
+// then the two abort words (0 where there is none), in pinned host memory.
+struct Report {
+    double *out = nullptr;
+    const double *feps = nullptr;
+    int n = 0;
+    const unsigned *sweep_abort = nullptr, *cg_abort = nullptr;
+};
+
 // Gauss-Legendre nodes / weights on [-1, 1], ascending.
 void gauss_legendre(int n, std::vector<double> &x, std::vector<double> &w);
 // Directions and weights on the sphere (two- and three-dimensional
