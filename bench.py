@@ -229,7 +229,7 @@ def bench_transient(args):
         "vs_baseline": None, "dtype": "f32 (e), f64 (moments)", "data": "synthetic (seeded bands, laser pulse)",
         "config": {"workload": "cube3d_laser: %d^3 cells, 2 um, 40 bands, 128 directions, MC limiter, dt 0.5 ps"
                    % n, "n": n},
-        "roofline": {"bound": "hbm", "kernel": "k_transient3d<float,MC> (one launch per step)",
+        "roofline": {"bound": "hbm", "kernel": "k_transient3d_quad<float,MC> (one launch per step)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic, "avg_launch_ms": kern_ms,
                      "bytes_per_launch": BYTES_PER_UPDATE[B.F32] * r["upd"]},
@@ -323,7 +323,7 @@ def bench_ttg(args):
         "data": "synthetic (gray band, cosine grating)",
         "config": {"workload": "ttg1d: 1000 cells, one 1 um period, 512 directions, 1 band, xi 0.1 / 1 / 10 "
                    "to t* = 2, no limiter"},
-        "roofline": {"bound": "hbm", "kernel": "k_transient_tile<float,1D,NONE> (one launch per step)",
+        "roofline": {"bound": "hbm", "kernel": "k_transient1d<float,NONE> (one launch per step, T_L included)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": None, "avg_launch_ms": kern_ms,
                      "bytes_per_launch": BYTES_PER_UPDATE[B.F32] * f32[0]["upd"],
@@ -564,9 +564,9 @@ def bench_mesh(args):
            "ms_per_iteration": t / st["iters"] * 1e3,
            "phase_ms_per_iteration": {"sweep": sweep_ms, "gradient_walls_residual": st["ms_walls"] / st["iters"],
                                       "moments": st["ms_post"] / st["iters"]},
-           "roofline": {"bound": "hbm", "kernel": "k_mesh_sweep_level<float> (the level launches of one sweep)",
+           "roofline": {"bound": "hbm", "kernel": "k_mesh_sweep_dir<float> (a block per direction and group of bands)",
                         "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                        "traffic": None, "avg_sweep_ms": sweep_ms, "launches_per_sweep": prob.n_levels,
+                        "traffic": None, "avg_sweep_ms": sweep_ms, "launches_per_sweep": 1,
                         "bytes_per_sweep": sweep_bytes}}
     if not args.no_cpu_baseline:
         from oracle import mesh as M
@@ -622,9 +622,9 @@ def bench_mesh3d(args):
            "ms_per_iteration": t / st["iters"] * 1e3,
            "phase_ms_per_iteration": {"sweep": sweep_ms, "gradient_walls_residual": st["ms_walls"] / st["iters"],
                                       "moments": st["ms_post"] / st["iters"]},
-           "roofline": {"bound": "hbm", "kernel": "k_mesh_sweep_level<float> (the level launches of one sweep)",
+           "roofline": {"bound": "hbm", "kernel": "k_mesh_sweep_dir<float> (a block per direction and group of bands)",
                         "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                        "traffic": None, "avg_sweep_ms": sweep_ms, "launches_per_sweep": prob.n_levels,
+                        "traffic": None, "avg_sweep_ms": sweep_ms, "launches_per_sweep": 1,
                         "bytes_per_sweep": sweep_bytes}}
     print(json.dumps(out), flush=True)
 
