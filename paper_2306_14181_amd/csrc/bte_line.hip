@@ -76,6 +76,10 @@ __device__ inline float quot(float n, float, float inv) { return n * inv; }
 __device__ inline double recip(double d) { return 1.0 / d; }
 __device__ inline float recip(float d) { return __builtin_amdgcn_rcpf(d); }
 
+// What an inflow x adds behind cells that pass it by the factor a: nothing where
+// a is zero (a pore, an end, damped below the smallest number), whatever x is.
+template <typename T> __device__ inline T inflow(T a, T x) { return a * (a != (T)0 ? x : (T)0); }
+
 // Forward sweep of a line.  Block (geometry, octant, group of 16 lanes); the
 // lanes by 4 runs of kSeg cells in a wavefront, a round of (wavefronts) x 4 x
 // kSeg cells at a time, the last increment of a round handed to the next.
@@ -163,7 +167,7 @@ __global__ __launch_bounds__(kLineThreads) void k_sweep1d(Dev d, const T *__rest
         for (int o = LW; o < 64; o *= 2) {
             const T Ap = __shfl_up(A, o, 64), Bp = __shfl_up(Bv, o, 64);
             if (lane >= o) {
-                Bv += A * Bp;
+                Bv += inflow(A, Bp);
                 A *= Ap;
             }
         }
@@ -177,17 +181,17 @@ __global__ __launch_bounds__(kLineThreads) void k_sweep1d(Dev d, const T *__rest
         __syncthreads();
         T in = carry;
         for (int w = 0; w < nwave; ++w) {
-            const T next = totB[w][kl] + totA[w][kl] * carry;
+            const T next = totB[w][kl] + inflow(totA[w][kl], carry);
             if (w == wave) in = carry;
             carry = next;
         }
-        in = exB + exA * in;
+        in = exB + inflow(exA, in);
 #pragma unroll
         for (int j = 0; j < kSeg; ++j) {
             if (f0 + q0 + j >= n) break;
             const LineCell me = tab[q0 + j + 2];
             const bool solid = me.code & kSolidBit;
-            const T en = solid ? v[j + 2] + (b[j] + g[j] * in) : v[j + 2];
+            const T en = solid ? v[j + 2] + (b[j] + inflow(g[j], in)) : v[j + 2];
             if (active) eout[(size_t)me.cell * d.nk + k] = en;
             const double x = solid && active ? (double)en : 0.0;
             const double m0 = row_sum(L.w * x), m1 = row_sum(L.witau * x), m2 = row_sum(L.wv[0] * x);

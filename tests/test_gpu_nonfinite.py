@@ -1,0 +1,57 @@
+"""Values that are not finite stay where the scheme carries them: along a lane
+of one part of a line, and not across a pore.  The field that a stopped solve
+leaves is compared with the solve of the same field without those values."""
+import numpy as np
+import pytest
+
+import bte_inputs as I
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+T, S, D = I.BC_THERMAL, I.BC_SPECULAR, I.BC_DIFFUSE
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2306_14181_amd import bte
+    bte.load()
+    return bte
+
+
+def solve(B, prob, e):
+    """The field that one source iteration leaves, and whether it ended on a value that is not finite."""
+    try:
+        prob.steady_solve(e, init=False, allow_not_converged=True)
+        bad = False
+    except B.BteError as x:
+        assert x.status == B.BTE_ERR_NONFINITE
+        bad = True
+    return e.cpu().numpy(), bad
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("n,pore", [(40, 20), (40, 21), (300, 63), (300, 255), (300, 256), (700, 530)])
+def test_line_behind_a_pore(B, prec, value, n, pore):
+    solid = np.ones(n, dtype=np.uint8)
+    solid[pore] = 0
+    geo = dict(dim=1, n=[n, 1, 1], len=[n * 20e-9, 1.0, 1.0], bc=[T, T] + [S] * 4, bcT=[301.0, 299.0] + [300.0] * 4,
+               pdT=[0.0] * 3, solid=solid, pore_bc=D)
+    mat = I.bands(17, 5, 1e-12, 1e-10)
+    mat.update(n_theta=3, n_phi=1, Tref=300.0)
+    prob = B.Problem(geo, mat, dict(precision=B.F64 if prec == "f64" else B.F32, scheme=B.SEQUENTIAL, max_iter=1,
+                                    residual_temp=0.0, residual_flux=0.0))
+    rng = np.random.default_rng(8)
+    e0 = rng.uniform(-1, 1, (n, 30)) * np.tile(mat["C"] / (4 * np.pi), 6) * solid[:, None]
+    for part, at in ((slice(pore + 1, n), pore - 3), (slice(0, pore), pore + 3)):
+        want, bad = solve(B, prob, torch.as_tensor(e0.reshape(-1), device="cuda").to(prob.dtype))
+        assert not bad
+        e1 = e0.copy()
+        e1[at] = value
+        got, bad = solve(B, prob, torch.as_tensor(e1.reshape(-1), device="cuda").to(prob.dtype))
+        assert bad
+        np.testing.assert_array_equal(got.reshape(n, 30)[part], want.reshape(n, 30)[part])
