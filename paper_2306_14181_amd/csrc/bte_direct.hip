@@ -83,7 +83,9 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // One axis: out[o][j][q] = sum_i M[j][i] in[o][i][q], M = V^T (fwd) or V;
 // columns are numbered o inner + q.  The last forward axis divides by the
-// eigenvalue of the operator (0 for its null vector).
+// eigenvalue of the operator (0 for its null vector).  The last axis back
+// (fin) gives 0 where the sum is not finite, that is everywhere if one value
+// of b is not: CG, too, returns 0 for such a b.
 // A block takes 16 x 16 outputs on the FP64 matrix cores (16 x 16 x 4); its
 // four wavefronts split the sum over i, so that the few outputs of a line or a
 // small plane still keep loads in flight, straight from the caches: both
@@ -94,7 +96,7 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void k_axis_product(const double *__restrict__ in, double *__restrict__ out,
                                                       const double *__restrict__ V, int n, int inner, int cols, int fwd,
                                                       const double *__restrict__ lx, const double *__restrict__ ly,
-                                                      const double *__restrict__ lz, int n0, int n1, double zero)
+                                                      const double *__restrict__ lz, int n0, int n1, double zero, int fin)
 {
     constexpr int U = 8;   // steps of 4 in flight
     __shared__ double sm[4][kDT][kDT + 1];
@@ -133,7 +135,7 @@ __global__ __launch_bounds__(256) void k_axis_product(const double *__restrict__
         const double l = lx[i % n0] + (ly ? ly[i / n0 % n1] : 0.0) + (lz ? lz[i / (n0 * n1)] : 0.0);
         v = l > zero ? v / l : 0.0;
     }
-    out[at] = v;
+    out[at] = fin && !isfinite(v) ? 0.0 : v;
 }
 
 }  // namespace
@@ -155,7 +157,8 @@ hipError_t launch_direct(int dim, const int *n, const double *V, const double *l
         const int cols = nc / n[a];
         hipLaunchKernelGGL(k_axis_product, dim3((n[a] + kDT - 1) / kDT, (cols + kDT - 1) / kDT), dim3(256), 0, s, src, dst,
                            Va[a], n[a], inner[a], cols, fwd ? 1 : 0, last ? la[0] : nullptr,
-                           last && dim > 1 ? la[1] : nullptr, last && dim > 2 ? la[2] : nullptr, n[0], n[1], zero);
+                           last && dim > 1 ? la[1] : nullptr, last && dim > 2 ? la[2] : nullptr, n[0], n[1], zero,
+                           k == 2 * dim - 1 ? 1 : 0);
         src = dst;
     }
     return hipGetLastError();

@@ -55,3 +55,34 @@ def test_line_behind_a_pore(B, prec, value, n, pore):
         got, bad = solve(B, prob, torch.as_tensor(e1.reshape(-1), device="cuda").to(prob.dtype))
         assert bad
         np.testing.assert_array_equal(got.reshape(n, 30)[part], want.reshape(n, 30)[part])
+
+
+def box(dim, n):
+    n = list(n) + [1] * (3 - dim)
+    return dict(dim=dim, n=n, len=[x * 20e-9 if a < dim else 1.0 for a, x in enumerate(n)], bc=[T, T] + [S, D] * 2,
+                bcT=[301.0, 299.0] + [300.0] * 4, pdT=[0.0] * 3, solid=np.ones(np.prod(n), dtype=np.uint8), pore_bc=D)
+
+
+def after(B, dim, n, e0, gamma, **ctl):
+    """The field after a solve whose correction goes by eigenvectors (gamma None) or by CG (gamma zero)."""
+    mat = I.bands(17, 3, 1e-12, 1e-10)
+    mat.update(n_theta=2, n_phi=1, Tref=300.0)
+    prob = B.Problem(box(dim, n), mat, dict(precision=B.F64, scheme=B.SYNTHETIC, residual_temp=0.0, residual_flux=0.0,
+                                            **ctl))
+    if gamma:
+        prob.set_fields(None, torch.zeros(prob.n_cells, dtype=torch.float64, device="cuda"))
+    e = np.random.default_rng(3).uniform(-1, 1, prob.n_unknowns)
+    if e0 is not None:
+        e[prob.n_unknowns // 2] = e0
+    return solve(B, prob, torch.as_tensor(e, device="cuda"))
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("dim,n", [(1, (50,)), (2, (13, 11)), (3, (7, 6, 5))])
+def test_correction_of_a_defect_that_is_not_finite(B, dim, n, value):
+    """CG stops before its first step and corrects nothing; so do the eigenvectors."""
+    got, bad = after(B, dim, n, value, False, max_iter=3)
+    want, bad2 = after(B, dim, n, value, True, max_iter=3)
+    assert bad and bad2
+    np.testing.assert_array_equal(got, want)
+    assert np.isfinite(got).any()
