@@ -1048,7 +1048,7 @@ void plan_direct(bte_problem *p)
 double cg_bound(const bte_problem::Direct &q, double rtol)
 {
     if (q.low.empty()) return 1.0;
-    double best = 1e300, lost = std::log(2.0 * std::sqrt(2.0 / q.low[0]) / std::min(rtol, 1.0));
+    double best = 1e300, lost = std::log(2.0 * std::sqrt(2.0 / q.low[0]) / rtol);
     for (size_t m = 0; m < q.low.size(); ++m) {
         best = std::min(best, (double)m + 0.5 * std::sqrt(2.0 / q.low[m]) * lost);
         lost += std::log(2.0 / q.low[m]);
@@ -1059,10 +1059,10 @@ double cg_bound(const bte_problem::Direct &q, double rtol)
 // Whether a solve goes by eigenvectors: where CG could not have stopped short of
 // rtol, so that the direct solution is the one it was asked for (cg_bound
 // iterations allowed, or as many as cells).  With fewer the iterate that the cap
-// leaves is the result asked for.
+// leaves is the result asked for, and with a tolerance that zero meets CG's zero.
 bool direct_use(const bte_problem *p, int corr, double rtol, int maxit)
 {
-    if (!p->direct_ok || !p->gamma_zero) return false;
+    if (!p->direct_ok || !p->gamma_zero || !(rtol < 1.0)) return false;
     return maxit >= std::min((double)p->nc, cg_bound(p->direct[corr], rtol));
 }
 

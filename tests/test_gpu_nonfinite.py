@@ -86,3 +86,12 @@ def test_correction_of_a_defect_that_is_not_finite(B, dim, n, value):
     assert bad and bad2
     np.testing.assert_array_equal(got, want)
     assert np.isfinite(got).any()
+
+
+@pytest.mark.parametrize("rtol", [1.0, 4.0])
+@pytest.mark.parametrize("dim,n", [(1, (50,)), (2, (13, 11)), (3, (7, 6, 5))])
+def test_correction_met_by_zero(B, dim, n, rtol):
+    """A tolerance that zero meets: no step of CG, no correction."""
+    got, _ = after(B, dim, n, None, False, max_iter=3, cg_rtol=rtol)
+    want, _ = after(B, dim, n, None, True, max_iter=3, cg_rtol=rtol)
+    np.testing.assert_array_equal(got, want)
