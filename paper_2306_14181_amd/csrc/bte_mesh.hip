@@ -85,12 +85,13 @@ struct alignas(16) MeshRec {
 constexpr int kDirThreads = 256;
 constexpr int kDirAhead = 4;    // steps a thread's own values are loaded ahead (their cells: twice that)
 
-// Schedule of the per-direction sweep: S items per step, nb bands per block.
+// Schedule of the per-direction sweep: up to S items per step, nb bands per block.
 struct DirPlan {
-    const int *base;       // [na] first step of a direction (in the step-major arrays)
+    const int *base;       // [na] first entry of a direction in `first`
     const int *nstep;      // [na] its steps, padded to a multiple of kDirAhead
-    const int *cell;       // [steps][S] cell of an item, -1: none
-    const MeshRec *rec;    // [steps][S]
+    const int *first;      // per direction: first item of each step, and 3 kDirAhead + 1 times the end
+    const int *cell;       // [na nc] cell of an item, step by step
+    const MeshRec *rec;    // [na nc]
     int S, nb, ng, slots;  // items per step, bands per block, blocks per direction, LDS slots (zero slot first, waste last)
 };
 
@@ -406,7 +407,10 @@ __global__ __launch_bounds__(kBlock) void k_mesh_sweep_level(MeshDev d, T *__res
 // that the host gives out again after an item's last reader (a few hundred
 // live at a time, 2 000 on 48 000 tetrahedra); the residual, the energy and the item records do not
 // depend on the sweep and are loaded kDirAhead steps before their use, the
-// cells that address them kDirAhead steps earlier still.  The barrier orders
+// cells that address them kDirAhead steps earlier still, a step's bounds another
+// kDirAhead.  Items are stored step after step without gaps: a strip of 4000 x 4
+// squares in triangles (20 bands) has about 8 000 steps of a few items each, and
+// S places a step took 9.1 GB of tables instead of 0.2.  The barrier orders
 // LDS only, so those loads stay in flight across it.  Sweep of the 2D mesh x
 // 128 directions x 20 bands FP32 2.46 -> 0.59 ms, of 48 000 tetrahedra x 96
 // directions 1.73 -> 0.89 ms; what is left is the fetch of row pieces (12
@@ -460,26 +464,40 @@ __global__ __launch_bounds__(kDirThreads) void k_mesh_sweep_dir(MeshDev d, DirPl
         vl[i] = d.v[l + i];
         itau[i] = d.itau[l + i];
     }
-    const size_t first = (size_t)q.base[al] * q.S + (lane ? item : 0);
-    const int *__restrict__ cp = q.cell + first;
-    const MeshRec *__restrict__ rp = q.rec + first;
-    const int n = q.nstep[al];
-    if ((int)threadIdx.x < q.nb) inc[threadIdx.x] = (T)0;   // slot 0: the increment of an absent coupling
-    int cell[kDirAhead], next[kDirAhead];
+    // the thread's item of the step [i, end) of items, its cell, and what the
+    // cell addresses; a thread that has none loads the step's last and drops it
+    const int *__restrict__ fp = q.first + q.base[al];
+    const int place = lane ? item : q.S;
+    auto mine = [&](int i, int end) { return min(i + place, end - 1); };
+    int cell[kDirAhead], next[kDirAhead], nidx[kDirAhead], end[kDirAhead + 1];
+    bool on[kDirAhead], non[kDirAhead];
     MeshRec rec[kDirAhead];
     Vec bv[kDirAhead], ev[kDirAhead];
-#pragma unroll
-    for (int u = 0; u < kDirAhead; ++u) {
-        cell[u] = cp[(size_t)u * q.S];
-        next[u] = cp[(size_t)(u + kDirAhead) * q.S];
-        rec[u] = rp[(size_t)u * q.S];
-        const size_t at = (size_t)(cell[u] < 0 ? 0 : cell[u]) * nk + k0;
+    auto fetch = [&](int u, int i) {
+        rec[u] = q.rec[i];
+        const size_t at = (size_t)cell[u] * nk + k0;
         bv[u] = *reinterpret_cast<const Vec *>(b + at);
         ev[u] = band_load<T, V, EA>(e + at);
+    };
+    const int n = q.nstep[al];
+    if ((int)threadIdx.x < q.nb) inc[threadIdx.x] = (T)0;   // slot 0: the increment of an absent coupling
+#pragma unroll
+    for (int u = 0; u < kDirAhead; ++u) {
+        const int i = mine(fp[u], fp[u + 1]);
+        on[u] = place < fp[u + 1] - fp[u];
+        cell[u] = q.cell[i];
+        nidx[u] = mine(fp[u + kDirAhead], fp[u + kDirAhead + 1]);
+        non[u] = place < fp[u + kDirAhead + 1] - fp[u + kDirAhead];
+        next[u] = q.cell[nidx[u]];
+        fetch(u, i);
     }
+#pragma unroll
+    for (int u = 0; u <= kDirAhead; ++u) end[u] = fp[2 * kDirAhead + u];
     lds_barrier();
-    // the arrays hold 2 kDirAhead steps past a direction's last
     for (int k = 0; k < n; k += kDirAhead) {
+        int ahead[kDirAhead + 1];   // bounds of the steps k + 3 kDirAhead ..
+#pragma unroll
+        for (int u = 0; u <= kDirAhead; ++u) ahead[u] = fp[k + 3 * kDirAhead + u];
 #pragma unroll
         for (int u = 0; u < kDirAhead; ++u) {
             const MeshRec r = rec[u];
@@ -497,20 +515,21 @@ __global__ __launch_bounds__(kDirThreads) void k_mesh_sweep_dir(MeshDev d, DirPl
                 de.x[i] = (T)q0;
                 en.x[i] = (T)((double)ev[u].x[i] + q0);
             }
-            if (lane) {
+            if (on[u]) {
                 *reinterpret_cast<Vec *>(inc + (int)r.own * q.nb + off) = de;
-                if (cell[u] >= 0) band_store<T, V, EA>(e + (size_t)cell[u] * nk + k0, en);
+                band_store<T, V, EA>(e + (size_t)cell[u] * nk + k0, en);
             }
-            // step k + u + kDirAhead into this place
-            const size_t s1 = (size_t)(k + u + kDirAhead);
+            // step k + u + kDirAhead into this place, the cell of the one as far behind it
             cell[u] = next[u];
-            next[u] = cp[(s1 + kDirAhead) * q.S];
-            rec[u] = rp[s1 * q.S];
-            const size_t at = (size_t)(cell[u] < 0 ? 0 : cell[u]) * nk + k0;
-            bv[u] = *reinterpret_cast<const Vec *>(b + at);
-            ev[u] = band_load<T, V, EA>(e + at);
+            on[u] = non[u];
+            fetch(u, nidx[u]);
+            nidx[u] = mine(end[u], end[u + 1]);
+            non[u] = place < end[u + 1] - end[u];
+            next[u] = q.cell[nidx[u]];
             lds_barrier();
         }
+#pragma unroll
+        for (int u = 0; u <= kDirAhead; ++u) end[u] = ahead[u];
     }
 }
 
@@ -637,7 +656,7 @@ struct bte_mesh_problem {
     std::vector<int> item_c, item_al;
     // per-direction sweep (dir_V > 0): bands per thread, schedule
     int dir_V = 0;
-    std::vector<int> dir_base, dir_nstep, dir_cell;
+    std::vector<int> dir_base, dir_nstep, dir_first, dir_cell;
     std::vector<MeshRec> dir_rec;
     DirPlan dir{};
     std::vector<int4> item_up;
@@ -803,11 +822,12 @@ static void morton_order(const std::vector<double> &xc, int nc, int D, std::vect
 
 // Schedule of one direction: cells in level order, each in the first step
 // after its upwind cells' that has room for it; slots given out step by step
-// and taken back after the step of an item's last reader.  cells / recs:
-// steps of S, n steps padded to a multiple of kDirAhead plus 2 kDirAhead empty
-// ones (read ahead).  Returns the number of slots (0: the zero slot).
+// and taken back after the step of an item's last reader.  cells / recs: the
+// direction's nc items, step by step; first: first item of each of n steps (a
+// multiple of kDirAhead), then their end 3 kDirAhead + 1 times (read ahead).
+// Returns the number of slots (0: the zero slot).
 int dir_direction(const bte_mesh_problem *p, int al, const int *level, const uint8_t *lagm, int S, int &n,
-                  std::vector<int> &cells, std::vector<MeshRec> &recs)
+                  std::vector<int> &first, int *cells, MeshRec *recs)
 {
     const int nc = p->nc;
     std::vector<int> order(nc), start(p->nlev + 1, 0), step(nc), room, place;
@@ -854,9 +874,8 @@ int dir_direction(const bte_mesh_problem *p, int al, const int *level, const uin
     }
     const int ns = (int)used.size();
     n = (ns + kDirAhead - 1) / kDirAhead * kDirAhead;
-    cells.assign((size_t)(n + 2 * kDirAhead) * S, -1);
-    recs.assign((size_t)(n + 2 * kDirAhead) * S, MeshRec{});
-    std::vector<int> fill(ns, 0), slot(nc, 0), spare;
+    first.assign(n + 3 * kDirAhead + 1, (al + 1) * nc);
+    std::vector<int> slot(nc, 0), spare;
     std::vector<std::vector<int>> back(ns + 1);   // slots free again at the start of a step
     std::vector<std::vector<int>> at(ns);
     for (int c : order) at[step[c]].push_back(c);
@@ -875,15 +894,17 @@ int dir_direction(const bte_mesh_problem *p, int al, const int *level, const uin
         }
     }
     if (slots + 1 > 65535) return -1;
-    for (int k = 0; k < ns; ++k)
+    int i = 0;
+    for (int k = 0; k < ns; ++k) {
+        first[k] = al * nc + i;
         for (int c : at[k]) {
-            const size_t i = (size_t)k * S + fill[k]++;
             MeshRec r = rec[c];
             for (int m = 0; m < 3; ++m) r.up[m] = up[c][m] >= 0 ? (unsigned short)slot[up[c][m]] : 0;
             r.own = slot[c] >= 0 ? (unsigned short)slot[c] : 0xffff;
             cells[i] = c;
-            recs[i] = r;
+            recs[i++] = r;
         }
+    }
     return slots;
 }
 
@@ -920,7 +941,7 @@ template <typename F> bool on_threads(int n, F &&fn)
 // often; 48 000 tetrahedra x 96 directions: 0.89, 0.91 and 0.98 ms), fewer
 // where the live increments do not fit the LDS.  False if they never do (the
 // launch per level is used then).
-bool dir_schedule(bte_mesh_problem *p, const std::vector<int> &level, const std::vector<uint8_t> &lagm)
+bool dir_plan(bte_mesh_problem *p, const std::vector<int> &level, const std::vector<uint8_t> &lagm)
 {
     const int es = (int)p->esize();
     int V = 16 / es;
@@ -928,27 +949,24 @@ bool dir_schedule(bte_mesh_problem *p, const std::vector<int> &level, const std:
     const int ng0 = std::max(1, std::min(p->nl / V, 256 / p->na));
     for (int nb = ((p->nl + ng0 - 1) / ng0 + V - 1) / V * V;; nb = std::max(V, nb / 2 / V * V)) {
         const int S = kDirThreads / (nb / V);
-        std::vector<std::vector<int>> cells(p->na);
-        std::vector<std::vector<MeshRec>> recs(p->na);
+        std::vector<std::vector<int>> first(p->na);
         std::vector<int> nstep(p->na, 0), w(p->na, 0);
+        p->dir_cell.resize((size_t)p->na * p->nc);
+        p->dir_rec.resize((size_t)p->na * p->nc);
         const bool done = on_threads(p->na, [&](int al) {
             const size_t o = (size_t)al * p->nc;
-            w[al] = dir_direction(p, al, &level[o], &lagm[o], S, nstep[al], cells[al], recs[al]);
+            w[al] = dir_direction(p, al, &level[o], &lagm[o], S, nstep[al], first[al], &p->dir_cell[o], &p->dir_rec[o]);
         });
         if (!done || *std::min_element(w.begin(), w.end()) < 0) return false;
         const int slots = *std::max_element(w.begin(), w.end());
         if ((size_t)(slots + 1) * nb * es <= 150 * 1024) {
-            int total = 0;
             for (int al = 0; al < p->na; ++al) {
-                p->dir_base.push_back(total);
-                total += nstep[al] + 2 * kDirAhead;
-                p->dir_cell.insert(p->dir_cell.end(), cells[al].begin(), cells[al].end());
-                p->dir_rec.insert(p->dir_rec.end(), recs[al].begin(), recs[al].end());
-                std::vector<MeshRec>().swap(recs[al]);
+                p->dir_base.push_back((int)p->dir_first.size());
+                p->dir_first.insert(p->dir_first.end(), first[al].begin(), first[al].end());
             }
             p->dir_nstep = nstep;
             for (MeshRec &r : p->dir_rec)
-                if (r.own == 0xffff || r.own == 0) r.own = (unsigned short)slots;   // empty places and unread items
+                if (r.own == 0xffff) r.own = (unsigned short)slots;   // items nobody reads
             p->dir.S = S;
             p->dir.nb = nb;
             p->dir.ng = (p->nl + nb - 1) / nb;
@@ -958,6 +976,24 @@ bool dir_schedule(bte_mesh_problem *p, const std::vector<int> &level, const std:
         }
         if (nb == V) return false;
     }
+}
+
+// dir_plan, with nothing left behind where it finds no plan or no memory for it.
+bool dir_schedule(bte_mesh_problem *p, const std::vector<int> &level, const std::vector<uint8_t> &lagm)
+{
+    bool ok = false;
+    try {
+        ok = dir_plan(p, level, lagm);
+    } catch (...) {
+    }
+    if (ok) return true;
+    std::vector<int>().swap(p->dir_cell);
+    std::vector<int>().swap(p->dir_first);
+    std::vector<MeshRec>().swap(p->dir_rec);
+    p->dir_base.clear();
+    p->dir_nstep.clear();
+    p->dir_V = 0;
+    return false;
 }
 
 // Everything after the cells' geometry: least-squares stencils and
@@ -1543,6 +1579,7 @@ size_t bte_mesh_workspace_bytes(const bte_mesh_problem *p)
     add(8 * p->rec_den.size() + 8);
     if (p->dir_V > 0) {
         add(8 * (size_t)p->na);
+        add(4 * p->dir_first.size());
         add(4 * p->dir_cell.size());
         add(sizeof(MeshRec) * p->dir_rec.size());
     }
@@ -1617,6 +1654,7 @@ bte_status bte_mesh_bind(bte_mesh_problem *p, void *ws_dev, size_t bytes)
         MHIP(p, up(p->dir_nstep.data(), 4 * (size_t)p->na, x + 4 * (size_t)p->na));
         q.base = (const int *)x;
         q.nstep = q.base + p->na;
+        x = take(4 * p->dir_first.size()); MHIP(p, up(p->dir_first.data(), 4 * p->dir_first.size(), x)); q.first = (const int *)x;
         x = take(4 * p->dir_cell.size()); MHIP(p, up(p->dir_cell.data(), 4 * p->dir_cell.size(), x)); q.cell = (const int *)x;
         x = take(sizeof(MeshRec) * p->dir_rec.size());
         MHIP(p, up(p->dir_rec.data(), sizeof(MeshRec) * p->dir_rec.size(), x));
