@@ -1166,70 +1166,64 @@ bte_status bte_setup(const bte_geometry *geo, int n_geo, const bte_material *mat
     return bte_setup_multi(geo, n_geo, mat, 1, nullptr, nullptr, 0, ctl, out);
 }
 
-bte_status bte_setup_multi(const bte_geometry *geo, int n_geo, const bte_material *mats, int n_mat,
-                           const int *geo_mat, const bte_interface *ifc, int n_ifc, const bte_control *ctl,
-                           bte_problem **out)
+}  // extern "C"
+
+namespace {
+
+bte_status setup_problem(bte_problem *p, const bte_geometry *geo, int n_geo, const bte_material *mats, int n_mat,
+                         const int *geo_mat, const bte_interface *ifc, int n_ifc, const bte_control *ctl)
 {
-    if (!out) return BTE_ERR_ARG;
-    *out = nullptr;
-    bte_problem *p = new (std::nothrow) bte_problem();
-    if (!p) return BTE_ERR_ARG;
     bte_status st = BTE_OK;
-    auto bail = [&](bte_status s) {
-        // keep the handle so the caller can read the message
-        *out = p;
-        return s;
-    };
     if (!geo || n_geo < 1 || !mats || n_mat < 1 || !ctl || n_ifc < 0 || (n_ifc > 0 && !ifc)) {
         p->err = "null argument, n_geo < 1, n_mat < 1 or n_ifc < 0";
-        return bail(BTE_ERR_ARG);
+        return BTE_ERR_ARG;
     }
     const bte_material *mat = &mats[0];
     if (geo[0].dim < 1 || geo[0].dim > 3) {
         p->err = "dim must be 1, 2 or 3";
-        return bail(BTE_ERR_ARG);
+        return BTE_ERR_ARG;
     }
     for (int m = 0; m < n_mat; ++m) {
         const bte_material &mm = mats[m];
         if (mm.n_bands < 1 || mm.n_bands > 256 || !mm.C || !mm.v || !mm.tau) {
             p->err = "n_bands must be in [1, 256] with C, v, tau given";
-            return bail(BTE_ERR_ARG);
+            return BTE_ERR_ARG;
         }
         if (mm.n_bands != mat->n_bands || mm.n_theta != mat->n_theta || mm.n_phi != mat->n_phi ||
             mm.T_ref != mat->T_ref || mm.material_dim != mat->material_dim) {
             p->err = "materials must share n_bands, n_theta, n_phi, T_ref and material_dim";
-            return bail(BTE_ERR_ARG);
+            return BTE_ERR_ARG;
         }
     }
     for (int f = 0; f < n_geo; ++f)
         if (geo_mat && (geo_mat[f] < 0 || geo_mat[f] >= n_mat)) {
             p->err = "geo_mat out of range";
-            return bail(BTE_ERR_ARG);
+            return BTE_ERR_ARG;
         }
     p->ctl = *ctl;
     if (p->ctl.precision != BTE_F32 && p->ctl.precision != BTE_F64) {
         p->err = "precision must be BTE_F32 or BTE_F64";
-        return bail(BTE_ERR_ARG);
+        return BTE_ERR_ARG;
     }
     if (p->ctl.scheme != BTE_SEQUENTIAL && p->ctl.scheme != BTE_SYNTHETIC) {
         p->err = "scheme must be sequential or synthetic";
-        return bail(BTE_ERR_ARG);
+        return BTE_ERR_ARG;
     }
     if (p->ctl.limiter < 0 || p->ctl.limiter > 2) {
         p->err = "bad limiter";
-        return bail(BTE_ERR_ARG);
+        return BTE_ERR_ARG;
     }
     if (p->ctl.max_iter <= 0) p->ctl.max_iter = 10000;
     if (p->ctl.cg_max_iter <= 0) p->ctl.cg_max_iter = 2000;
     if (!(p->ctl.cg_rtol > 0)) p->ctl.cg_rtol = 1e-10;
     if (mat->material_dim != 0 && mat->material_dim != 2 && mat->material_dim != 3) {
         p->err = "material_dim must be 0, 2 or 3";
-        return bail(BTE_ERR_ARG);
+        return BTE_ERR_ARG;
     }
     const bool planar = mat->material_dim == 2;
     if (planar && geo[0].dim == 3) {
         p->err = "a two-dimensional material takes a 1D or 2D geometry";
-        return bail(BTE_ERR_ARG);
+        return BTE_ERR_ARG;
     }
     p->omega = planar ? 2.0 * M_PI : 4.0 * M_PI;
     p->Tref = mat->T_ref;
@@ -1245,7 +1239,7 @@ bte_status bte_setup_multi(const bte_geometry *geo, int n_geo, const bte_materia
             const bte_material &mm = mats[m];
             if (!(mm.C[l] > 0) || !(mm.v[l] >= 0) || !(mm.tau[l] > 0)) {
                 p->err = "band properties must satisfy C > 0, v >= 0, tau > 0";
-                return bail(BTE_ERR_ARG);
+                return BTE_ERR_ARG;
             }
             const size_t i = (size_t)m * p->nl + l;
             p->C4[i] = mm.C[l] / p->omega;
@@ -1264,30 +1258,30 @@ bte_status bte_setup_multi(const bte_geometry *geo, int n_geo, const bte_materia
         if (q.geo_a < 0 || q.geo_a >= n_geo || q.geo_b < 0 || q.geo_b >= n_geo || q.face_a < 0 ||
             q.face_a >= 2 * geo[0].dim || q.face_b < 0 || q.face_b >= 2 * geo[0].dim || !q.beta_ab || !q.beta_ba) {
             p->err = "interface " + std::to_string(i) + ": bad geometry, face or beta";
-            return bail(BTE_ERR_ARG);
+            return BTE_ERR_ARG;
         }
         const int ax = q.face_a >> 1;
         if ((q.face_b >> 1) != ax || q.face_b == q.face_a) {
             p->err = "interface " + std::to_string(i) + ": the faces must be opposite faces of one axis";
-            return bail(BTE_ERR_ARG);
+            return BTE_ERR_ARG;
         }
         const bte_geometry &ga = geo[q.geo_a], &gb = geo[q.geo_b];
         if (ga.bc[q.face_a] != BTE_BC_INTERFACE || gb.bc[q.face_b] != BTE_BC_INTERFACE) {
             p->err = "interface " + std::to_string(i) + ": both faces must be BTE_BC_INTERFACE";
-            return bail(BTE_ERR_ARG);
+            return BTE_ERR_ARG;
         }
         for (int a = 0; a < ga.dim; ++a) {
             const double ha = ga.len[a] / ga.n[a], hb = gb.len[a] / gb.n[a];
             const bool same_n = a == ax || ga.n[a] == gb.n[a];
             if (!same_n || std::fabs(ha - hb) > 1e-12 * std::max(ha, hb)) {
                 p->err = "interface " + std::to_string(i) + ": the faces do not match cell for cell";
-                return bail(BTE_ERR_ARG);
+                return BTE_ERR_ARG;
             }
         }
         bte_problem::IfcEnd &ea = p->ifc_end[6 * q.geo_a + q.face_a], &eb = p->ifc_end[6 * q.geo_b + q.face_b];
         if (ea.film >= 0 || eb.film >= 0) {
             p->err = "interface " + std::to_string(i) + ": a face is used twice";
-            return bail(BTE_ERR_ARG);
+            return BTE_ERR_ARG;
         }
         ea = {q.geo_b, q.face_b, i, 1};
         eb = {q.geo_a, q.face_a, i, 0};
@@ -1297,33 +1291,53 @@ bte_status bte_setup_multi(const bte_geometry *geo, int n_geo, const bte_materia
             bt[p->nl + l] = q.beta_ba[l];
             if (!(bt[l] >= 0 && bt[l] <= 1) || !(bt[p->nl + l] >= 0 && bt[p->nl + l] <= 1)) {
                 p->err = "interface " + std::to_string(i) + ": beta outside [0, 1]";
-                return bail(BTE_ERR_ARG);
+                return BTE_ERR_ARG;
             }
         }
         p->ifcs.push_back(q);
         p->ifc_beta.push_back(bt);
     }
-    if ((st = build_geometry(p, geo, n_geo)) != BTE_OK) return bail(st);
+    if ((st = build_geometry(p, geo, n_geo)) != BTE_OK) return st;
     for (int f = 0; f < n_geo; ++f) {
         Film &fm = p->films[f];
         fm.mat = geo_mat ? geo_mat[f] : 0;
         fm.moff = fm.mat * p->nl;
         fm.Ctot = p->Ctot_m[fm.mat];
     }
-    if ((st = build_quadrature(p, mat->n_theta, mat->n_phi, planar)) != BTE_OK) return bail(st);
+    if ((st = build_quadrature(p, mat->n_theta, mat->n_phi, planar)) != BTE_OK) return st;
     finish_materials(p);
     if (n_ifc > 0)
         for (int f = 0; f < n_geo; ++f)
             if (p->films[f].floating) {
                 p->err = "with interfaces every geometry needs a thermalizing wall";
-                return bail(BTE_ERR_UNSUPPORTED);
+                return BTE_ERR_UNSUPPORTED;
             }
     p->nk = p->na * p->nl;
     choose_default_tiles(p);
     build_schedule(p);
     plan_workspace(p);
-    *out = p;
     return BTE_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+bte_status bte_setup_multi(const bte_geometry *geo, int n_geo, const bte_material *mats, int n_mat,
+                           const int *geo_mat, const bte_interface *ifc, int n_ifc, const bte_control *ctl,
+                           bte_problem **out)
+{
+    if (!out) return BTE_ERR_ARG;
+    // the handle is kept on an error so that the caller can read the message
+    bte_problem *p = *out = new (std::nothrow) bte_problem();
+    if (!p) return BTE_ERR_ARG;
+    try {
+        return setup_problem(p, geo, n_geo, mats, n_mat, geo_mat, ifc, n_ifc, ctl);
+    } catch (...) {
+        p->layout.clear();
+        p->err = "out of memory";
+        return BTE_ERR_ARG;
+    }
 }
 
 bte_status bte_set_control(bte_problem *p, const bte_control *ctl)
@@ -1350,6 +1364,7 @@ int bte_num_directions(const bte_problem *p) { return p ? p->na : 0; }
 bte_status bte_bind(bte_problem *p, void *ws, size_t bytes)
 {
     if (!p) return BTE_ERR_ARG;
+    if (p->layout.empty()) FAIL(p, BTE_ERR_STATE, "setup failed");
     if (!ws || bytes < p->ws_bytes) FAIL(p, BTE_ERR_ARG, "workspace too small (%zu < %zu)", bytes, p->ws_bytes);
     if ((uintptr_t)ws & 255) FAIL(p, BTE_ERR_ARG, "workspace must be 256-byte aligned");
     p->ws = (char *)ws;

@@ -29,6 +29,7 @@
 #include <array>
 #include <atomic>
 #include <map>
+#include <new>
 #include <string>
 #include <thread>
 #include <type_traits>
@@ -1157,7 +1158,7 @@ bte_status mesh_finish(bte_mesh_problem *p, const bte_material *mat, int stencil
         nlag[al] = (int)lagged.size();
         deepest[al] = maxlev;
     });
-    if (!done_all) MFAIL(p, BTE_ERR_ARG, "mesh: out of memory");
+    if (!done_all) throw std::bad_alloc();
     p->nlag = 0;
     int maxlev = 0;
     for (int al = 0; al < p->na; ++al) {
@@ -1513,6 +1514,18 @@ bte_status mesh_solve(bte_mesh_problem *p, T *e, int init, bte_solve_stats *stat
     return BTE_OK;
 }
 
+// A set-up whose tables do not fit the memory: an error, and nothing to bind.
+template <typename F> bte_status in_memory(bte_mesh_problem *p, F &&build)
+{
+    try {
+        return build();
+    } catch (...) {
+        p->nc = 0;
+        p->err = "out of memory";
+        return BTE_ERR_ARG;
+    }
+}
+
 }  // namespace
 
 extern "C" {
@@ -1533,7 +1546,7 @@ bte_status bte_mesh_setup(const bte_mesh *mesh, const bte_material *mat, const b
     if (mat->material_dim == 2) MFAIL(p, BTE_ERR_UNSUPPORTED, "meshes take bulk materials");
     if (mat->n_bands < 1 || mat->n_bands > kBlock || !mat->C || !mat->v || !mat->tau)
         MFAIL(p, BTE_ERR_ARG, "n_bands must be 1 .. %d with C, v, tau given", kBlock);
-    return mesh_build(p, mesh, mat);
+    return in_memory(p, [&] { return mesh_build(p, mesh, mat); });
 }
 
 bte_status bte_mesh_setup_tet(const bte_tet_mesh *mesh, const bte_material *mat, const bte_control *ctl,
@@ -1552,7 +1565,7 @@ bte_status bte_mesh_setup_tet(const bte_tet_mesh *mesh, const bte_material *mat,
     if (mat->material_dim == 2) MFAIL(p, BTE_ERR_UNSUPPORTED, "meshes take bulk materials");
     if (mat->n_bands < 1 || mat->n_bands > kBlock || !mat->C || !mat->v || !mat->tau)
         MFAIL(p, BTE_ERR_ARG, "n_bands must be 1 .. %d with C, v, tau given", kBlock);
-    return mesh_build_tet(p, mesh, mat);
+    return in_memory(p, [&] { return mesh_build_tet(p, mesh, mat); });
 }
 
 size_t bte_mesh_workspace_bytes(const bte_mesh_problem *p)
