@@ -58,7 +58,7 @@ hipError_t adj_kernels_init(size_t);
 template <typename T>
 hipError_t launch_sweep2d(const Dev &, const T *, T *, const double *, const double *, const double *,
                           const Sweep2Item *, int, int, int, int, int, double *, unsigned *, hipStream_t);
-hipError_t launch_queue_reset(unsigned *, int, hipStream_t);
+hipError_t launch_queue_reset(unsigned *, int, unsigned, hipStream_t);
 template <typename T>
 hipError_t launch_transient3d(const Dev &, const T *, T *, const double *, const double *, const ColItem *, int, int,
                               int, int, double, double, double *, hipStream_t);
@@ -253,6 +253,10 @@ struct bte_problem {
     std::vector<int> cg_cell, cg_gptr, cg_gid;
     CgPlan cgplan{};
     unsigned cg_epoch = 0;                // tags used so far
+    // one-launch sweeps and CG solves that gave up waiting, and (bits 0 and 1)
+    // those that are made to (bte_internal_give_up)
+    int give_ups[2] = {0, 0};
+    unsigned force_give_up = 0;
     // diffusion operators (0: heat diffusion, 1: correction) by eigenvectors,
     // while no per-cell scattering rate is set
     struct Direct {
@@ -1666,6 +1670,9 @@ bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int
         }
         *epoch = p->cg_epoch + 1;
         p->cg_epoch += need;
+        if ((p->force_give_up & 2) &&
+            hipMemcpyAsync(p->cgplan.abortw, epoch, 4, hipMemcpyHostToDevice, s) != hipSuccess)
+            return false;
         if (launch_cg_solve(d, g, p->cgplan, p->cg_nblk, p->cg_R, b, maxit, *epoch, s) != hipSuccess) return false;
     } else {
         // one launch per iteration, enqueued in chunks; between chunks the host
@@ -1699,7 +1706,9 @@ bool run_cg_now(bte_problem *p, int corr, double *b, double *x_out, double rtol,
     if (!epoch) return true;
     if (hipMemcpyAsync(&word, p->cgplan.abortw, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return false;
     if (hipStreamSynchronize(s) != hipSuccess) return false;
-    return word != epoch || run_cg(p, corr, b, x_out, rtol, maxit, s);
+    if (word != epoch) return true;
+    ++p->give_ups[1];
+    return run_cg(p, corr, b, x_out, rtol, maxit, s);
 }
 
 // A captured launch sequence, instantiated once and replayed.
@@ -1751,7 +1760,7 @@ template <typename T> hipError_t sweep_launches(bte_problem *p, const T *ein, T 
     if (one) {
         // the whole sweep in one launch: every item waits for its upwind items
         const int n = (int)p->items2.size();
-        hipError_t r = launch_queue_reset(p->d_queue, n, q);
+        hipError_t r = launch_queue_reset(p->d_queue, n, p->force_give_up & 1, q);
         if (r == hipSuccess)
             r = launch_sweep2d<T>(d, ein, eout, p->dpend, p->TL, p->din, p->d_items2, 0, n, p->tdim.z, p->na_oct,
                                   p->nchunk_oct, p->part, p->d_queue, q);
@@ -1872,6 +1881,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
             if (p->persistent > 0) FAIL(p, BTE_ERR_HIP, "one-launch sweep: a wait for an upwind tile gave up");
             // T_L and the pending correction are still those of this iteration's start: the iteration again
             gave_up = true;
+            ++p->give_ups[0];
             st.updates -= active_cells * (double)p->nk;
             st.sweep_launches -= 1;
             --iter;
@@ -1879,6 +1889,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
         }
         if (cg_epoch && cg_abort == cg_epoch) {
             // the blocks gave up waiting for each other: this correction again, a launch per iteration
+            ++p->give_ups[1];
             if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
             launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, Report{}, s);
         }
@@ -2710,6 +2721,18 @@ bte_status bte_autotune(bte_problem *p, void *e_scratch, int reps, bte_tune_entr
     if (p->ctl.precision == BTE_F64)
         return autotune_impl<double>(p, static_cast<const double *>(e_scratch), reps, entries, cap, n, s);
     return autotune_impl<float>(p, static_cast<const float *>(e_scratch), reps, entries, cap, n, s);
+}
+
+// Not part of the interface (tests): makes the one-launch sweeps (bit 0 of what)
+// and CG solves (bit 1) from here on end as if a wait had given up, by their
+// abort words; bit 2 leaves few tags for the coming CG solves.  Reports how many
+// of either have given up so far.
+void bte_internal_give_up(bte_problem *p, int what, int *counts)
+{
+    p->force_give_up = (unsigned)what;
+    if (what & 4) p->cg_epoch = 0xffffffffu - 30u;
+    counts[0] = p->give_ups[0];
+    counts[1] = p->give_ups[1];
 }
 
 bte_status bte_set_timing(bte_problem *p, int on)

@@ -149,10 +149,10 @@ template <typename T> __device__ inline void dev_store(T *p, T v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void k_queue_reset(unsigned *q, int n)
+__global__ void k_queue_reset(unsigned *q, int n, unsigned given_up)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n + kQueueDone) q[i] = 0u;
+    if (i < n + kQueueDone) q[i] = i == kQueueAbort ? given_up : 0u;
 }
 
 }  // namespace
@@ -772,10 +772,11 @@ template hipError_t launch_sweep2d<double>(const Dev &, const double *, double *
                                            unsigned *, hipStream_t);
 
 // Zero the queue words of a one-launch sweep of n items (a kernel, not a
-// memset: the sweep launches are replayed from graphs).
-hipError_t launch_queue_reset(unsigned *queue, int n, hipStream_t s)
+// memset: the sweep launches are replayed from graphs).  given_up: the abort
+// word (1: as if a wait had given up already).
+hipError_t launch_queue_reset(unsigned *queue, int n, unsigned given_up, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_queue_reset, dim3((n + kQueueDone + 255) / 256), dim3(256), 0, s, queue, n);
+    hipLaunchKernelGGL(k_queue_reset, dim3((n + kQueueDone + 255) / 256), dim3(256), 0, s, queue, n, given_up);
     return hipGetLastError();
 }
 
