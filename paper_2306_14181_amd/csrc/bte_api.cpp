@@ -249,6 +249,7 @@ struct bte_problem {
     // one-launch CG: blocks, cells per thread (0: launches per iteration only), ghosts
     int cg_nblk = 0, cg_R = 0;
     bool cg_one = false;                  // the bound device can hold every block at once
+    bool cg_gave_up = false;              // a solve of this call gave up waiting: launches per iteration from then on
     std::vector<unsigned short> cg_lidx;
     std::vector<int> cg_cell, cg_gptr, cg_gid;
     CgPlan cgplan{};
@@ -1662,7 +1663,7 @@ bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int
         const bte_problem::Direct &q = p->direct[corr];
         if (launch_direct(p->dim, p->films[0].n, q.V, q.lam, b, x_out, p->cg_r, p->cg_z, q.zero, s) != hipSuccess)
             return false;
-    } else if (epoch && p->cg_one) {
+    } else if (epoch && p->cg_one && !p->cg_gave_up) {
         const unsigned need = (unsigned)maxit + 2u;
         if (p->cg_epoch > 0xffffffffu - need) {   // tags used up: start again on cleared words
             if (hipMemsetAsync(p->cgplan.wword, 0, 8 * cg_word_count(p->nc), s) != hipSuccess) return false;
@@ -1707,6 +1708,9 @@ bool run_cg_now(bte_problem *p, int corr, double *b, double *x_out, double rtol,
     if (hipMemcpyAsync(&word, p->cgplan.abortw, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return false;
     if (hipStreamSynchronize(s) != hipSuccess) return false;
     if (word != epoch) return true;
+    // what holds the compute units may hold them for the whole call, and each
+    // try costs the length of a wait
+    p->cg_gave_up = true;
     ++p->give_ups[1];
     return run_cg(p, corr, b, x_out, rtol, maxit, s);
 }
@@ -1790,6 +1794,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
     bte_solve_stats st{};
     T *buf[2] = {e, (T *)p->e2};
     int cur = 0;
+    p->cg_gave_up = false;
     HIPCHK(p, hipMemsetAsync(p->dpend, 0, 8 * (size_t)nc, s));
     HIPCHK(p, hipMemsetAsync(p->cg_scal, 0, 8 * 16, s));
     if (init) {
@@ -1857,7 +1862,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
         HIPCHK(p, hipGetLastError());
         unsigned cg_epoch = 0;
         if (synthetic) {
-            if (p->cg_one) {
+            if (p->cg_one && !p->cg_gave_up) {
                 if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s, &cg_epoch))
                     FAIL(p, BTE_ERR_HIP, "CG failed");
             } else if (p->graphs && p->ctl.cg_max_iter <= kCgChunk) {
@@ -1888,7 +1893,9 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
             continue;
         }
         if (cg_epoch && cg_abort == cg_epoch) {
-            // the blocks gave up waiting for each other: this correction again, a launch per iteration
+            // the blocks gave up waiting for each other: this correction again, and
+            // those to come, a launch per iteration
+            p->cg_gave_up = true;
             ++p->give_ups[1];
             if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
             launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, Report{}, s);
@@ -2081,6 +2088,7 @@ bte_status adjoint_impl(bte_problem *p, const T *e, double *grad, bte_solve_stat
     bte_solve_stats st{};
     T *buf[2] = {(T *)p->psi, (T *)p->psi2};
     int cur = 0;
+    p->cg_gave_up = false;
     // forward T and T_L deviations of e
     launch_moments<T>(d, e, nullptr, p->part, s);
     launch_finalize(d, p->part, 1, p->Tref, nullptr, nullptr, nullptr, p->adjTL, p->adjT, nullptr, s);

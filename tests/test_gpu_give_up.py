@@ -102,7 +102,7 @@ def test_cg(B, n, bc, init):
     prob, e = problem(B, geo)
     give_up(B, prob, CG)
     st = prob.steady_solve(e, init=init, allow_not_converged=True)
-    assert give_up(B, prob, 0)[1] >= 1
+    assert give_up(B, prob, 0)[1] == 1    # not tried again in the same call
     assert (e - want).abs().max() <= 1e-10 * want.abs().max()
     assert st["iters"] == rs["iters"] and st["sweep_launches"] == rs["sweep_launches"]
 
@@ -115,7 +115,7 @@ def test_cg_of_the_gradient(B):
     prob, _ = problem(B, geo, **ctl)
     give_up(B, prob, CG)
     g, st = prob.adjoint(e, allow_not_converged=True)
-    assert give_up(B, prob, 0)[1] >= 1 and give_up(B, ref, 0) == [0, 0]
+    assert give_up(B, prob, 0)[1] == 1 and give_up(B, ref, 0) == [0, 0]
     assert (g - want).abs().max() <= 1e-10 * want.abs().max()
     assert st["iters"] == rs["iters"]
 
