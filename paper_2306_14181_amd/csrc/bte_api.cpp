@@ -1697,6 +1697,20 @@ bool run_cg(bte_problem *p, int corr, double *b, double *x_out, double rtol, int
     return hipGetLastError() == hipSuccess;
 }
 
+// Takes the last solve's iterations out of the count again (a solve that is
+// repeated, or of an iteration that is).  Of a one-launch solve that gave up,
+// the block that counts may have ended with or without the others.
+bool cg_uncount(bte_problem *p, unsigned epoch, hipStream_t s)
+{
+    double sc[16];
+    if (hipMemcpyAsync(sc, p->cg_scal, sizeof sc, hipMemcpyDeviceToHost, s) != hipSuccess) return false;
+    if (hipStreamSynchronize(s) != hipSuccess) return false;
+    if (epoch && sc[14] != (double)epoch) return true;
+    sc[9] -= sc[6];
+    return hipMemcpyAsync(p->cg_scal + 9, sc + 9, 8, hipMemcpyHostToDevice, s) == hipSuccess &&
+           hipStreamSynchronize(s) == hipSuccess;
+}
+
 // run_cg to its end: one launch where there is a plan, repeated with a launch
 // per iteration if its blocks gave up waiting for each other.
 bool run_cg_now(bte_problem *p, int corr, double *b, double *x_out, double rtol, int maxit, hipStream_t s)
@@ -1712,6 +1726,7 @@ bool run_cg_now(bte_problem *p, int corr, double *b, double *x_out, double rtol,
     // try costs the length of a wait
     p->cg_gave_up = true;
     ++p->give_ups[1];
+    if (!cg_uncount(p, epoch, s)) return false;
     return run_cg(p, corr, b, x_out, rtol, maxit, s);
 }
 
@@ -1887,6 +1902,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
             // T_L and the pending correction are still those of this iteration's start: the iteration again
             gave_up = true;
             ++p->give_ups[0];
+            if (synthetic && !cg_uncount(p, cg_epoch, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
             st.updates -= active_cells * (double)p->nk;
             st.sweep_launches -= 1;
             --iter;
@@ -1897,6 +1913,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
             // those to come, a launch per iteration
             p->cg_gave_up = true;
             ++p->give_ups[1];
+            if (!cg_uncount(p, cg_epoch, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
             if (!run_cg(p, 1, p->r, p->delta, p->ctl.cg_rtol, p->ctl.cg_max_iter, s)) FAIL(p, BTE_ERR_HIP, "CG failed");
             launch_tl_update(nc, p->TLkin, p->delta, p->TL, p->dpend, d.fid, d.fdone, Report{}, s);
         }

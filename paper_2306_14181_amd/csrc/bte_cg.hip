@@ -310,6 +310,7 @@ __global__ __launch_bounds__(kCgThreads) void k_cg_solve(Dev d, CgArgs g, CgPlan
         g.scal[5] = stopped ? 1.0 : 0.0;
         g.scal[6] = it;
         g.scal[9] += it;
+        g.scal[14] = epoch;   // this solve is counted
     }
 }
 

@@ -768,7 +768,8 @@ __global__ void k_cg_coef(Dev d, CgArgs g, double *coef, double *dgo)
 // the block partials of the previous launch itself, in the same fixed order,
 // so all blocks take the same decisions.
 // scal: [1] |b|^2, [5] done, [6] iterations of this solve, [9] iterations
-// accumulated, [10 + parity] gamma, [12 + parity] alpha.
+// accumulated, [10 + parity] gamma, [12 + parity] alpha, [14] epoch of the last
+// one-launch solve that [9] holds.
 __device__ inline void part_sum3(const double *__restrict__ part, int n, double *sh, double &a, double &b, double &c)
 {
     double v[3] = {0, 0, 0};

@@ -72,7 +72,7 @@ def test_sweep(B, geos, scheme, prec, graphs):
     st = prob.steady_solve(e, init=False, allow_not_converged=True)
     assert give_up(B, prob, 0) == [1, 0]
     assert torch.equal(e, want)
-    for k in ("iters", "sweep_launches", "updates", "eps_T", "eps_q"):
+    for k in ("iters", "cg_iters", "sweep_launches", "updates", "eps_T", "eps_q"):
         assert st[k] == rs[k], k
     # the next solve waits again
     _, e = problem(B, geo, **ctl)
@@ -105,6 +105,7 @@ def test_cg(B, n, bc, init):
     assert give_up(B, prob, 0)[1] == 1    # not tried again in the same call
     assert (e - want).abs().max() <= 1e-10 * want.abs().max()
     assert st["iters"] == rs["iters"] and st["sweep_launches"] == rs["sweep_launches"]
+    assert st["cg_iters"] == rs["cg_iters"] == 5 * 12
 
 
 def test_cg_of_the_gradient(B):
@@ -118,6 +119,7 @@ def test_cg_of_the_gradient(B):
     assert give_up(B, prob, 0)[1] == 1 and give_up(B, ref, 0) == [0, 0]
     assert (g - want).abs().max() <= 1e-10 * want.abs().max()
     assert st["iters"] == rs["iters"]
+    assert st["cg_iters"] == rs["cg_iters"] > 0
 
 
 @pytest.mark.parametrize("n,bc", [((700,), [T, T]), ((70, 80), [T, T, S, D])])
