@@ -214,6 +214,7 @@ struct bte_problem {
     int nw = 0;
     // sweep schedule
     int3 tdim{1, 1, 1};      // sweep tiles
+    int edge3 = 4;           // 3D sweeps: columns of a block along x and y (choose_default_tiles)
     int3 tdim_tr{1, 1, 1};   // transient tiles
     size_t items_cap = 0, titems_cap = 0;   // work-list room for every candidate tile shape
     int tile_cap_tr = 0;
@@ -572,7 +573,11 @@ bool one_launch(const bte_problem *p)
     if (p->persistent >= 0) return p->persistent != 0;
     return p->items.size() <= 1536 * (p->diag_off.size() - 1);
 }
-int3 lds_tdim(const bte_problem *p) { return reg2d(p) ? make_int3(8, 8, 1) : p->tdim; }
+int3 lds_tdim(const bte_problem *p)
+{
+    if (p->dim == 3) return make_int3(p->edge3, p->edge3, p->tdim.z);
+    return reg2d(p) ? make_int3(8, 8, 1) : p->tdim;
+}
 
 // Tile shapes the LDS-tile kernels may use for one kind (bte_tune_kind), the
 // default shape first: at most 64 cells (the kernels keep 64-entry per-cell
@@ -607,7 +612,7 @@ std::vector<int3> tile_candidates(const bte_problem *p, int kind)
         else if (p->dim == 2) c = {make_int3(16, 4, 1), make_int3(4, 16, 1), make_int3(8, 4, 1)};   // LDS tiles
         else {
             // column segments of 1 x 1 x z cells (k_sweep3d, at most 48 cells;
-            // a block takes kS3X x kS3Y columns): shorter segments shorten each
+            // a block takes edge3 x edge3 columns): shorter segments shorten each
             // hyperplane launch, longer ones need fewer launches; lengths past
             // the tallest geometry are the same
             int nz = 1;
@@ -654,7 +659,7 @@ std::vector<int3> tile_candidates(const bte_problem *p, int kind)
 size_t count_tiles(const bte_problem *p, int3 td)
 {
     size_t n = 0;
-    if (p->dim == 3 && td.x == 1 && td.y == 1) td.x = kS3X, td.y = kS3Y;   // sweeps: a block's columns
+    if (p->dim == 3 && td.x == 1 && td.y == 1) td.x = td.y = p->edge3;   // sweeps: a block's columns
     for (const Film &fm : p->films)
         n += (size_t)((fm.n[0] + td.x - 1) / td.x) * ((fm.n[1] + td.y - 1) / td.y) * ((fm.n[2] + td.z - 1) / td.z);
     return n;
@@ -666,28 +671,45 @@ void choose_default_tiles(bte_problem *p)
     const int lanes_oct = p->na_oct * p->nl;
     const int nchunk = (lanes_oct + 63) / 64;
     p->tdim = tile_candidates(p, BTE_TUNE_SWEEP)[0];
-    // 3D segments: a hyperplane's blocks take rounds of one per compute unit,
-    // and a round its segment's cells, the 6 cells by which the last of 4 x 4
-    // columns starts late, and a start of about 8 more.  Few blocks per
-    // hyperplane favour short segments (24^3, 48 lane chunks and octants,
-    // FP64: 0.60, 0.50, 0.36 and 0.40 ms per sweep with 24, 16, 8 and 4),
-    // many long ones (48^3, 64: 3.41, 3.58, 3.75 and 4.67 ms with 48, 24, 16
-    // and 8)
+    // 3D: segment length and columns of a block by a model of the sweep: per
+    // hyperplane a launch and rounds of (segment + start of the last column)
+    // cells, a cell's time growing with the share of the chip that a round
+    // fills.  4 x 4 columns share rows and need fewer launches, and hold a compute
+    // unit alone whether the columns exist or not; 2 x 2 and single columns
+    // spread, and in FP64 they keep their values in registers (4 x 4 spill).
+    // Constants fitted to 55 shapes and band counts x 3 edges x up to 7 lengths in
+    // either precision: the choice takes 1 % longer than the best on average, 9 % at
+    // most.  ms a sweep with 4 x 4 / 2 x 2 / 1, each at its best length: FP32 1 x 1 x
+    // 300 x 20 480 lanes 1.04 / 0.55 / 0.46, 5 x 5 x 100 1.43 / 0.83 / 0.71, 10 x 10 x 200 x
+    // 1920 1.02 / 0.91 / 0.98, 32^3 0.94 / 1.07 / 1.38; FP64 24^3 0.82 / 0.75 / 0.92, 2 x
+    // 60 x 60 0.65 / 0.79 / 1.03.
     if (p->dim == 3) {
+        struct Form {
+            int edge, cap;              // columns along x and y, blocks that the chip holds
+            double cell, fill, start;   // a cell's time on an empty chip, its growth on a full one, cells of the start
+        };
+        static const Form f32[] = {{4, 256, 1.0, 0.45, 3.1}, {2, 1024, 0.91, 0.45, 3.5}, {1, 4096, 0.645, 1.22, 3.9}};
+        static const Form f64[] = {{4, 256, 1.0, 0.679, 4.64}, {2, 768, 0.697, 0.576, 2.87}, {1, 3072, 0.56, 1.454, 1.4}};
+        const double launch = p->esize() == 4 ? 2.9 : 2.05;
         double best = 0;
-        for (const int3 &t : tile_candidates(p, BTE_TUNE_SWEEP)) {
-            std::vector<double> blocks;
-            for (const Film &fm : p->films) {
-                const int a = (fm.n[0] + kS3X - 1) / kS3X, b = (fm.n[1] + kS3Y - 1) / kS3Y, c = (fm.n[2] + t.z - 1) / t.z;
-                if ((int)blocks.size() < a + b + c - 2) blocks.resize(a + b + c - 2, 0.0);
-                for (int i = 0; i < a; ++i)
-                    for (int j = 0; j < b; ++j)
-                        for (int k = 0; k < c; ++k) blocks[i + j + k] += p->noct * nchunk;
+        for (const Form &f : p->esize() == 4 ? f32 : f64)
+            for (const int3 &t : tile_candidates(p, BTE_TUNE_SWEEP)) {
+                std::vector<double> blocks;
+                for (const Film &fm : p->films) {
+                    const int a = (fm.n[0] + f.edge - 1) / f.edge, b = (fm.n[1] + f.edge - 1) / f.edge,
+                              c = (fm.n[2] + t.z - 1) / t.z;
+                    if ((int)blocks.size() < a + b + c - 2) blocks.resize(a + b + c - 2, 0.0);
+                    for (int i = 0; i < a; ++i)
+                        for (int j = 0; j < b; ++j)
+                            for (int k = 0; k < c; ++k) blocks[i + j + k] += p->noct * nchunk;
+                }
+                double cost = 0;
+                for (double n : blocks) {
+                    const double rounds = std::ceil(n / f.cap);
+                    cost += launch + rounds * (t.z + f.start) * f.cell * (1.0 + f.fill * n / (rounds * f.cap));
+                }
+                if (best == 0 || cost < best) best = cost, p->tdim = t, p->edge3 = f.edge;
             }
-            double cost = 0;
-            for (double n : blocks) cost += std::ceil(n / 256) * (t.z + 14);
-            if (best == 0 || cost < best) best = cost, p->tdim = t;
-        }
     }
     // explicit steps in 1D: a block takes every lane of its cells, so a short
     // domain needs short tiles to give the chip enough blocks; take the
@@ -720,8 +742,8 @@ void build_schedule(bte_problem *p)
     int maxd = 0;
     for (int f = 0; f < p->nfilm; ++f) {
         const Film &fm = p->films[f];
-        // 3D: tiles of kS3X x kS3Y columns
-        const int tx3 = p->dim == 3 ? kS3X : p->tdim.x, ty3 = p->dim == 3 ? kS3Y : p->tdim.y;
+        // 3D: tiles of edge3 x edge3 columns
+        const int tx3 = p->dim == 3 ? p->edge3 : p->tdim.x, ty3 = p->dim == 3 ? p->edge3 : p->tdim.y;
         const int nt[3] = {(fm.n[0] + tx3 - 1) / tx3, (fm.n[1] + ty3 - 1) / ty3,
                            (fm.n[2] + p->tdim.z - 1) / p->tdim.z};
         for (int o = 0; o < p->noct; ++o) {

@@ -82,9 +82,6 @@ struct Dev {
     const int *fdone;        // [nfilm] 1: geometry converged, its steady sweep is skipped
 };
 
-// Columns of a 3D sweep's tile along x and y (a wavefront each).
-constexpr int kS3X = 4, kS3Y = 4;
-
 // One work item of the sweep: a tile of one geometry for 64 lanes of one octant.
 struct SweepItem {
     int film, oct, chunk, tile;

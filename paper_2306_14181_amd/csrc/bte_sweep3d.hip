@@ -3,9 +3,9 @@
 // first-order upwind operator of eq. "Linear system") on three-dimensional
 // geometries, and its transpose for the adjoint.
 //
-// Work item: a tile of 4 x 4 (x, y) columns over a segment of zseg cells, for
-// 64 (direction, band) lanes of one octant; one block per item, one wavefront
-// per column.  The wavefront walks its column along z in the flow direction of
+// Work item: a tile of 4 x 4 (x, y) columns (or fewer, see below) over a
+// segment of zseg cells, for 64 (direction, band) lanes of one octant; one block
+// per item, one wavefront per column.  The wavefront walks its column along z in the flow direction of
 // the octant: the z stencil (two upwind cells, the cell, the downwind cell) is a
 // window of registers that shifts by one load per cell, the increment of the
 // z-upwind cell is the previous cell's, and the upwind recurrence of the cell
@@ -16,6 +16,13 @@
 // ones), across the tile's edge from memory: the tiles are launched by
 // hyperplanes fx + fy + fz (flow coordinates of the tile and of the segment),
 // so every upwind tile is complete when a tile starts.
+// A small cross section leaves most of 4 x 4 columns absent, with a block's
+// registers and LDS held all the same: tiles of 2 x 2 columns or of one are
+// taken where the host's model of the launches finds them faster
+// (choose_default_tiles); they are held to two wavefronts per SIMD, so that FP64
+// does not spill (1 x 1 x 300 x 20 480 lanes FP64: 1.25 ms with 4 x 4, 0.68 with
+// single columns at four wavefronts per SIMD, 0.49 at two; 5 x 5 x 100: 2.08, 1.33
+// and 1.01).
 // What bounds it: a column's step takes about 2 800 cycles with 16 wavefronts
 // per compute unit, 1 650 of them vector issue (100 instructions per cell and
 // wavefront) and the rest the step's own latency (LDS, branches, scalar work),
@@ -78,7 +85,7 @@ template <typename T> __device__ inline T rl_t(T v, int q)
 // ADD: the stencil values carry additive terms (pending correction of the
 // synthetic scheme, periodic temperature jumps); false: plain values.
 template <typename T, int LIM, bool ADJ, bool ADD, int TX, int TY>
-__global__ __launch_bounds__(64 * TX * TY) void k_sweep3d(Dev d, const T *__restrict__ ein, T *__restrict__ eout,
+__global__ __launch_bounds__(64 * TX * TY, TX * TY == 16 ? 4 : 2) void k_sweep3d(Dev d, const T *__restrict__ ein, T *__restrict__ eout,
                                                  const double *__restrict__ dpend, const double *__restrict__ TLdev,
                                                  const double *__restrict__ din, const SweepItem *__restrict__ items,
                                                  int item0, int count, int zseg, int na_oct, int nchunk_oct,
@@ -455,8 +462,8 @@ __global__ __launch_bounds__(64 * TX * TY) void k_sweep3d(Dev d, const T *__rest
             if (cj + 1 < TY) col_wait(&done[wv + TX], mloc - 7);
         }
         xs[wv][mloc & 7][lane] = (active && (mode & S3_SOLID)) ? en : (T)0;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        if (lane == 0) __hip_atomic_store(&done[wv], mloc + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (NW > 1) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (NW > 1 && lane == 0) __hip_atomic_store(&done[wv], mloc + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if ((mloc & 7) == 7 || f == fe - 1) {
             const int j = lane >> 3, p8 = lane & 7;
             double acc[NM];
@@ -525,37 +532,41 @@ __global__ __launch_bounds__(64 * TX * TY) void k_sweep3d(Dev d, const T *__rest
 
 // --------------------------------------------------------------- launchers
 
-// Segment lengths the kernel takes (the host also keeps (zseg + 2) planes
+// Tile edges and segment lengths the kernel takes (the host also keeps (zseg + 2) planes
 // of rows of every geometry below 4 GiB: the row offsets are 32-bit).
-static bool sweep3d_fits(const Dev &, int zseg, size_t) { return zseg >= 1 && zseg <= 48; }
+static bool sweep3d_fits(int edge, int zseg) { return (edge == 1 || edge == 2 || edge == 4) && zseg >= 1 && zseg <= 48; }
 
 template <typename T, int LIM, bool ADJ, bool ADD>
 void sweep3d_launch(const Dev &d, const T *ein, T *eout, const double *dpend, const double *TLdev, const double *din,
-                    const SweepItem *items, int item0, int count, int zseg, int na_oct, int nchunk_oct, double *part,
-                    hipStream_t s)
+                    const SweepItem *items, int item0, int count, int edge, int zseg, int na_oct, int nchunk_oct,
+                    double *part, hipStream_t s)
 {
     const int blocks = (count + 7) / 8 * 8;   // a multiple of the XCDs
-    hipLaunchKernelGGL((k_sweep3d<T, LIM, ADJ, ADD, kS3X, kS3Y>), dim3(blocks), dim3(64 * kS3X * kS3Y), 0, s, d, ein,
-                       eout, dpend, TLdev, din, items, item0, count, zseg, na_oct, nchunk_oct, part);
+#define BTE_EDGE(E)                                                                                                  \
+    if (edge == E)                                                                                                   \
+        hipLaunchKernelGGL((k_sweep3d<T, LIM, ADJ, ADD, E, E>), dim3(blocks), dim3(64 * E * E), 0, s, d, ein, eout,  \
+                           dpend, TLdev, din, items, item0, count, zseg, na_oct, nchunk_oct, part);
+    BTE_EDGE(1) BTE_EDGE(2) BTE_EDGE(4)
+#undef BTE_EDGE
 }
 
 // Forward sweep of the items [item0, item0 + count) (one hyperplane).
 template <typename T>
 hipError_t launch_sweep3d(const Dev &d, const T *ein, T *eout, const double *dpend, const double *TLdev,
-                          const double *din, const SweepItem *items, int item0, int count, int zseg, int na_oct,
-                          int nchunk_oct, double *part, hipStream_t s)
+                          const double *din, const SweepItem *items, int item0, int count, int edge, int zseg,
+                          int na_oct, int nchunk_oct, double *part, hipStream_t s)
 {
     if (count <= 0) return hipSuccess;
-    if (!sweep3d_fits(d, zseg, sizeof(T))) return hipErrorInvalidValue;
+    if (!sweep3d_fits(edge, zseg)) return hipErrorInvalidValue;
     const bool add = dpend != nullptr || d.jumps;
 #define BTE_S3(LIM)                                                                                                  \
     if (d.limiter == LIM) {                                                                                          \
         if (add)                                                                                                     \
-            sweep3d_launch<T, LIM, false, true>(d, ein, eout, dpend, TLdev, din, items, item0, count, zseg, na_oct,  \
-                                                nchunk_oct, part, s);                                                \
+            sweep3d_launch<T, LIM, false, true>(d, ein, eout, dpend, TLdev, din, items, item0, count, edge, zseg,     \
+                                                na_oct, nchunk_oct, part, s);                                        \
         else                                                                                                         \
-            sweep3d_launch<T, LIM, false, false>(d, ein, eout, dpend, TLdev, din, items, item0, count, zseg, na_oct, \
-                                                 nchunk_oct, part, s);                                               \
+            sweep3d_launch<T, LIM, false, false>(d, ein, eout, dpend, TLdev, din, items, item0, count, edge, zseg,    \
+                                                 na_oct, nchunk_oct, part, s);                                       \
     }
     BTE_S3(LIM_NONE) BTE_S3(LIM_MC) BTE_S3(LIM_MINMOD)
 #undef BTE_S3
@@ -565,26 +576,26 @@ hipError_t launch_sweep3d(const Dev &d, const T *ein, T *eout, const double *dpe
 // Transposed sweep of the adjoint iteration (X: isotropic closure term).
 template <typename T>
 hipError_t launch_sweep3d_adj(const Dev &d, const T *ein, T *eout, const double *X, const double *dinA,
-                              const SweepItem *items, int item0, int count, int zseg, int na_oct, int nchunk_oct,
-                              double *part, hipStream_t s)
+                              const SweepItem *items, int item0, int count, int edge, int zseg, int na_oct,
+                              int nchunk_oct, double *part, hipStream_t s)
 {
     if (count <= 0) return hipSuccess;
-    if (!sweep3d_fits(d, zseg, sizeof(T))) return hipErrorInvalidValue;
-    sweep3d_launch<T, LIM_NONE, true, false>(d, ein, eout, nullptr, X, dinA, items, item0, count, zseg, na_oct,
-                                             nchunk_oct, part, s);
+    if (!sweep3d_fits(edge, zseg)) return hipErrorInvalidValue;
+    sweep3d_launch<T, LIM_NONE, true, false>(d, ein, eout, nullptr, X, dinA, items, item0, count, edge, zseg,
+                                             na_oct, nchunk_oct, part, s);
     return hipGetLastError();
 }
 
 template hipError_t launch_sweep3d<float>(const Dev &, const float *, float *, const double *, const double *,
-                                          const double *, const SweepItem *, int, int, int, int, int, double *,
+                                          const double *, const SweepItem *, int, int, int, int, int, int, double *,
                                           hipStream_t);
 template hipError_t launch_sweep3d<double>(const Dev &, const double *, double *, const double *, const double *,
-                                           const double *, const SweepItem *, int, int, int, int, int, double *,
+                                           const double *, const SweepItem *, int, int, int, int, int, int, double *,
                                            hipStream_t);
 template hipError_t launch_sweep3d_adj<float>(const Dev &, const float *, float *, const double *, const double *,
-                                              const SweepItem *, int, int, int, int, int, double *, hipStream_t);
+                                              const SweepItem *, int, int, int, int, int, int, double *, hipStream_t);
 template hipError_t launch_sweep3d_adj<double>(const Dev &, const double *, double *, const double *,
-                                               const double *, const SweepItem *, int, int, int, int, int, double *,
+                                               const double *, const SweepItem *, int, int, int, int, int, int, double *,
                                                hipStream_t);
 
 }  // namespace bte

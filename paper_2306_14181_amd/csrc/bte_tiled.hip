@@ -338,15 +338,15 @@ __global__ __launch_bounds__(256) void k_transient_tile(Dev d, const T *__restri
 // --------------------------------------------------------------- launchers
 
 // three-dimensional sweeps walk column segments (bte_sweep3d.hip); a
-// segment item is a tile of 1 x 1 x tdim.z cells
+// segment item is a tile of tdim.x x tdim.x x tdim.z cells
 template <typename T>
 hipError_t launch_sweep3d(const Dev &d, const T *ein, T *eout, const double *dpend, const double *TLdev,
-                          const double *din, const SweepItem *items, int item0, int count, int zseg, int na_oct,
-                          int nchunk_oct, double *part, hipStream_t s);
+                          const double *din, const SweepItem *items, int item0, int count, int edge, int zseg,
+                          int na_oct, int nchunk_oct, double *part, hipStream_t s);
 template <typename T>
 hipError_t launch_sweep3d_adj(const Dev &d, const T *ein, T *eout, const double *X, const double *dinA,
-                              const SweepItem *items, int item0, int count, int zseg, int na_oct, int nchunk_oct,
-                              double *part, hipStream_t s);
+                              const SweepItem *items, int item0, int count, int edge, int zseg, int na_oct,
+                              int nchunk_oct, double *part, hipStream_t s);
 
 template <typename T, int DIM, int LIM>
 void sweep_launch(const Dev &d, const T *ein, T *eout, const double *dpend, const double *TLdev, const double *din,
@@ -365,8 +365,8 @@ hipError_t launch_sweep_tile(const Dev &d, const T *ein, T *eout, const double *
 {
     if (count <= 0) return hipSuccess;
     if (d.dim == 3)
-        return launch_sweep3d<T>(d, ein, eout, dpend, TLdev, din, items, item0, count, tdim.z, na_oct, nchunk_oct,
-                                 part, s);
+        return launch_sweep3d<T>(d, ein, eout, dpend, TLdev, din, items, item0, count, tdim.x, tdim.z, na_oct,
+                                 nchunk_oct, part, s);
 #define BTE_SWEEP(DIM, LIM)                                                                                          \
     if (d.dim == DIM && d.limiter == LIM)                                                                            \
         sweep_launch<T, DIM, LIM>(d, ein, eout, dpend, TLdev, din, items, item0, count, tdim, na_oct, nchunk_oct,    \
@@ -395,7 +395,8 @@ hipError_t launch_sweep_adj(const Dev &d, const T *ein, T *eout, const double *X
     if (d.dim == 1) sweep_adj_launch<T, 1>(d, ein, eout, X, dinA, items, item0, count, tdim, na_oct, nchunk_oct, cap, part, s);
     if (d.dim == 2) sweep_adj_launch<T, 2>(d, ein, eout, X, dinA, items, item0, count, tdim, na_oct, nchunk_oct, cap, part, s);
     if (d.dim == 3)
-        return launch_sweep3d_adj<T>(d, ein, eout, X, dinA, items, item0, count, tdim.z, na_oct, nchunk_oct, part, s);
+        return launch_sweep3d_adj<T>(d, ein, eout, X, dinA, items, item0, count, tdim.x, tdim.z, na_oct, nchunk_oct, part,
+                                     s);
     return hipGetLastError();
 }
 
