@@ -225,6 +225,8 @@ struct bte_problem {
     std::vector<TileItem> titems;   // transient: (geometry, octant, tile)
     std::vector<ColItem> citems;    // three-dimensional transient: (geometry, octant, chunk, column)
     std::vector<ColItem> qitems;    // the same by 2 x 2 columns (forward step; empty: column by column)
+    double quad_walls = 0;          // x and y axes off the interior stencil, per four cells of a step by 2 x 2
+    int quad_force = -1;            // 0, 1: column by column, by 2 x 2 (bte_internal_quads); -1: quad_step's rule
     int tile_cap = 0;               // star slots of a full tile
     int floating_any = 0, thermal_any = 0;
     // workspace
@@ -791,13 +793,14 @@ void build_schedule(bte_problem *p)
                             for (int x = x0; x < std::min(x0 + kColStrip, fm.n[0]); ++x)
                                 p->citems.push_back({f, o, ch, x + fm.n[0] * y});
         }
-    // 2 x 2 columns for the forward step, where every geometry has them, a
-    // plane's rows lie within 31-bit byte offsets and they still fill the
-    // chip's 4096 resident wavefronts once.  us a step, one column / 2 x 2, MC
-    // limiter, FP32 unless noted, by wavefronts of 2 x 2: 16^3 x 320 (512) 27 /
-    // 51, 20 x 20 x 200 x 1280 (2400) 561 / 626, 24^3 x 1280 (3456) 98 / 95, 32^3
-    // x 5120 (20 480) 605 / 493, FP64 32^3 x 2560 (10 240) 579 / 550, 64^3 x 5120
-    // (81 920) 4602 / 3538
+    // 2 x 2 columns for the forward step (quad_step chooses), where every
+    // geometry has them, a plane's rows lie within 31-bit byte offsets and they
+    // still fill the chip's 4096 (FP64: 2048) resident wavefronts; FP32 takes them
+    // from 5120, with a second round worth its start.  us a step, one column / 2 x 2, MC limiter, FP32 unless noted, by
+    // wavefronts of 2 x 2: 16^3 x 320 (512) 27 / 51, 20 x 20 x 200 x 1280 (2400) 561 /
+    // 626, 22 x 22 x 60 x 2560 (4840) 304 / 314, 23^3 x 2560 (5760) 140 / 136, 32^3 x
+    // 5120 (20 480) 605 / 493, 64^3 x 5120 (81 920) 4602 / 3538; FP64 unlimited 22 x 22
+    // x 60 x 2560 567 / 526
     p->qitems.clear();
     bool quads = p->dim == 3;
     size_t nq = 0;
@@ -889,6 +892,52 @@ void build_schedule(bte_problem *p)
             if (q.upx >= (int)i || q.upy >= (int)i) p->queue_ok = false;
         }
     }
+}
+
+// Steps by 2 x 2 columns take an axis along straight-line code only where all four
+// cells have its interior stencil, and its loads again where one has not, so walls
+// and pores decide.  us a step, one column / 2 x 2, by the axes (of x and y) per
+// four cells that are off it; FP32 unlimited (limited alike): 32^3 periodic (0) 286 /
+// 222, 2 % pores (0.57) 383 / 350, 24^3 2 % (0.65) 187 / 185, pores of 4^3 (0.75) 201 /
+// 204, 28^3 (0.78) 292 / 313, 10 % (1.41) 354 / 382; FP64 unlimited 32^3 10 % (1.36) 743 /
+// 727, 12 x 12 x 100 (1.55) 1277 / 1304; FP64 limited, where its registers do not hold
+// four cells: 64 x 64 x 8 (0.13) 661 / 604, 28^3 (0.29) 398 / 391, 24^3 (0.33) 260 / 267,
+// 16^3 (0.5) 216 / 231, 32^3 10 % 708 / 832.
+bool quad_step(const bte_problem *p)
+{
+    if (p->qitems.empty()) return false;
+    if (p->quad_force >= 0) return p->quad_force != 0;
+    if (p->esize() == 4 && p->qitems.size() < 5120) return false;
+    return p->quad_walls <= (p->esize() == 4 ? 0.7 : p->ctl.limiter == BTE_LIM_NONE ? 1.35 : 0.28);
+}
+
+// p->quad_walls, of the two octants whose signs are all equal (the others are
+// their mirror images along an axis)
+void count_quad_walls(bte_problem *p)
+{
+    double off = 0, all = 0;
+    for (const Film &fm : p->films)
+        for (int sg = -1; sg <= 1; sg += 2)
+            for (int z = 0; z < fm.n[2]; ++z)
+                for (int y = 0; y < fm.n[1]; y += 2)
+                    for (int x = 0; x < fm.n[0]; x += 2) {
+                        bool in[2] = {true, true}, solid = true;
+                        for (int q = 0; q < 4; ++q) {
+                            const int cx = std::min(x, fm.n[0] - 2) + (q & 1), cy = std::min(y, fm.n[1] - 2) + (q >> 1);
+                            const int c = fm.cell0 + cx + fm.n[0] * (cy + fm.n[1] * z);
+                            solid = solid && (p->code[c] & kSolidBit);
+                            for (int a = 0; a < 2; ++a) {
+                                const uint32_t ab = axis_bits(p->code[c], a);
+                                const bool hu = side_is_cell(ab, -sg);
+                                const int u = hu ? p->nb[(size_t)face_of(a, -sg) * p->nc + c] : -1;
+                                in[a] = in[a] && hu && side_is_cell(ab, sg) && u >= 0 &&
+                                        side_is_cell(axis_bits(p->code[u], a), -sg);
+                            }
+                        }
+                        off += solid ? !in[0] + !in[1] : 2;
+                        all += 1;
+                    }
+    p->quad_walls = off / all;
 }
 
 // Per geometry: the wall emission conductance of the correction operator
@@ -1342,6 +1391,7 @@ bte_status setup_problem(bte_problem *p, const bte_geometry *geo, int n_geo, con
     p->nk = p->na * p->nl;
     choose_default_tiles(p);
     build_schedule(p);
+    if (!p->qitems.empty()) count_quad_walls(p);
     plan_workspace(p);
     return BTE_OK;
 }
@@ -2051,7 +2101,7 @@ hipError_t one_step(bte_problem *p, const T *ein, T *eout, double src, hipEvent_
         r = launch_transient1d<T>(d, ein, eout, p->TL, p->TL, p->din, p->d_titems, (int)p->titems.size() / p->noct,
                                   p->tdim_tr.x, src, p->ctl.dt, s);
     } else if (p->dim == 3) {
-        const bool quad = !p->qitems.empty();
+        const bool quad = quad_step(p);
         r = launch_transient3d<T>(d, ein, eout, p->TL, p->din, quad ? p->d_qitems : p->d_citems,
                                   (int)(quad ? p->qitems : p->citems).size(), quad, p->na_oct, p->nchunk_oct, src,
                                   p->ctl.dt, p->part, s);
@@ -2780,6 +2830,15 @@ void bte_internal_give_up(bte_problem *p, int what, int *counts)
     if (what & 4) p->cg_epoch = 0xffffffffu - 30u;
     counts[0] = p->give_ups[0];
     counts[1] = p->give_ups[1];
+}
+
+// Not part of the interface (tests): 3D explicit steps column by column (0), by 2 x
+// 2 columns (1, where the problem has them), by quad_step's rule (-1).  Returns
+// the form that the steps take then.
+int bte_internal_quads(bte_problem *p, int on)
+{
+    p->quad_force = on;
+    return quad_step(p);
 }
 
 bte_status bte_set_timing(bte_problem *p, int on)
