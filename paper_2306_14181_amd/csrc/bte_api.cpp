@@ -33,7 +33,7 @@ hipError_t launch_sweep_tile(const Dev &, const T *, T *, const double *, const 
 template <typename T>
 hipError_t launch_transient_tile(const Dev &, const T *, T *, const double *, const double *, const TileItem *, int,
                                  int3, int, int, int, double, double, double *, hipStream_t);
-int line_parts(int lanes_oct);
+int line_parts(int lanes_oct, int nfilm, int max_n, size_t nc);
 template <typename T>
 hipError_t launch_sweep1d(const Dev &, const T *, T *, const double *, const double *, const double *, int, int,
                           double *, hipStream_t);
@@ -1142,6 +1142,14 @@ bool direct_use(const bte_problem *p, int corr, double rtol, int maxit)
     return maxit >= std::min((double)p->nc, cg_bound(p->direct[corr], rtol));
 }
 
+// cells of the longest line of a 1D problem
+int longest(const bte_problem *p)
+{
+    int n = 1;
+    for (const Film &fm : p->films) n = std::max(n, fm.n[0]);
+    return n;
+}
+
 void plan_workspace(bte_problem *p)
 {
     build_cg_plan(p);
@@ -1209,7 +1217,7 @@ void plan_workspace(bte_problem *p)
     add("din", 8 * (size_t)p->nw * p->nl);
     const int nchunk_stream = (p->nk + kBlock - 1) / kBlock;
     p->npart_max = std::max(nchunk_stream, p->noct * p->nchunk_oct);
-    if (p->dim == 1) p->npart_max = std::max(p->npart_max, line_parts(p->na_oct * p->nl));
+    if (p->dim == 1) p->npart_max = std::max(p->npart_max, line_parts(p->na_oct * p->nl, p->nfilm, longest(p), nc));
     add("part", 8 * (size_t)kMomN * nc * p->npart_max);
     add("e2", p->esize() * p->nelem());
     add("zrow", 8 * 8 * (size_t)p->nk);   // 8 cells of zeros (a missing row of a tile)
@@ -1842,9 +1850,7 @@ template <typename T> hipError_t sweep_launches(bte_problem *p, const T *ein, T 
 {
     const Dev &d = p->dev;
     if (p->dim == 1) {
-        int max_n = 1;
-        for (const Film &fm : p->films) max_n = std::max(max_n, fm.n[0]);
-        return launch_sweep1d<T>(d, ein, eout, p->dpend, p->TL, p->din, p->na_oct, max_n, p->part, q);
+        return launch_sweep1d<T>(d, ein, eout, p->dpend, p->TL, p->din, p->na_oct, longest(p), p->part, q);
     }
     const bool reg = reg2d(p);
     const int3 lt = lds_tdim(p);
@@ -1901,7 +1907,7 @@ bte_status steady_impl(bte_problem *p, T *e, int init, bte_solve_stats *stats, h
     std::vector<int> fdone(p->nfilm, 0);
     int ndone = 0;
     int *fdone_dev = const_cast<int *>(d.fdone);
-    const int np = p->dim == 1 ? line_parts(p->na_oct * p->nl) : p->noct * p->nchunk_oct;
+    const int np = p->dim == 1 ? line_parts(p->na_oct * p->nl, p->nfilm, longest(p), nc) : p->noct * p->nchunk_oct;
     bte_status ret = BTE_ERR_NOT_CONVERGED;
     // phase timers: events on the solve stream, read after the per-iteration sync
     hipEvent_t ev[5];

@@ -19,6 +19,7 @@ namespace {
 constexpr int kSeg = 4;          // cells of a thread
 constexpr int LW = 16;           // lanes of a sweep's block
 constexpr int kLineThreads = 1024;
+constexpr int kFold = 4;         // groups of lanes of a folded block
 constexpr int kStepThreads = 512;
 constexpr int kStepCells = 64;   // most cells of an explicit step's block
 
@@ -88,123 +89,128 @@ template <typename T> __device__ inline T inflow(T a, T x) { return a * (a != (T
 // one line of 200 cells x 80 lanes, of 1000 x 1280, of 256 lines of 200 x 80:
 // 152, 578 and 576 us with a launch per tile of 64 cells x 64 lanes, 20, 43
 // and 98 us here (38, 127 and 132 us with 64 lanes a block: a quarter of the
-// wavefronts on a line).
-template <typename T, int LIM>
+// wavefronts on a line).  FOLD: a block takes four groups of lanes one after
+// another and adds their moments (line_fold).
+template <typename T, int LIM, bool FOLD>
 __global__ __launch_bounds__(kLineThreads) void k_sweep1d(Dev d, const T *__restrict__ ein, T *__restrict__ eout,
                                                           const double *__restrict__ dpend,
                                                           const double *__restrict__ TLdev,
-                                                          const double *__restrict__ din, int na_oct, int ngrp,
+                                                          const double *__restrict__ din, int na_oct, int nparts,
                                                           double *__restrict__ part)
 {
     constexpr int NS = 64 / LW, kCells = kLineThreads / LW * kSeg;
     __shared__ LineCell tab[kCells + 3];                  // flow positions f0 - 2 .. f0 + round
     __shared__ double tl[kCells], gam[kCells], qs[kCells];
     __shared__ T totA[kLineThreads / 64][LW], totB[kLineThreads / 64][LW];
-    const int film = blockIdx.x / (2 * ngrp), oct = (int)(blockIdx.x / ngrp) & 1, grp = blockIdx.x % ngrp;
+    const int film = blockIdx.x / (2 * nparts), oct = (int)(blockIdx.x / nparts) & 1, gpart = blockIdx.x % nparts;
     if (d.nfilm > 1 && d.fdone[film]) return;             // converged geometry of a batch (uniform)
     const Film &fm = d.film[film];
     const int n = fm.n[0];
     const int wave = threadIdx.x >> 6, nwave = blockDim.x >> 6, lane = threadIdx.x & 63;
     const int sub = lane / LW, kl = lane % LW;
     const int kbeg = oct * na_oct * d.nl, kend = kbeg + na_oct * d.nl;
-    const int k = kbeg + grp * LW + kl;
-    const bool active = k < kend;
-    const int kk = active ? k : kbeg;
-    const LaneT<T> L = lane_make<T>(d, fm, kk);
     const int sg = octant_sign(d, oct, na_oct, 0);
     const int q0 = (wave * NS + sub) * kSeg, round = nwave * NS * kSeg;
     const T *zrow = static_cast<const T *>(d.zrow);
-    const int pidx = oct * ngrp + grp;
-    T carry = (T)0;
-    for (int f0 = 0; f0 < n; f0 += round) {
-        for (int q = threadIdx.x; q < round + 3; q += blockDim.x) {
-            const int f = f0 + q - 2;
-            LineCell t{-1, 0u, 0.0};
-            if (f <= n) t = line_cell(d, fm, sg > 0 ? f : n - 1 - f, dpend);
-            tab[q] = t;
-            if (q >= 2 && q < round + 2 && f < n) {
-                tl[q - 2] = TLdev[t.cell];
-                gam[q - 2] = d.gamma[t.cell];
-                qs[q - 2] = d.P ? d.P[t.cell] / fm.Ctot : 0.0;
+    const int pidx = oct * nparts + gpart;
+    for (int grp = 0; grp < (FOLD ? kFold : 1); ++grp) {
+        const int k0 = kbeg + (gpart * (FOLD ? kFold : 1) + grp) * LW, k = k0 + kl;
+        if (FOLD && k0 >= kend) break;
+        const bool active = k < kend;
+        const int kk = active ? k : kbeg;
+        const LaneT<T> L = lane_make<T>(d, fm, kk);
+        T carry = (T)0;
+        for (int f0 = 0; f0 < n; f0 += round) {
+            for (int q = threadIdx.x; q < round + 3; q += blockDim.x) {
+                const int f = f0 + q - 2;
+                LineCell t{-1, 0u, 0.0};
+                if (f <= n) t = line_cell(d, fm, sg > 0 ? f : n - 1 - f, dpend);
+                tab[q] = t;
+                if (q >= 2 && q < round + 2 && f < n) {
+                    tl[q - 2] = TLdev[t.cell];
+                    gam[q - 2] = d.gamma[t.cell];
+                    qs[q - 2] = d.P ? d.P[t.cell] / fm.Ctot : 0.0;
+                }
             }
-        }
-        __syncthreads();
-        T v[kSeg + 3], b[kSeg], g[kSeg];
-#pragma unroll
-        for (int j = 0; j < kSeg + 3; ++j) {
-            const int c = tab[q0 + j].cell;
-            const T *row = c >= 0 ? ein + (size_t)c * d.nk : zrow;
-            v[j] = row[kk];
-        }
-#pragma unroll
-        for (int j = 0; j < kSeg + 3; ++j) v[j] += L.C4 * (T)tab[q0 + j].x;
-        // increments without inflow into the segment, and the factor of an inflow
-        T de = (T)0, pass = (T)1;
-#pragma unroll
-        for (int j = 0; j < kSeg; ++j) {
-            const LineCell me = tab[q0 + j + 2];
-            b[j] = (T)0;
-            g[j] = (T)0;
-            if (f0 + q0 + j < n && (me.code & kSolidBit)) {
-                const T ec = v[j + 2];
-                const uint32_t ab = axis_bits(me.code, 0);
-                const T D = L.cpl[0] * line_delta<T, LIM>(d, fm, ein, din, me, tab[q0 + j].code, tab[q0 + j + 3], sg, L,
-                                                          v[j], v[j + 1], ec, v[j + 3]);
-                const T ga = (T)gam[q0 + j], itc = L.itau + ga;
-                const T rhs = -D - (ec - L.C4 * (T)tl[q0 + j]) * itc + L.C4 * (T)qs[q0 + j];
-                // a wall, a pore or a periodic face (lagged) upwind: no coupling
-                const T cp = side_is_cell(ab, -sg) && !side_wraps(ab, -sg) ? L.cpl[0] : (T)0;
-                const T den = L.cpl[0] + L.itau + ga, inv = recip(den);
-                b[j] = quot(rhs + cp * de, den, inv);
-                g[j] = quot(cp * pass, den, inv);
+            __syncthreads();
+            T v[kSeg + 3], b[kSeg], g[kSeg];
+    #pragma unroll
+            for (int j = 0; j < kSeg + 3; ++j) {
+                const int c = tab[q0 + j].cell;
+                const T *row = c >= 0 ? ein + (size_t)c * d.nk : zrow;
+                v[j] = row[kk];
             }
-            de = b[j];
-            pass = g[j];
-        }
-        // join: runs of the wavefront, then wavefronts
-        T A = pass, Bv = de;
-#pragma unroll
-        for (int o = LW; o < 64; o *= 2) {
-            const T Ap = __shfl_up(A, o, 64), Bp = __shfl_up(Bv, o, 64);
-            if (lane >= o) {
-                Bv += inflow(A, Bp);
-                A *= Ap;
+    #pragma unroll
+            for (int j = 0; j < kSeg + 3; ++j) v[j] += L.C4 * (T)tab[q0 + j].x;
+            // increments without inflow into the segment, and the factor of an inflow
+            T de = (T)0, pass = (T)1;
+    #pragma unroll
+            for (int j = 0; j < kSeg; ++j) {
+                const LineCell me = tab[q0 + j + 2];
+                b[j] = (T)0;
+                g[j] = (T)0;
+                if (f0 + q0 + j < n && (me.code & kSolidBit)) {
+                    const T ec = v[j + 2];
+                    const uint32_t ab = axis_bits(me.code, 0);
+                    const T D = L.cpl[0] * line_delta<T, LIM>(d, fm, ein, din, me, tab[q0 + j].code, tab[q0 + j + 3], sg,
+                                                              L, v[j], v[j + 1], ec, v[j + 3]);
+                    const T ga = (T)gam[q0 + j], itc = L.itau + ga;
+                    const T rhs = -D - (ec - L.C4 * (T)tl[q0 + j]) * itc + L.C4 * (T)qs[q0 + j];
+                    // a wall, a pore or a periodic face (lagged) upwind: no coupling
+                    const T cp = side_is_cell(ab, -sg) && !side_wraps(ab, -sg) ? L.cpl[0] : (T)0;
+                    const T den = L.cpl[0] + L.itau + ga, inv = recip(den);
+                    b[j] = quot(rhs + cp * de, den, inv);
+                    g[j] = quot(cp * pass, den, inv);
+                }
+                de = b[j];
+                pass = g[j];
             }
-        }
-        if (sub == NS - 1) {
-            totA[wave][kl] = A;
-            totB[wave][kl] = Bv;
-        }
-        T exA = (T)1, exB = (T)0;
-        const T Ap = __shfl_up(A, LW, 64), Bp = __shfl_up(Bv, LW, 64);
-        if (sub > 0) exA = Ap, exB = Bp;
-        __syncthreads();
-        T in = carry;
-        for (int w = 0; w < nwave; ++w) {
-            const T next = totB[w][kl] + inflow(totA[w][kl], carry);
-            if (w == wave) in = carry;
-            carry = next;
-        }
-        in = exB + inflow(exA, in);
-#pragma unroll
-        for (int j = 0; j < kSeg; ++j) {
-            if (f0 + q0 + j >= n) break;
-            const LineCell me = tab[q0 + j + 2];
-            const bool solid = me.code & kSolidBit;
-            const T en = solid ? v[j + 2] + (b[j] + inflow(g[j], in)) : v[j + 2];
-            if (active) eout[(size_t)me.cell * d.nk + k] = en;
-            const double x = solid && active ? (double)en : 0.0;
-            const double m0 = row_sum(L.w * x), m1 = row_sum(L.witau * x), m2 = row_sum(L.wv[0] * x);
-            if (kl == 0) {
-                double *o = part + ((size_t)pidx * d.nc + me.cell) * kMomN;
-                o[0] = m0;
-                o[1] = m1 + gam[q0 + j] * m0;
-                o[2] = m2;
-                o[3] = 0.0;   // no direction of a line has components off it
-                o[4] = 0.0;
+            // join: runs of the wavefront, then wavefronts
+            T A = pass, Bv = de;
+    #pragma unroll
+            for (int o = LW; o < 64; o *= 2) {
+                const T Ap = __shfl_up(A, o, 64), Bp = __shfl_up(Bv, o, 64);
+                if (lane >= o) {
+                    Bv += inflow(A, Bp);
+                    A *= Ap;
+                }
             }
+            if (sub == NS - 1) {
+                totA[wave][kl] = A;
+                totB[wave][kl] = Bv;
+            }
+            T exA = (T)1, exB = (T)0;
+            const T Ap = __shfl_up(A, LW, 64), Bp = __shfl_up(Bv, LW, 64);
+            if (sub > 0) exA = Ap, exB = Bp;
+            __syncthreads();
+            T in = carry;
+            for (int w = 0; w < nwave; ++w) {
+                const T next = totB[w][kl] + inflow(totA[w][kl], carry);
+                if (w == wave) in = carry;
+                carry = next;
+            }
+            in = exB + inflow(exA, in);
+    #pragma unroll
+            for (int j = 0; j < kSeg; ++j) {
+                if (f0 + q0 + j >= n) break;
+                const LineCell me = tab[q0 + j + 2];
+                const bool solid = me.code & kSolidBit;
+                const T en = solid ? v[j + 2] + (b[j] + inflow(g[j], in)) : v[j + 2];
+                if (active) eout[(size_t)me.cell * d.nk + k] = en;
+                const double x = solid && active ? (double)en : 0.0;
+                const double m0 = row_sum(L.w * x), m1 = row_sum(L.witau * x), m2 = row_sum(L.wv[0] * x);
+                if (kl == 0) {
+                    double *o = part + ((size_t)pidx * d.nc + me.cell) * kMomN;
+                    double s[3] = {m0, m1 + gam[q0 + j] * m0, m2};
+                    if (FOLD && grp > 0)   // the same thread's, of the groups before
+                        for (int m = 0; m < 3; ++m) s[m] += o[m];
+                    for (int m = 0; m < 3; ++m) o[m] = s[m];
+                    o[3] = 0.0;   // no direction of a line has components off it
+                    o[4] = 0.0;
+                }
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -299,20 +305,50 @@ __global__ __launch_bounds__(kStepThreads) void k_transient1d(Dev d, const T *__
     }
 }
 
-template <typename T, int LIM>
-void sweep1d_launch(const Dev &d, const T *ein, T *eout, const double *dpend, const double *TLdev, const double *din,
-                    int na_oct, int max_n, double *part, hipStream_t s)
+int line_groups(int lanes_oct) { return (lanes_oct + LW - 1) / LW; }
+int line_waves(int max_n)
 {
-    const int grp = (na_oct * d.nl + LW - 1) / LW, per_wave = 64 / LW * kSeg;
-    const int waves = std::min(kLineThreads / 64, (max_n + per_wave - 1) / per_wave);
-    hipLaunchKernelGGL((k_sweep1d<T, LIM>), dim3((unsigned)d.nfilm * 2 * grp), dim3(64 * waves), 0, s, d, ein, eout,
-                       dpend, TLdev, din, na_oct, grp, part);
+    const int per_wave = 64 / LW * kSeg;
+    return std::min(kLineThreads / 64, (max_n + per_wave - 1) / per_wave);
+}
+
+// Whether blocks are folded, which leaves a quarter of the moment partials (0.6
+// bytes a value instead of 2.5): where the partials pass 256 MiB and the
+// wavefronts still fill the chip's 4096 places.  20 lines of 2000 cells x 1280 lanes
+// FP32: sweep 0.385 -> 0.477 ms, the sums over the partials 0.039 -> 0.021; 200 cells x
+// 51 200: 0.094 -> 0.120 and 0.079 -> 0.028.
+bool line_fold(int lanes_oct, int nfilm, int max_n, size_t nc)
+{
+    return 2.0 * nfilm * line_groups(lanes_oct) * line_waves(max_n) >= 4096.0 * kFold &&
+           8 * kMomN * nc * 2 * line_groups(lanes_oct) >= size_t(256) << 20;
 }
 
 }  // namespace
 
-// moment partials per cell of a sweep
-int line_parts(int lanes_oct) { return 2 * ((lanes_oct + LW - 1) / LW); }
+// moment partials per cell of a sweep (lines of up to max_n cells)
+int line_parts(int lanes_oct, int nfilm, int max_n, size_t nc)
+{
+    const int fold = line_fold(lanes_oct, nfilm, max_n, nc) ? kFold : 1;
+    return 2 * ((line_groups(lanes_oct) + fold - 1) / fold);
+}
+
+namespace {
+
+template <typename T, int LIM>
+void sweep1d_launch(const Dev &d, const T *ein, T *eout, const double *dpend, const double *TLdev, const double *din,
+                    int na_oct, int max_n, double *part, hipStream_t s)
+{
+    const int parts = line_parts(na_oct * d.nl, d.nfilm, max_n, d.nc) / 2;
+    const dim3 grid((unsigned)d.nfilm * 2 * parts), block(64 * line_waves(max_n));
+    if (line_fold(na_oct * d.nl, d.nfilm, max_n, d.nc))
+        hipLaunchKernelGGL((k_sweep1d<T, LIM, true>), grid, block, 0, s, d, ein, eout, dpend, TLdev, din, na_oct, parts,
+                           part);
+    else
+        hipLaunchKernelGGL((k_sweep1d<T, LIM, false>), grid, block, 0, s, d, ein, eout, dpend, TLdev, din, na_oct, parts,
+                           part);
+}
+
+}  // namespace
 
 template <typename T>
 hipError_t launch_sweep1d(const Dev &d, const T *ein, T *eout, const double *dpend, const double *TLdev,
