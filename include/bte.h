@@ -259,9 +259,10 @@ bte_status bte_transient_step(bte_problem *p, void *e_dev, int n_steps, double t
 
 /* Steady solve (Algorithm 1), in place on e.  init != 0 starts from the
  * heat-diffusion solution (Sec. 3.5, eq. diff), else from e.  The diffusion
- * problems are solved by CG, or, for one geometry without pores, interfaces
- * and scattering rates (gamma NULL) whose CG could not reach its cap before
- * its tolerance, directly by the operator's eigenvectors.  Synchronous
+ * problems are solved by CG, or, for one geometry of up to 512 cells per axis
+ * without pores, interfaces and scattering rates (gamma NULL) whose CG could
+ * not reach its cap before its tolerance (below one), directly by the
+ * operator's eigenvectors.  Synchronous
  * (reads one convergence flag per iteration).  Returns BTE_ERR_NOT_CONVERGED
  * with the last iterate if max_iter is reached.  stats may be NULL. */
 bte_status bte_steady_solve(bte_problem *p, void *e_dev, int init, bte_solve_stats *stats,

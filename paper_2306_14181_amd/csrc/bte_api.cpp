@@ -563,12 +563,16 @@ bool reg2d(const bte_problem *p) { return p->dim == 2 && p->tdim.x == 8 && p->td
 // 2D sweeps in one launch: as the caller chose, else where the tile diagonals
 // are short.  A launch per diagonal costs its start and its last, part-empty
 // round each time; one launch costs each block its ticket and its wait for the
-// upwind tiles, and wins while a diagonal fills the chip's 1024 resident blocks
-// at most about once.  ms per sweep, launch per diagonal / one launch, FP32
-// unless noted, by items per diagonal: 97 x 83 FP64 (50) 0.343 / 0.142; squares
-// of 64 (171) 0.211 / 0.130, 256 (650) 1.129 / 0.668, 512 (1290) 3.18 / 2.37;
-// batches of 24 films of 30 to 200 cells a side (1300) 2.19 / 2.19, of 96 (5000)
-// 7.22 / 8.51, of 200 films of 16 to 40 (3200) 1.10 / 1.23.
+// upwind tiles, and wins while a diagonal is a few rounds of the chip's resident
+// blocks (1024, in FP64 512).  The two precisions meet at about the same number of
+// items: in FP64 a launch per diagonal takes twice the rounds, but a block's wait
+// is hidden by half as many others.  ms per sweep, launch per diagonal / one
+// launch, by items per diagonal: FP32 squares of 64 (171) 0.211 / 0.130, 256 (650)
+// 1.129 / 0.668, 512 (1290) 3.51 / 2.37, 16 films of 64 (2730) 0.740 / 0.703, 24 of
+// them (4100) 1.000 / 1.028, 24 films of 30 to 200 cells a side (1300) 2.19 / 2.19, 200
+// of 16 to 40 (3200) 1.10 / 1.23; FP64 97 x 83 (50) 0.343 / 0.142, 128^2 (661) 0.952 /
+// 0.640, (1486) 1.65 / 1.41, (1982) 2.00 / 1.86, 512^2 (1290) 5.82 / 4.67, 16 films of 64
+// (2730) 1.41 / 1.37, 24 of them (4100) 2.01 / 2.05.
 bool one_launch(const bte_problem *p)
 {
     if (!reg2d(p) || !p->queue_ok) return false;

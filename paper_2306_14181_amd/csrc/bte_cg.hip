@@ -79,16 +79,6 @@ __device__ inline bool ll_wait(const unsigned long long *p, unsigned tag, const 
     }
 }
 
-// sum over the 16 lanes of a row, in every lane of the row
-__device__ inline double row_sum(double v)
-{
-    v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
-    v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
-    v += dpp_f64<0x141>(v);   // row_half_mirror
-    v += dpp_f64<0x140>(v);   // row_mirror
-    return v;
-}
-
 // sum of the block's rows of 16 lanes, in every lane of a wave
 constexpr int kRows = kCgThreads / 16;
 __device__ inline void block_total(const double *srow, int lane, double (&v)[3])

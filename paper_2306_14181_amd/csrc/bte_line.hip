@@ -23,16 +23,6 @@ constexpr int kFold = 4;         // groups of lanes of a folded block
 constexpr int kStepThreads = 512;
 constexpr int kStepCells = 64;   // most cells of an explicit step's block
 
-// Sum over each row of 16 lanes, in every lane of the row.
-__device__ inline double row_sum(double v)
-{
-    v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
-    v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
-    v += dpp_f64<0x141>(v);   // row_half_mirror
-    v += dpp_f64<0x140>(v);   // row_mirror
-    return v;
-}
-
 // What a thread needs to know of a cell of the line, staged per block.
 struct LineCell {
     int cell;        // global cell, -1 outside the line

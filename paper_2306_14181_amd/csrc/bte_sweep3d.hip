@@ -23,13 +23,13 @@
 // does not spill (1 x 1 x 300 x 20 480 lanes FP64: 1.25 ms with 4 x 4, 0.68 with
 // single columns at four wavefronts per SIMD, 0.49 at two; 5 x 5 x 100: 2.08, 1.33
 // and 1.01).
-// What bounds it: a column's step takes about 2 800 cycles with 16 wavefronts
-// per compute unit, 1 650 of them vector issue (100 instructions per cell and
-// wavefront) and the rest the step's own latency (LDS, branches, scalar work),
-// so the tile's columns keep in step and the stencil rows that they share come
-// from the near caches (10 GB fetched per sweep of the 48^3 block instead of 18
-// GB with independent columns on a hyperplane of 97, where a launch was two
-// rounds of 16-cell walks, the second nearly empty).  48^3, 96 directions x 40
+// What bounds it: a wavefront lives about 3 100 cycles per cell with 16 of them
+// per compute unit, 1 650 of these vector issue (103 instructions per cell, beside
+// 72 scalar and 11 LDS) and the rest the step's own latency (LDS, branches), so the
+// tile's columns keep in step and the stencil rows that they share come from the
+// near caches (5.2 GB fetched per sweep of the 48^3 block instead of 18.6 GB with
+// independent columns on a hyperplane of 97, where a launch was two rounds of
+// 16-cell walks, the second nearly empty).  48^3, 96 directions x 40
 // bands FP32: 4.52 -> 3.41 ms per sweep (floor 0.71 ms, reading and writing the
 // state); 24^3, 48 x 20 FP64: 0.95 -> 0.36 ms.
 // Per-cell values (geometry codes, T_L, scattering rate, source, pending

@@ -249,6 +249,16 @@ __device__ inline double dpp_f64(double v)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Sum over each row of 16 lanes, in every lane of the row.
+__device__ inline double row_sum(double v)
+{
+    v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
+    v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
+    v += dpp_f64<0x141>(v);   // row_half_mirror
+    v += dpp_f64<0x140>(v);   // row_mirror
+    return v;
+}
+
 // Limited or least-squares slope difference of the fast path: face value
 // difference f(i) - f(i-1) along the flow with all three neighbours present.
 template <typename T, int LIM>
