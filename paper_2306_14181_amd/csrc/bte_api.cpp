@@ -916,32 +916,37 @@ bool quad_step(const bte_problem *p)
 }
 
 // p->quad_walls, of the two octants whose signs are all equal (the others are
-// their mirror images along an axis)
+// their mirror images along an axis), on an odd number of planes apart from one
+// another in large problems
 void count_quad_walls(bte_problem *p)
 {
-    double off = 0, all = 0;
+    const int skip = p->nc < 1 << 17 ? 1 : (p->nc >> 16) | 1;
+    long long off = 0, all = 0;
     for (const Film &fm : p->films)
-        for (int sg = -1; sg <= 1; sg += 2)
-            for (int z = 0; z < fm.n[2]; ++z)
-                for (int y = 0; y < fm.n[1]; y += 2)
-                    for (int x = 0; x < fm.n[0]; x += 2) {
-                        bool in[2] = {true, true}, solid = true;
-                        for (int q = 0; q < 4; ++q) {
-                            const int cx = std::min(x, fm.n[0] - 2) + (q & 1), cy = std::min(y, fm.n[1] - 2) + (q >> 1);
-                            const int c = fm.cell0 + cx + fm.n[0] * (cy + fm.n[1] * z);
-                            solid = solid && (p->code[c] & kSolidBit);
-                            for (int a = 0; a < 2; ++a) {
-                                const uint32_t ab = axis_bits(p->code[c], a);
-                                const bool hu = side_is_cell(ab, -sg);
-                                const int u = hu ? p->nb[(size_t)face_of(a, -sg) * p->nc + c] : -1;
-                                in[a] = in[a] && hu && side_is_cell(ab, sg) && u >= 0 &&
-                                        side_is_cell(axis_bits(p->code[u], a), -sg);
+        for (int z = 0; z < fm.n[2]; z += skip)
+            for (int y = 0; y < fm.n[1]; y += 2)
+                for (int x = 0; x < fm.n[0]; x += 2) {
+                    const int c0 = fm.cell0 + std::min(x, fm.n[0] - 2) + fm.n[0] * (std::min(y, fm.n[1] - 2) + fm.n[1] * z);
+                    unsigned in = 15, solid = 1;   // bit a: octant of negative signs; bit 2 + a: of positive ones
+                    for (int q = 0; q < 4; ++q) {
+                        const int c = c0 + (q & 1) + fm.n[0] * (q >> 1);
+                        const uint32_t code = p->code[c];
+                        if (!(code & kSolidBit)) solid = 0;
+                        for (int a = 0; a < 2 && solid; ++a) {
+                            const uint32_t ab = axis_bits(code, a);
+                            if (!side_is_cell(ab, -1) || !side_is_cell(ab, 1)) {
+                                in &= ~(5u << a);
+                                continue;
                             }
+                            const int lo = p->nb[(size_t)face_of(a, -1) * p->nc + c], hi = p->nb[(size_t)face_of(a, 1) * p->nc + c];
+                            if (!side_is_cell(axis_bits(p->code[hi], a), 1)) in &= ~(1u << a);
+                            if (!side_is_cell(axis_bits(p->code[lo], a), -1)) in &= ~(4u << a);
                         }
-                        off += solid ? !in[0] + !in[1] : 2;
-                        all += 1;
                     }
-    p->quad_walls = off / all;
+                    off += solid ? 4 - __builtin_popcount(in) : 4;
+                    all += 2;
+                }
+    p->quad_walls = (double)off / (double)all;
 }
 
 // Per geometry: the wall emission conductance of the correction operator
@@ -1017,6 +1022,7 @@ void build_cg_plan(bte_problem *p)
     // numbers: tile by tile of every geometry
     std::vector<int> num(nc);
     p->cg_cell.clear();
+    p->cg_cell.reserve(nc);
     for (const Film &fm : p->films) {
         const int tx = p->dim == 1 ? fm.n[0] : p->dim == 2 ? 32 : 8, ty = p->dim == 2 ? 16 : 8, tz = 8;
         for (int z0 = 0; z0 < fm.n[2]; z0 += tz)
