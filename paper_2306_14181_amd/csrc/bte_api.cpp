@@ -694,7 +694,7 @@ void choose_default_tiles(bte_problem *p)
             int edge, cap;              // columns along x and y, blocks that the chip holds
             double cell, fill, start;   // a cell's time on an empty chip, its growth on a full one, cells of the start
         };
-        static const Form f32[] = {{4, 256, 1.0, 0.45, 3.1}, {2, 1024, 0.91, 0.45, 3.5}, {1, 4096, 0.645, 1.22, 3.9}};
+        static const Form f32[] = {{4, 256, 1.0, 0.45, 3.1}, {2, 1024, 0.92, 0.5, 3.5}, {1, 4096, 0.645, 1.22, 3.9}};
         static const Form f64[] = {{4, 256, 1.0, 0.679, 4.64}, {2, 768, 0.697, 0.576, 2.87}, {1, 3072, 0.56, 1.454, 1.4}};
         const double launch = p->esize() == 4 ? 2.9 : 2.05;
         double best = 0;
