@@ -401,7 +401,9 @@ bte_status bte_set_tiles(bte_problem *p, int kind, const int *tile);
  * sweeps (or steps) with each candidate after one untimed run, keep the
  * fastest and report every candidate in entries[0 .. *n) (at most cap).
  * The two sweep kinds are one choice: the fastest candidate of either is
- * kept (with its launch form) and is the one marked chosen.
+ * kept (with its launch form) and is the one marked chosen.  In 1D the forward
+ * sweep has no tiles: the shapes are the transposed sweep's, timed if the
+ * problem has an adjoint; else every candidate times the forward sweep.
  * e_scratch: device buffer of bte_num_unknowns() elements of the problem's
  * precision, overwritten (it is the input state of the timed runs); the
  * diffuse-wall records, T_L and pending-correction fields are cleared.

@@ -2722,7 +2722,9 @@ template <typename T> hipError_t tune_run(bte_problem *p, int kind, const T *ein
         if (kind == BTE_TUNE_TRANSIENT)   // T_L of the new state into scratch
             return launch_transient1d<T>(d, ein, eout, p->TL, p->part, p->din, p->d_titems,
                                          (int)p->titems.size() / p->noct, p->tdim_tr.x, 0.0, p->ctl.dt, s);
-        // the forward sweep has no tiles: the shape is the transposed sweep's
+        // the forward sweep has no tiles: the shape is the transposed sweep's, and
+        // where no adjoint is asked for, every candidate is the forward sweep
+        if (!p->ctl.adjoint) return sweep_launches<T>(p, ein, eout, s, false);
         for (size_t dg = 0; dg + 1 < p->diag_off.size(); ++dg) {
             const int i0 = p->diag_off[dg], cnt = p->diag_off[dg + 1] - i0;
             const hipError_t r = launch_sweep_adj<T>(d, ein, eout, p->TL, p->din, p->d_items, i0, cnt, p->tdim,

@@ -86,3 +86,15 @@ def test_steps(B, prec, ns, ends, lim):
         prob.transient_step(e, 3, 0.0, (1e-12, 2e-12))
         ref = np.concatenate([O.transient(c, h, 3, dt, 0.0, (1e-12, 2e-12))[0] for c, h in zip(cases, host)])
         assert np.abs(e.double().cpu().numpy() - ref).max() <= (1e-11 if f64 else 1e-5) * np.abs(ref).max(), tile
+
+
+def test_autotune_times_the_sweep_that_runs(B):
+    # without an adjoint the forward sweep, which has no tiles; the transposed sweep of 1000 cells x 1280 lanes takes
+    # 13 times as long
+    prob, _, e, _ = problem(B, [line(1000, (T, T), False)], 20, 64, precision=B.F64, scheme=B.SEQUENTIAL, max_iter=50,
+                            residual_temp=0.0, residual_flux=0.0)
+    ent = [x for x in prob.autotune(reps=20) if x["kind"] == B.TUNE_SWEEP]
+    prob.steady_solve(e, init=False, allow_not_converged=True)
+    st = prob.steady_solve(e, init=False, allow_not_converged=True)
+    assert len(ent) > 1 and sum(x["chosen"] for x in ent) == 1
+    assert max(x["ms"] for x in ent) < 4.0 * st["ms_sweep"] / st["iters"], (ent, st["ms_sweep"] / st["iters"])
