@@ -826,6 +826,7 @@ void build_schedule(bte_problem *p)
     p->tile_cap = tile_cap_of(p, lds_tdim(p));
     p->tile_cap_tr = tile_cap_of(p, p->tdim_tr);
     p->items.clear();
+    p->items.reserve(recs.size());
     p->diag_off.assign(maxd + 2, 0);
     for (auto &r : recs) {
         p->items.push_back(r.it);
@@ -834,6 +835,7 @@ void build_schedule(bte_problem *p)
     for (int d = 0; d <= maxd; ++d) p->diag_off[d + 1] += p->diag_off[d];
     p->items2.clear();
     if (reg2d(p)) {
+        p->items2.reserve(p->items.size());
         for (const SweepItem &it : p->items) {
             const Film &fm = p->films[it.film];
             Sweep2Item q{};
