@@ -1023,53 +1023,56 @@ void build_cg_plan(bte_problem *p)
     const int cpb = kCgThreads * R;
     // numbers: tile by tile of every geometry
     std::vector<int> num(nc);
-    p->cg_cell.clear();
-    p->cg_cell.reserve(nc);
+    p->cg_cell.resize(nc);
+    int at = 0;
     for (const Film &fm : p->films) {
         const int tx = p->dim == 1 ? fm.n[0] : p->dim == 2 ? 32 : 8, ty = p->dim == 2 ? 16 : 8, tz = 8;
         for (int z0 = 0; z0 < fm.n[2]; z0 += tz)
             for (int y0 = 0; y0 < fm.n[1]; y0 += ty)
-                for (int x0 = 0; x0 < fm.n[0]; x0 += tx)
+                for (int x0 = 0; x0 < fm.n[0]; x0 += tx) {
+                    const int x1 = std::min(fm.n[0], x0 + tx);
                     for (int z = z0; z < std::min(fm.n[2], z0 + tz); ++z)
-                        for (int y = y0; y < std::min(fm.n[1], y0 + ty); ++y)
-                            for (int x = x0; x < std::min(fm.n[0], x0 + tx); ++x) {
-                                const int c = fm.cell0 + x + fm.n[0] * (y + fm.n[1] * z);
-                                num[c] = (int)p->cg_cell.size();
-                                p->cg_cell.push_back(c);
+                        for (int y = y0; y < std::min(fm.n[1], y0 + ty); ++y) {
+                            const int row = fm.cell0 + fm.n[0] * (y + fm.n[1] * z);
+                            for (int c = row + x0; c < row + x1; ++c) {
+                                num[c] = at;
+                                p->cg_cell[at++] = c;
                             }
+                        }
+                }
     }
-    p->cg_lidx.assign((size_t)nf * nc, 0);
+    p->cg_lidx.resize((size_t)nf * nc);
     p->cg_gptr.assign(nblk + 1, 0);
-    std::vector<int> mark(nc, -1), place(nc, 0);   // block that holds a cell as a ghost, and where
-    std::vector<char> sent(nc, 0);
+    std::vector<unsigned> held(nc, 0u);   // last block that holds a cell as a ghost (counted from 1) and its place there
     int most = 0;
     for (int blk = 0; blk < nblk; ++blk) {
-        const int i0 = blk * cpb, i1 = std::min(nc, i0 + cpb);
+        const int i0 = blk * cpb, n = std::min(nc - i0, cpb);
+        const int *cell = p->cg_cell.data() + i0;
         const int first = (int)p->cg_gid.size();
-        for (int f = 0; f < nf; ++f)
-            for (int i = i0; i < i1; ++i) {
-                const int j = p->nb[(size_t)f * nc + p->cg_cell[i]];
-                int l = i - i0;
-                if (j >= 0 && num[j] >= i0 && num[j] < i1) {
-                    l = num[j] - i0;
-                } else if (j >= 0) {
-                    if (mark[j] != blk) {
-                        mark[j] = blk;
-                        place[j] = (int)p->cg_gid.size() - first;
+        for (int f = 0; f < nf; ++f) {
+            const int *nb = p->nb.data() + (size_t)f * nc;
+            unsigned short *to = p->cg_lidx.data() + (size_t)f * nc + i0;
+            for (int i = 0; i < n; ++i) {
+                const int j = nb[cell[i]];
+                int l = j >= 0 ? num[j] - i0 : i;
+                if (l < 0 || l >= n) {
+                    unsigned &h = held[j];
+                    if (h >> 16 != (unsigned)blk + 1) {
+                        const int place = (int)p->cg_gid.size() - first;
+                        if (cpb + place > 0x7fff) return;   // no room in 15 bits (nor in LDS)
+                        h = (unsigned)(blk + 1) << 16 | (unsigned)place;
                         p->cg_gid.push_back(j);
-                        sent[num[j]] = 1;
                     }
-                    l = cpb + place[j];
+                    l = cpb + (int)(h & 0xffffu);
                 }
-                if (l > 0x7fff) return;   // no room in 15 bits (nor in LDS)
-                p->cg_lidx[(size_t)f * nc + i] = (unsigned short)l;
+                to[i] = (unsigned short)l;
             }
+        }
         p->cg_gptr[blk + 1] = (int)p->cg_gid.size();
         most = std::max(most, (int)p->cg_gid.size() - first);
     }
     if (cg_solve_smem(R, most) > 150 * 1024) return;
-    for (int i = 0; i < nc; ++i)
-        if (sent[i]) p->cg_lidx[i] |= 0x8000u;
+    for (int j : p->cg_gid) p->cg_lidx[num[j]] |= 0x8000u;   // cells that are sent
     p->cg_R = R;
     p->cg_nblk = nblk;
     p->cgplan.max_ghost = most;
